@@ -59,6 +59,10 @@ using Fn64 = void (*)(bool, AxMode, const AxArgs<double> &, const double *, cons
 #define SEM_AX_FUSED_MAX_BLOCKS 2048
 #endif
 constexpr int64_t kAxFusedMaxBlocks = SEM_AX_FUSED_MAX_BLOCKS;
+// FP64 blocks are smaller (one element at N = 7, 9, 10 and 11): at 12 M points
+// twice the blocks run the FP64 iteration 0-7% faster (N = 9 on the fly 233 ->
+// 217 us, N = 11 stored 349 -> 323 us); FP32 gains nothing steady from it.
+constexpr int64_t kAxFusedMaxBlocks64 = 2 * kAxFusedMaxBlocks;
 // the matrix-core form: blocks of one wave (N = 7; measured best of 8192,
 // 16384 and 32768) and of two waves (N = 9: 1536, the blocks resident at
 // once at 3 waves per SIMD and 6 blocks per CU, ahead of 3072 and 4096 at
@@ -79,9 +83,9 @@ constexpr int64_t kAxMfma2MaxBlocks = SEM_AX_MFMA2_MAX_BLOCKS;
 #endif
 constexpr int64_t kAxPlainMaxBlocks = SEM_AX_PLAIN_MAX_BLOCKS;
 
-static int64_t ax_grid(int64_t ntiles, AxMode mode, bool mfma, int threads = 64) {
-    const int64_t cap =
-        mfma ? (threads == 64 ? kAxMfmaMaxBlocks : kAxMfma2MaxBlocks) : kAxFusedMaxBlocks;
+static int64_t ax_grid(int64_t ntiles, AxMode mode, bool fp64, bool mfma, int threads = 64) {
+    const int64_t cap = mfma ? (threads == 64 ? kAxMfmaMaxBlocks : kAxMfma2MaxBlocks)
+                             : (fp64 ? kAxFusedMaxBlocks64 : kAxFusedMaxBlocks);
     if (mode == AxMode::CgFused && ntiles > cap) return cap;
     if (mode != AxMode::CgFused && kAxPlainMaxBlocks > 0 && ntiles > kAxPlainMaxBlocks)
         return kAxPlainMaxBlocks;
@@ -97,12 +101,16 @@ static const Fn64 kFn64[kMaxOrder + 1] = {nullptr,        ax_order_1_f64, ax_ord
                                           ax_order_6_f64, ax_order_7_f64, ax_order_8_f64,
                                           ax_order_9_f64, ax_order_10_f64, ax_order_11_f64};
 
-// Default elements per block: fill a multiple of 64 lanes with (i, j)
-// columns as tightly as possible, at most 512 threads and 64 KiB of LDS.
+// Default elements per block, at most 512 threads and 64 KiB of LDS: a
+// multiple of 64 lanes filled as tightly as possible with (i, j) columns,
+// except where one element per block measured faster because its barriers
+// hold back fewer waves (3 M points, plain operator on the fly: FP64 N = 9
+// 39.6 us with three elements, 29.6 with one; FP32 N = 11 32.2 us with two,
+// 21.3 with one; FP64 N = 7, whose elements are one wave each, 24.1 / 22.9).
 // The autotuner (sem_ax_shape_set) overrides them per order, precision
 // and geometric-factor form.
-static const int kEpb32[kMaxOrder + 1] = {0, 64, 28, 16, 10, 7, 5, 4, 3, 2, 2, 3};
-static const int kEpb64[kMaxOrder + 1] = {0, 64, 28, 16, 10, 7, 5, 4, 3, 3, 2, 1};
+static const int kEpb32[kMaxOrder + 1] = {0, 64, 28, 16, 5, 7, 5, 4, 3, 1, 1, 1};
+static const int kEpb64[kMaxOrder + 1] = {0, 64, 28, 16, 5, 7, 5, 1, 3, 1, 1, 1};
 
 // Process-wide tile shapes set by the autotuner (0: built-in default),
 // indexed [on-the-fly][fp64][N], and a generation counter that tells cached
@@ -163,7 +171,7 @@ AxShape ax_shape(int N, bool fp64, bool otf, int epb_override) {
     // the next tile's r, p and vertices in LDS)
     const bool staged = !fp64 && P3 % 4 == 0;
     auto lds = [&](int q) {
-        return 2 * tsz * (size_t)q * P3 + (staged ? 8 * (size_t)q * P3 + 96 * (size_t)q : 0);
+        return 2 * tsz * (size_t)q * ax_tile_stride(P) + (staged ? 8 * (size_t)q * P3 + 96 * (size_t)q : 0);
     };
     while (epb > 1 && (((epb * P2 + 63) / 64) * 64 > 512 || lds(epb) > 65536)) --epb;
     AxShape s;
@@ -189,7 +197,7 @@ void launch_ax<float>(const Mesh &m, bool otf, AxMode mode, AxArgs<float> a, hip
     if (!otf) a.G = m.G32;
     const int64_t ntiles = (m.E + sh.epb - 1) / sh.epb;
     kFn32[m.N](otf, mode, a, m.h_D.data(), m.h_xi.data(), m.h_w.data(),
-               ax_grid(ntiles, mode, sh.mfma, sh.threads), s);
+               ax_grid(ntiles, mode, false, sh.mfma, sh.threads), s);
     check_hip(hipGetLastError(), "ax kernel launch (fp32)");
 }
 
@@ -208,7 +216,7 @@ void launch_ax<double>(const Mesh &m, bool otf, AxMode mode, AxArgs<double> a, h
     if (!otf) a.G = m.G64;
     const int64_t ntiles = (m.E + sh.epb - 1) / sh.epb;
     kFn64[m.N](otf, mode, a, m.h_D.data(), m.h_xi.data(), m.h_w.data(),
-               ax_grid(ntiles, mode, false), s);
+               ax_grid(ntiles, mode, true, false), s);
     check_hip(hipGetLastError(), "ax kernel launch (fp64)");
 }
 
@@ -224,7 +232,7 @@ void ax_batch_desc(const Mesh &m, bool otf, AxArgs<float> &a) {
     a.vert = m.vert32;
     a.edge = m.edge32;
     a.G = otf ? nullptr : m.G32;
-    a.vgrid = ax_grid((m.E + sh.epb - 1) / sh.epb, AxMode::CgFused, sh.mfma, sh.threads);
+    a.vgrid = ax_grid((m.E + sh.epb - 1) / sh.epb, AxMode::CgFused, false, sh.mfma, sh.threads);
 }
 
 void launch_ax_batch(int N, bool otf, bool mfma, bool stream, const AxArgs<float> *descs,
@@ -250,7 +258,7 @@ int64_t cg_footprint(const Mesh &m, int tsz, bool table_free) {
 
 int64_t ax_blocks(const Mesh &m, bool fp64, bool otf, int epb_override) {
     const AxShape sh = ax_shape(m.N, fp64, otf, epb_override);
-    return ax_grid((m.E + sh.epb - 1) / sh.epb, AxMode::CgFused, sh.mfma, sh.threads);
+    return ax_grid((m.E + sh.epb - 1) / sh.epb, AxMode::CgFused, fp64, sh.mfma, sh.threads);
 }
 
 }  // namespace sem

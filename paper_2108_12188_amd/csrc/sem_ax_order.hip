@@ -21,10 +21,11 @@
 //     vector update), which already holds the point codes.
 //
 // Work decomposition (gfx950, 64-lane waves): a block holds `epb` elements;
-// one thread owns one (i, j) column of one element and walks the k
-// direction in registers.  The i- and j-direction contractions read the
-// element tile from LDS; the k-direction contraction is register-only with
-// D entries that are wave-uniform (kernel-argument / scalar registers).
+// one thread owns one (i, j) column of one element, one i-pencil and one
+// j-pencil.  Each direction is a P x P product with the lane's own vector:
+// the k direction in the column's registers, i and j on pencils exchanged
+// through LDS tiles; the D entries are wave-uniform (kernel-argument /
+// scalar registers).
 #include "sem_internal.h"
 #include "sem_reduce.h"
 
@@ -37,16 +38,6 @@ namespace {
 
 constexpr int kOrder = SEM_ORDER;
 constexpr int kP = kOrder + 1;
-
-// Precomputed form: issue the loads of all 6 P factors of a column before
-// the first barrier (more loads in flight per wave) when the registers allow.
-#ifndef SEM_AX_PREFETCH_G
-#define SEM_AX_PREFETCH_G 0
-#endif
-template <typename T>
-constexpr bool prefetch_g() {
-    return SEM_AX_PREFETCH_G && 6 * kP * sizeof(T) <= 6 * 8 * 4;
-}
 
 // The precomputed factors are read once per application and are the largest
 // stream (24 B of 32 per point in FP32): non-temporal loads keep them from
@@ -61,6 +52,13 @@ __device__ __forceinline__ T load_g(const T *p) {
     if constexpr (SEM_AX_G_STREAM && sizeof(T) == 4) return __builtin_nontemporal_load(p);
     else return *p;
 }
+
+// Precomputed form: the loads of all 6 P factors of a column go out before
+// the gradient where the registers allow it (FP32, N <= 6, 3 M points, plain
+// operator: N = 5 22.6 -> 20.0 us, N = 6 24.6 -> 22.1 us; N = 8 22.2 us
+// either way, and FP64 runs at the copy rate without it).
+template <typename T>
+constexpr bool prefetch_g() { return sizeof(T) == 4 && kP <= 7; }
 
 // Kernel-argument copy of the basis: indexed only with compile-time
 // constants, so every access is a scalar load.
@@ -120,8 +118,8 @@ struct ColumnGeom {
 // along eta (v2 - v0, v3 - v1, v6 - v4, v7 - v5), along gamma (v4 - v0,
 // v5 - v1, v6 - v2, v7 - v3); ed[t * 3 + d].  The host builds the same
 // FP32 array per element (Mesh::vedge32) with the same subtractions.
-template <typename T>
-__device__ __forceinline__ void element_edges(const T *__restrict__ ve, T (&ed)[36]) {
+template <typename T, typename VertPtr>
+__device__ __forceinline__ void element_edges(VertPtr ve, T (&ed)[36]) {
     constexpr int kA[12] = {1, 3, 5, 7, 2, 3, 6, 7, 4, 5, 6, 7};
     constexpr int kB[12] = {0, 2, 4, 6, 0, 1, 4, 5, 0, 1, 2, 3};
 #pragma unroll
@@ -172,9 +170,8 @@ __device__ __forceinline__ ColumnGeom<T> column_geom_edges(EdgePtr ed, T xi_i, T
     return g;
 }
 
-template <typename T>
-__device__ __forceinline__ ColumnGeom<T> column_geom(const T *__restrict__ ve, T xi_i, T eta_j,
-                                                     T wij) {
+template <typename T, typename VertPtr>
+__device__ __forceinline__ ColumnGeom<T> column_geom(VertPtr ve, T xi_i, T eta_j, T wij) {
     T ed[36];
     element_edges<T>(ve, ed);
     return column_geom_edges<T>(ed, xi_i, eta_j, wij);
@@ -224,11 +221,16 @@ __device__ __forceinline__ double block_sum(double v) {
     return block_sum_f64(v, red);
 }
 
-// FP32 kernels up to N = 7 are held to 128 VGPRs (4 waves per SIMD): the
-// on-the-fly form is latency-bound below that occupancy.  Higher orders and
-// FP64 keep their registers (capping them spills).
-template <typename T>
-constexpr int ax_min_waves() { return (sizeof(T) == 4 && kP <= 8) ? 4 : 1; }
+// Waves per SIMD the registers are held to.  FP32 up to N = 7: 4 (the
+// on-the-fly form is latency-bound below that occupancy).  FP64: 3 with
+// stored factors (N = 11, whose 178 registers leave 2: 53 -> 44 us at 3 M
+// points) and up to N = 5 (on the fly: 26.6 -> 23.2 us); the higher orders'
+// on-the-fly geometry would spill there (N = 9: 29 -> 44 us).
+template <typename T, bool OTF>
+constexpr int ax_min_waves() {
+    if (sizeof(T) == 4) return kP <= 8 ? 4 : 1;
+    return (!OTF || kP <= 6) ? 3 : 1;
+}
 
 // FP32 CG-fused tiles stage the next tile's r, p and vertices in LDS with
 // gfx950's direct global-to-LDS loads (16 bytes per lane, no registers held
@@ -245,7 +247,7 @@ __host__ __device__ constexpr bool ax_dma() {
 template <typename T, bool OTF, bool FUSED>
 __host__ __device__ constexpr size_t ax_lds_bytes(int epb) {
     constexpr size_t P3 = (size_t)kP * kP * kP;
-    return 2 * sizeof(T) * epb * P3 +
+    return 2 * sizeof(T) * epb * (size_t)ax_tile_stride(kP) +
            (ax_dma<T, FUSED>() ? 2 * sizeof(float) * epb * P3 + (OTF ? 24 * 4 * (size_t)epb : 0)
                                : 0);
 }
@@ -326,9 +328,77 @@ __device__ __forceinline__ void dma_to_lds_nt(const float *src, float *dst, int 
     dma_to_lds<NT ? kCpolNt : 0>(src, dst, nf, nwave);
 }
 
+// Element tile in LDS: point (i, j, k) at i + kRow j + kSlab k, elements of
+// a block kTile apart.  The strides keep a column access (lanes over (i, j)),
+// an i-pencil access (lanes over (j, k)) and a j-pencil access (lanes over
+// (i, k)) spread over the 32 four-byte banks: odd P needs no padding, even P
+// would meet 2- to 8-way conflicts on the pencils without it.
+constexpr int kRow = kP == 8 ? 9 : kP;
+constexpr int kSlabPad[kMaxP + 1] = {0, 0, 1, 0, 3, 0, 1, 0, 0, 0, 5, 0, 1};
+constexpr int kSlab = kRow * kP + kSlabPad[kP];
+constexpr int kTile = ax_tile_stride(kP);
+static_assert(kTile >= kSlab * (kP - 1) + kRow * (kP - 1) + kP, "tile stride too small");
+// The P^2 columns of every element lie in one wave: the exchanges of an
+// element then need no barrier.
+constexpr bool kWaveLocal = 64 % (kP * kP) == 0;
+
+// One element per wave: its vertices go through scalar registers.
+constexpr bool kWaveElem = kP * kP == 64;
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// LDS exchange between the threads of an element: a wave's LDS accesses
+// complete in issue order, so one wave only needs the compiler held back.
+__device__ __forceinline__ void elem_sync() {
+    if constexpr (kWaveLocal) {
+        __asm__ volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
+        __asm__ volatile("" ::: "memory");
+    } else {
+        lds_barrier();
+    }
+}
+
+// A matrix that every lane reads at one address, in scalar registers
+// (constant address space; read-only in the kernel).
+template <typename T>
+using kconst = __attribute__((address_space(4))) const T;
+
+// Up to this many 4-byte scalar registers the matrix stays resident;
+// a larger one is read again for each product (the scalar cache holds it),
+// because the compiler would spill it to vector lanes, two reads per entry.
+constexpr int kResidentScalars = 40;
+
+// out = M x of the lane's own vector; mt holds M's columns, entry M[r][l] at
+// mt[l P + r].  One fused multiply-add per step in the order l = 0 .. N, the
+// order of the matrix-core form, which gives the same bits.
+template <typename T>
+__device__ __forceinline__ void apply_m(const T *mt, const T (&x)[kP], T (&out)[kP]) {
+    kconst<T> *m = (kconst<T> *)mt;
+    if constexpr (kP * kP * (int)sizeof(T) / 4 > kResidentScalars)
+        __asm__ volatile("" : "+s"(m));      // a fresh read: not kept across products
+#pragma unroll
+    for (int r = 0; r < kP; ++r) out[r] = T(0);
+#pragma unroll
+    for (int l = 0; l < kP; ++l)
+#pragma unroll
+        for (int r = 0; r < kP; ++r) out[r] += m[l * kP + r] * x[l];
+}
+
 // Tiles vb, vb + vgrid, vb + 2 vgrid, ... of one problem; in the fused mode
 // the block's partial goes to a.partial[vb].  Every thread of the block
 // calls it.
+//
+// Bound by LDS and VALU issue on the fly, by HBM with stored factors.  A
+// thread takes whole pencils, so a P-vector costs P LDS reads instead of
+// the P^2 a column would read for its P outputs, and D needs no vector
+// registers (a row and a column of D and D^T per thread before: 4 P values).
+// Plain operator on the fly, 3 M points, column form -> pencil form: FP64
+// N = 7 33.1 -> 22.9 us, N = 9 61.4 -> 29.0, N = 11 89.0 -> 40.0; FP32 N = 8
+// 20.1 -> 15.4, N = 11 52.8 -> 20.6 us; the same bits.
 template <typename T, bool OTF, bool FUSED, bool NT = false>
 __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk, int64_t ntiles,
                                         int64_t vb, int64_t vgrid) {
@@ -336,12 +406,12 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
     constexpr bool kDma = ax_dma<T, FUSED>();
     extern __shared__ __align__(16) unsigned char lds_raw[];
     T *const sA = reinterpret_cast<T *>(lds_raw);
-    T *const sB = sA + a.epb * P3;
-    // staging (kDma): r and p of a tile, then its vertices; x goes to sA
-    float *const sR = reinterpret_cast<float *>(sB + a.epb * P3);
+    T *const sB = sA + a.epb * kTile;
+    // staging (kDma): r and p of a tile, then its vertices; x goes to sB
+    float *const sR = reinterpret_cast<float *>(sB + a.epb * kTile);
     float *const sP = sR + a.epb * P3;
     float *const sV = sP + a.epb * P3;
-    float *const sX = reinterpret_cast<float *>(sA);
+    float *const sX = reinterpret_cast<float *>(sB);
 
     // the CG state in one round of loads: stop, beta, the lagged x step
     T beta = T(0);
@@ -359,22 +429,18 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
 
     const int t = threadIdx.x;
     const int el = t / P2;
-    const int col = t - el * P2;
+    const int c = t - el * P2;
     const int nwave = (a.epb * P2 + 63) >> 6;   // the launch's block size in waves
-    const int i = col % P;
-    const int j = col / P;
-    T *const sa = sA + el * P3;
-    T *const sb = sB + el * P3;
+    // the thread's column (i, j) = (c % P, c / P), its i-pencil (j, k) and
+    // its j-pencil (i, k) with the same two indices
+    const int i = c % P;
+    const int j = c / P;
+    T *const sa = sA + el * kTile;
+    T *const sb = sB + el * kTile;
+    const int col = i + kRow * j;          // + kSlab k
+    const int ipen = kRow * i + kSlab * j;  // + l
+    const int jpen = i + kSlab * j;         // + kRow l
 
-    // per-lane rows of D and D^T for the i and j contractions
-    T Di[P], Dj[P], DiT[P], DjT[P];
-#pragma unroll
-    for (int l = 0; l < P; ++l) {
-        Di[l] = a.D[i * P + l];
-        Dj[l] = a.D[j * P + l];
-        DiT[l] = a.Dt[i * P + l];
-        DjT[l] = a.Dt[j * P + l];
-    }
     constexpr bool strm = FUSED && NT;   // p and x non-temporal
     // edge-array slots of the column (edge_slot): base ecb (-1 off the
     // border) holds k = 0, ecb + 1 holds k = N, and corner columns keep
@@ -426,7 +492,7 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
     for (int64_t tile = vb; tile < ntiles; tile += vgrid) {
         const int64_t e = tile * a.epb + el;
         const bool valid = (el < a.epb) && (e < a.E);
-        const int64_t base = e * P3 + col;   // global index of (i, j, k=0)
+        const int64_t base = e * P3 + c;     // global index of (i, j, k=0)
         T *const wep = (FUSED && a.wedge && valid && ecb >= 0)
                            ? a.wedge + e * edge_slots(kOrder) + ecb
                            : nullptr;
@@ -439,107 +505,140 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
         T uc[P];
         if (valid) {
             if constexpr (kDma) {
-                const float *const rr = sR + el * P3 + col;
-                const float *const pp = sP + el * P3 + col;
+                const float *const rr = sR + el * P3 + c;
+                const float *const pp = sP + el * P3 + c;
 #pragma unroll
                 for (int k = 0; k < P; ++k) uc[k] = rr[k * P2] + beta * pp[k * P2];
 #pragma unroll
                 for (int k = 0; k < P; ++k) store_nt<strm>(a.p + base + k * P2, uc[k]);
                 if (xlag) {
-                    // x was staged in this thread's own slots of the tile,
-                    // which the p-update below overwrites
-                    const float *const xx = sX + el * P3 + col;
+                    // x was staged over the second tiles
+                    const float *const xx = sX + el * P3 + c;
 #pragma unroll
                     for (int k = 0; k < P; ++k)
                         store_nt<strm>(a.x + base + k * P2, xx[k * P2] + aprev * pp[k * P2]);
                 }
             } else if constexpr (FUSED) {
+                T pold[P];
 #pragma unroll
                 for (int k = 0; k < P; ++k) {
-                    const T r = a.u[base + k * P2];
-                    const T pold = load_nt<strm>(a.p + base + k * P2);
-                    uc[k] = r + beta * pold;
-                    if (xlag)
-                        store_nt<strm>(a.x + base + k * P2,
-                                load_nt<strm>(a.x + base + k * P2) +
-                                    aprev * pold);
+                    uc[k] = a.u[base + k * P2];
+                    pold[k] = load_nt<strm>(a.p + base + k * P2);
+                }
+                if (xlag) {
+                    T xv[P];
+#pragma unroll
+                    for (int k = 0; k < P; ++k) xv[k] = load_nt<strm>(a.x + base + k * P2);
+#pragma unroll
+                    for (int k = 0; k < P; ++k)
+                        store_nt<strm>(a.x + base + k * P2, xv[k] + aprev * pold[k]);
                 }
 #pragma unroll
-                for (int k = 0; k < P; ++k) store_nt<strm>(a.p + base + k * P2, uc[k]);
+                for (int k = 0; k < P; ++k) {
+                    uc[k] = uc[k] + beta * pold[k];
+                    store_nt<strm>(a.p + base + k * P2, uc[k]);
+                }
             } else {
 #pragma unroll
                 for (int k = 0; k < P; ++k) uc[k] = a.u[base + k * P2];
             }
 #pragma unroll
-            for (int k = 0; k < P; ++k) sa[k * P2 + col] = uc[k];
+            for (int k = 0; k < P; ++k) sa[k * kSlab + col] = uc[k];
         }
+        // the staged x of one element may lie in another one's second tile,
+        // which is written next: every wave has read it
+        if constexpr (kDma) lds_barrier();
+        else elem_sync();
 
-        ColumnGeom<T> cg;
-        if constexpr (OTF) {
-            if (valid) {
-                if constexpr (kDma)
-                    cg = column_geom<T>(reinterpret_cast<const T *>(sV) + el * 24, xi_i, eta_j,
-                                        wij);
-                else
-                    cg = column_geom<T>(a.vert + e * 24, xi_i, eta_j, wij);
-            }
-        }
+        // the column's factors, in flight during the gradient
         constexpr bool kPre = !OTF && prefetch_g<T>();
         T gq[kPre ? 6 : 1][kPre ? P : 1];
         if constexpr (kPre) {
             if (valid) {
-                const T *Ge = a.G + e * (6 * P3) + col;
+                const T *const Ge = a.G + e * (6 * P3) + c;
 #pragma unroll
-                for (int c = 0; c < 6; ++c)
+                for (int q = 0; q < 6; ++q)
 #pragma unroll
-                    for (int k = 0; k < P; ++k) gq[c][k] = load_g(Ge + c * P3 + k * P2);
+                    for (int k = 0; k < P; ++k) gq[q][k] = load_g(Ge + q * P3 + k * P2);
             }
         }
-        lds_barrier();
-        // every thread is done with the staged tile: stage the next one
+        // gradient: k in the column's registers, i and j on pencils
+        T ut[P], dsj[P];
+        if (valid) {
+            T pc[P];
+            apply_m<T>(a.Dt, uc, ut);
+#pragma unroll
+            for (int l = 0; l < P; ++l) pc[l] = sa[ipen + l];
+            apply_m<T>(a.Dt, pc, dsj);
+#pragma unroll
+            for (int l = 0; l < P; ++l) sb[ipen + l] = dsj[l];
+#pragma unroll
+            for (int l = 0; l < P; ++l) pc[l] = sa[jpen + kRow * l];
+            apply_m<T>(a.Dt, pc, dsj);
+        }
+        elem_sync();                          // every pencil of u was read
+        if (valid) {
+#pragma unroll
+            for (int l = 0; l < P; ++l) sa[jpen + kRow * l] = dsj[l];
+        }
+        elem_sync();
+
+        // G pointwise, back in the column layout; each thread rewrites only
+        // its own column's slots, in place
+        if (valid) {
+            ColumnGeom<T> cg;
+            if constexpr (OTF) {
+                if constexpr (kDma)
+                    cg = column_geom<T>(reinterpret_cast<const T *>(sV) + el * 24, xi_i, eta_j,
+                                        wij);
+                else if constexpr (kWaveElem)
+                    cg = column_geom<T>((kconst<T> *)(a.vert + uniform64(e) * 24), xi_i, eta_j,
+                                        wij);
+                else
+                    cg = column_geom<T>(a.vert + e * 24, xi_i, eta_j, wij);
+            }
+            const T *const Ge = OTF ? nullptr : a.G + e * (6 * P3) + c;
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const int cs = k * kSlab + col;
+                const T ur = sb[cs], us = sa[cs];
+                T vr, vs;
+                point_flux<T, OTF, kPre>(cg, bk, k, gq, Ge, ur, us, ut[k], vr, vs, ut[k]);
+                sb[cs] = vr;
+                sa[cs] = vs;
+            }
+        }
+        if constexpr (kDma) lds_barrier();    // every wave's staging reads are done
+        else elem_sync();
         if constexpr (kDma) {
             if (tile + vgrid < ntiles) stage(tile + vgrid);
         }
 
-        T vsr[P], vtr[P];
+        // divergence: D^T along k in registers, along i and j on pencils,
+        // rewritten in place (each tile is read by its own direction only)
+        T wt[P];
         if (valid) {
+            T pc[P], d[P];
+            apply_m<T>(a.D, ut, wt);
 #pragma unroll
-            for (int k = 0; k < P; ++k) {
-                T ur = T(0), us = T(0), ut = T(0);
+            for (int l = 0; l < P; ++l) pc[l] = sb[ipen + l];
+            apply_m<T>(a.D, pc, d);
 #pragma unroll
-                for (int l = 0; l < P; ++l) {
-                    ur += Di[l] * sa[k * P2 + j * P + l];
-                    us += Dj[l] * sa[k * P2 + l * P + i];
-                    ut += bk.D[k * P + l] * uc[l];
-                }
-                T vr, vs, vt;
-                point_flux<T, OTF, kPre>(cg, bk, k, gq, OTF ? nullptr : a.G + e * (6 * P3) + col,
-                                         ur, us, ut, vr, vs, vt);
-                sb[k * P2 + col] = vr;
-                vsr[k] = vs;
-                vtr[k] = vt;
-            }
+            for (int l = 0; l < P; ++l) sb[ipen + l] = d[l];
+#pragma unroll
+            for (int l = 0; l < P; ++l) pc[l] = sa[jpen + kRow * l];
+            apply_m<T>(a.D, pc, d);
+#pragma unroll
+            for (int l = 0; l < P; ++l) sa[jpen + kRow * l] = d[l];
         }
-        lds_barrier();
-        if (valid) {
-#pragma unroll
-            for (int k = 0; k < P; ++k) sa[k * P2 + col] = vsr[k];
-        }
-        lds_barrier();
+        elem_sync();
 
         if (valid) {
 #pragma unroll
             for (int k = 0; k < P; ++k) {
-                // three chains, one per direction, summed (r + s) + t (the
-                // order of the matrix-core form, which gives the same bits)
-                T wr = T(0), ws = T(0), wt = T(0);
-#pragma unroll
-                for (int l = 0; l < P; ++l) {
-                    wr += DiT[l] * sb[k * P2 + j * P + l];
-                    ws += DjT[l] * sa[k * P2 + l * P + i];
-                    wt += bk.D[l * P + k] * vtr[l];
-                }
-                const T wv = (wr + ws) + wt;
+                // (r + s) + t: the order of the matrix-core form
+                const int cs = k * kSlab + col;
+                const T wv = (sb[cs] + sa[cs]) + wt[k];
                 if constexpr (FUSED) {
                     acc += (double)uc[k] * (double)wv;
                     // compact copy of the edge and corner nodes
@@ -549,10 +648,12 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
                 a.w[base + k * P2] = wv;
             }
         }
-        lds_barrier();   // the next tile overwrites the LDS tile
         if constexpr (kDma) {
+            lds_barrier();                    // the tiles are free: x lands in the second
             if (tile + vgrid < ntiles) stage_x(tile + vgrid);
         }
+        // without staging the next tile's first writes are the thread's own
+        // column slots of sA, which no other thread still reads
     }
     if constexpr (FUSED) {
         const double s = block_sum(acc);
@@ -768,15 +869,7 @@ __device__ __forceinline__ void ax_mfma_body(const AxArgs<float> &a, const Basis
             for (int k = 0; k < P; ++k) sA[cslot(k)] = uc[k];
             wave_lds_sync();
 
-            constexpr bool kPre = !OTF && prefetch_g<T>();
-            T gq[kPre ? 6 : 1][kPre ? P : 1];
-            if constexpr (kPre) {
-                const T *Ge = a.G + e * (6 * P3) + q;
-#pragma unroll
-                for (int c = 0; c < 6; ++c)
-#pragma unroll
-                    for (int k = 0; k < P; ++k) gq[c][k] = load_g(Ge + c * P3 + k * P2);
-            }
+            const T gq[1][1] = {{T(0)}};
 
             // gradient: k in the column's registers, i and j on pencils
             T ut[P], pi[P], pj[P], dri[P], dsj[P];
@@ -823,7 +916,7 @@ __device__ __forceinline__ void ax_mfma_body(const AxArgs<float> &a, const Basis
                 const int cs = cslot(k);
                 const T ur = sB[cs], us = sA[cs];
                 T vr, vs;
-                point_flux<T, OTF, kPre>(cg, bk, k, gq, OTF ? nullptr : a.G + e * (6 * P3) + q,
+                point_flux<T, OTF, false>(cg, bk, k, gq, OTF ? nullptr : a.G + e * (6 * P3) + q,
                                          ur, us, ut[k], vr, vs, vt[k]);
                 sB[cs] = vr;
                 sA[cs] = vs;
@@ -1007,15 +1100,7 @@ __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const Bas
             if constexpr (kDma) {
                 if (e + vgrid < ntiles) stage(e + vgrid);
             }
-            constexpr bool kPre = !OTF && prefetch_g<T>();
-            T gq[kPre ? 6 : 1][kPre ? P : 1];
-            if constexpr (kPre) {
-                const T *Ge = a.G + e * (6 * P3) + c;
-#pragma unroll
-                for (int cc = 0; cc < 6; ++cc)
-#pragma unroll
-                    for (int k = 0; k < P; ++k) gq[cc][k] = load_g(Ge + cc * P3 + k * P2);
-            }
+            const T gq[1][1] = {{T(0)}};
 
             // gradient: i- and j-pencils of sA into sB and sC
             T ut[P];
@@ -1052,7 +1137,7 @@ __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const Bas
                 const int cs = c + k * S;
                 const T ur = sB[cs], us = sC[cs];
                 T vr, vs;
-                point_flux<T, OTF, kPre>(cg, bk, k, gq, OTF ? nullptr : a.G + e * (6 * P3) + c,
+                point_flux<T, OTF, false>(cg, bk, k, gq, OTF ? nullptr : a.G + e * (6 * P3) + c,
                                          ur, us, ut[k], vr, vs, vt[k]);
                 if (active) {
                     sB[cs] = vr;
@@ -1138,7 +1223,7 @@ ax_mfma_batch_kernel(const AxArgs<float> *__restrict__ descs, const int2 *__rest
 }
 
 template <typename T, bool OTF, bool FUSED, bool NT = false>
-__global__ void __launch_bounds__(512, ax_min_waves<T>())
+__global__ void __launch_bounds__(512, (ax_min_waves<T, OTF>()))
 ax_kernel(const AxArgs<T> a, const BasisK<T> bk, int64_t ntiles) {
     ax_body<T, OTF, FUSED, NT>(a, bk, ntiles, blockIdx.x, gridDim.x);
 }
@@ -1148,7 +1233,7 @@ ax_kernel(const AxArgs<T> a, const BasisK<T> bk, int64_t ntiles) {
 // would run, so every problem's partials (and results) are bitwise those
 // of its solo solve.
 template <typename T, bool OTF, bool NT = false>
-__global__ void __launch_bounds__(512, ax_min_waves<T>())
+__global__ void __launch_bounds__(512, (ax_min_waves<T, OTF>()))
 ax_batch_kernel(const AxArgs<T> *__restrict__ descs, const int2 *__restrict__ blk,
                 const BasisK<T> bk) {
     const int2 pv = blk[blockIdx.x];

@@ -51,6 +51,13 @@ __host__ __device__ inline int edge_slot(int N, int i, int j, int k) {
     return corner ? cb + 1 + k : -1;
 }
 
+// Distance of two elements' tiles in the local operator's LDS, in values
+// (see the tile layout in sem_ax_order.hip).
+constexpr int ax_tile_stride(int P) {
+    return P == 2 ? 12 : P == 4 ? 80 : P == 6 ? 228 : P == 8 ? 576 : P == 10 ? 1060
+         : P == 12 ? 1740 : P * P * P;
+}
+
 // ---------------------------------------------------------------------------
 // Errors
 // ---------------------------------------------------------------------------
