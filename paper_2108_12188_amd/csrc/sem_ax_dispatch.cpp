@@ -25,7 +25,7 @@ SEM_DECL_ORDER(11)
 #undef SEM_DECL_ORDER
 
 #define SEM_DECL_BATCH(N)                                                                      \
-    void ax_batch_order_##N##_f32(bool, bool, bool, const AxArgs<float> *, const int2 *,       \
+    void ax_batch_order_##N##_f32(bool, bool, bool, bool, const AxArgs<float> *, const int2 *,       \
                                   int64_t, int, const double *, const double *, const double *, \
                                   hipStream_t);
 SEM_DECL_BATCH(1)
@@ -41,7 +41,7 @@ SEM_DECL_BATCH(10)
 SEM_DECL_BATCH(11)
 #undef SEM_DECL_BATCH
 
-using FnB = void (*)(bool, bool, bool, const AxArgs<float> *, const int2 *, int64_t, int,
+using FnB = void (*)(bool, bool, bool, bool, const AxArgs<float> *, const int2 *, int64_t, int,
                      const double *, const double *, const double *, hipStream_t);
 static const FnB kFnB[kMaxOrder + 1] = {
     nullptr,           ax_batch_order_1_f32, ax_batch_order_2_f32, ax_batch_order_3_f32,
@@ -235,14 +235,16 @@ void ax_batch_desc(const Mesh &m, bool otf, AxArgs<float> &a) {
     a.vgrid = ax_grid((m.E + sh.epb - 1) / sh.epb, AxMode::CgFused, false, sh.mfma, sh.threads);
 }
 
-void launch_ax_batch(int N, bool otf, bool mfma, bool stream, const AxArgs<float> *descs,
+void launch_ax_batch(int N, bool otf, bool mfma, bool stream, bool rho, const AxArgs<float> *descs,
                      const int2 *blk, int64_t nblk, int epb, const double *D, const double *xi,
                      const double *w,
                      hipStream_t s) {
     if (nblk <= 0) return;
-    kFnB[N](otf, mfma, stream, descs, blk, nblk, epb, D, xi, w, s);
+    kFnB[N](otf, mfma, stream, rho, descs, blk, nblk, epb, D, xi, w, s);
     check_hip(hipGetLastError(), "batched ax kernel launch");
 }
+
+int ax_threads(int N, bool fp64, bool otf) { return ax_shape(N, fp64, otf, 0).threads; }
 
 int64_t cg_footprint(const Mesh &m, int tsz, bool table_free) {
     const int64_t es = edge_slots(m.N);
@@ -250,6 +252,7 @@ int64_t cg_footprint(const Mesh &m, int tsz, bool table_free) {
     if (table_free) b += m.E * (6 + es) * 8 + tsz * m.n_egroups;       // records, edge sums
     else if (m.gs_in_update) b += 4 * m.n + tsz * m.n_groups_multi;    // table, group sums
     if (m.gsum_wedge || table_free) b += m.E * es * tsz;                // edge copy
+    if (m.direct) b += m.E * (es + 8) * 16;                             // edge lists
     // vertices (the matrix-core operator at N = 7 reads the element edge
     // vectors instead), point codes
     b += (m.edge32 && tsz == 4 ? m.E * 36 * 4 : m.E * 24 * tsz) + m.n;

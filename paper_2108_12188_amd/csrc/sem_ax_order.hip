@@ -216,10 +216,12 @@ __device__ __forceinline__ void point_flux(const ColumnGeom<T> &cg, const BasisK
     }
 }
 
-__device__ __forceinline__ double block_sum(double v) {
+// the block's one array for sums across waves
+__device__ __forceinline__ double *block_red() {
     __shared__ double red[16];
-    return block_sum_f64(v, red);
+    return red;
 }
+__device__ __forceinline__ double block_sum(double v) { return block_sum_f64(v, block_red()); }
 
 // Waves per SIMD the registers are held to.  FP32 up to N = 7: 4 (the
 // on-the-fly form is latency-bound below that occupancy).  FP64: 3 with
@@ -252,20 +254,70 @@ __host__ __device__ constexpr size_t ax_lds_bytes(int epb) {
                                : 0);
 }
 
-// s_waitcnt immediates (gfx9 encoding): vmcnt(0) alone, lgkmcnt(0) alone
+// s_waitcnt immediates (gfx9 encoding): vmcnt(0), vmcnt(8)
 constexpr int kWaitVmcnt0 = 0x0F70;
 constexpr int kWaitVmcnt8 = 0x0F78;
-constexpr int kWaitLgkmcnt0 = 0xC07F;
 
-// Barrier for LDS traffic only: the wave's own LDS accesses complete
-// before it, but global loads and stores -- and the staging loads, which
-// write LDS -- keep flying across it (a fenced __syncthreads would wait for
-// all of them).  The memory clobber keeps the compiler from moving any
-// memory access across the barrier.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
-    __asm__ volatile("s_barrier" ::: "memory");
+// The scalars of one CG-fused operator launch.
+template <typename T>
+struct CgOpen {
+    T beta, aprev;     // beta; the lagged x step's alpha
+    bool xlag;         // x += aprev p_old in this launch
+    bool run;          // false: stopped, the whole grid exits
+};
+
+// The state as the last launch left it, in one round of loads.
+template <typename T>
+__device__ __forceinline__ CgOpen<T> cg_open(const AxArgs<T> &a) {
+    CgOpen<T> c;
+    const int stopped = a.st->stop;
+    c.beta = (T)a.st->beta;
+    c.xlag = a.x != nullptr && a.st->x_lag != 0;
+    c.aprev = (T)a.st->alpha;
+    c.run = stopped == 0;
+    return c;
 }
+
+// The same where rho is still to be formed (RHO): every block sums the last
+// update's partials (n_rho of them, in an order that depends on the block
+// size alone) and block 0 writes the new state.  The state and the first
+// partials are read before the first tile is staged, and used after.
+template <typename T, bool kOneWave = false>
+struct CgOpenRho {
+    CgStep h;
+    double thresh;
+    int max_iter, fixed, hist_len;
+    double *hist_rho;
+    PartialSum<kOneWave> sum;
+    __device__ __forceinline__ void read(const AxArgs<T> &a, int nthr) {
+        h = load_step(a.st);
+        thresh = a.st->thresh;
+        max_iter = a.st->max_iter;
+        fixed = a.st->fixed;
+        hist_len = a.st->hist_len;
+        hist_rho = a.st->hist_rho;
+        sum.load(a.rho_part, a.n_rho, nthr, 0);
+    }
+    __device__ __forceinline__ CgOpen<T> finish(const AxArgs<T> &a, int64_t vb, int nthr) {
+        double *const red = kOneWave ? nullptr : block_red();
+        const double rho = sum.finish(a.rho_part, a.n_rho, nthr, red);
+        const double rr =
+            a.rr_part ? sum_partials_all<kOneWave>(a.rr_part, a.n_rho, nthr, red) : rho;
+        const bool pending = !h.stop && h.rho_pending;
+        if (pending) rho_step(h, rho, rr, thresh, max_iter, fixed);
+        CgOpen<T> c;
+        c.run = h.stop == 0;
+        c.beta = (T)h.beta;
+        c.aprev = (T)h.alpha;
+        c.xlag = a.x != nullptr && h.x_lag != 0;
+        if (vb == 0 && threadIdx.x == 0) {
+            if (c.run) h.x_lag = 0;          // applied by this launch
+            *a.st_out = h;
+            if (pending && hist_rho && h.iter < hist_len) hist_rho[h.iter] = rr;
+        }
+        return c;
+    }
+};
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void glb_void_t;
@@ -399,7 +451,7 @@ __device__ __forceinline__ void apply_m(const T *mt, const T (&x)[kP], T (&out)[
 // Plain operator on the fly, 3 M points, column form -> pencil form: FP64
 // N = 7 33.1 -> 22.9 us, N = 9 61.4 -> 29.0, N = 11 89.0 -> 40.0; FP32 N = 8
 // 20.1 -> 15.4, N = 11 52.8 -> 20.6 us; the same bits.
-template <typename T, bool OTF, bool FUSED, bool NT = false>
+template <typename T, bool OTF, bool FUSED, bool NT = false, bool RHO = false>
 __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk, int64_t ntiles,
                                         int64_t vb, int64_t vgrid) {
     constexpr int P = kP, P2 = P * P, P3 = P2 * P;
@@ -413,24 +465,20 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
     float *const sV = sP + a.epb * P3;
     float *const sX = reinterpret_cast<float *>(sB);
 
-    // the CG state in one round of loads: stop, beta, the lagged x step
-    T beta = T(0);
-    // single-mesh CG: x += alpha_{i-1} p_{i-1} of the previous iteration,
-    // applied here where p_{i-1} is read anyway
-    bool xlag = false;
-    T aprev = T(0);
-    if constexpr (FUSED) {
-        const int stopped = a.st->stop;
-        beta = (T)a.st->beta;
-        xlag = a.x != nullptr && a.st->x_lag != 0;
-        aprev = (T)a.st->alpha;
-        if (stopped) return;             // uniform: the whole grid exits
-    }
-
     const int t = threadIdx.x;
     const int el = t / P2;
     const int c = t - el * P2;
     const int nwave = (a.epb * P2 + 63) >> 6;   // the launch's block size in waves
+    // the CG scalars: final (a stopped state ends the block), or formed
+    // below while the first tile's data flies
+    CgOpen<T> cgo{T(0), T(0), false, true};
+    CgOpenRho<T> rho_open;
+    if constexpr (FUSED && RHO) {
+        rho_open.read(a, nwave * 64);
+    } else if constexpr (FUSED) {
+        cgo = cg_open<T>(a);
+        if (!cgo.run) return;        // uniform: the whole grid exits
+    }
     // the thread's column (i, j) = (c % P, c / P), its i-pencil (j, k) and
     // its j-pencil (i, k) with the same two indices
     const int i = c % P;
@@ -473,17 +521,27 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
         if constexpr (kDma) {
             const int64_t e0 = tl * a.epb;
             const int nval = (int)(a.E - e0 < a.epb ? a.E - e0 : a.epb);
-            if (xlag)
+            if (RHO ? a.x != nullptr : cgo.xlag)
                 dma_to_lds_nt<strm>(reinterpret_cast<const float *>(a.x) + e0 * P3, sX, nval * P3,
                                    nwave);
         }
     };
     if constexpr (kDma) {
+        // the first tile's data flies while the scalars are formed
         if (vb < ntiles) {
             stage(vb);
             stage_x(vb);
         }
     }
+    if constexpr (FUSED && RHO) {
+        cgo = rho_open.finish(a, vb, nwave * 64);
+        if (!cgo.run) {                  // uniform: the whole grid exits
+            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);   // no load into LDS outlives the block
+            return;
+        }
+    }
+    const T beta = cgo.beta, aprev = cgo.aprev;
+    const bool xlag = cgo.xlag;   // x += alpha_{i-1} p_{i-1} here, where p_{i-1} is read anyway
 
     double acc = 0.0;
     // a tile is `epb` consecutive elements; the grid strides over tiles (in
@@ -765,7 +823,7 @@ __device__ __forceinline__ MfmaPencils mfma_pencils(int q) {
     return pc;
 }
 
-template <bool OTF, bool FUSED, bool NT = false>
+template <bool OTF, bool FUSED, bool NT = false, bool RHO = false>
 __device__ __forceinline__ void ax_mfma_body(const AxArgs<float> &a, const BasisK<float> &bk,
                                              int64_t ntiles, int64_t vb, int64_t vgrid) {
     if constexpr (kP == 8) {
@@ -782,16 +840,15 @@ __device__ __forceinline__ void ax_mfma_body(const AxArgs<float> &a, const Basis
         __shared__ __align__(16) float sP[FUSED ? P3 : 4];   // next element's p
         __shared__ __align__(16) float sX[FUSED ? P3 : 4];   // next element's x
 
-        // the CG state in one round of loads: stop, beta, the lagged x step
-        T beta = T(0);
-        bool xlag = false;
-        T aprev = T(0);
-        if constexpr (FUSED) {
-            const int stopped = a.st->stop;
-            beta = (T)a.st->beta;
-            xlag = a.x != nullptr && a.st->x_lag != 0;
-            aprev = (T)a.st->alpha;
-            if (stopped) return;
+        // the CG scalars: final (a stopped state ends the block), or formed
+        // below while the first tile's data flies
+        CgOpen<T> cgo{T(0), T(0), false, true};
+        CgOpenRho<T, true> rho_open;
+        if constexpr (FUSED && RHO) {
+            rho_open.read(a, 64);
+        } else if constexpr (FUSED) {
+            cgo = cg_open<T>(a);
+            if (!cgo.run) return;        // uniform: the whole grid exits
         }
         const int q = threadIdx.x;        // column (i, j) = (q & 7, q >> 3)
         const int i = q & 7, j = q >> 3;
@@ -818,7 +875,7 @@ __device__ __forceinline__ void ax_mfma_body(const AxArgs<float> &a, const Basis
                 dma_elem_to_lds(reinterpret_cast<const float *>(a.u) + e * P3, sR);
                 dma_elem_to_lds_nt<strm>(
                     reinterpret_cast<const float *>(a.p) + e * P3, sP);
-                if (xlag)
+                if (RHO ? a.x != nullptr : cgo.xlag)
                     dma_elem_to_lds_nt<strm>(
                         reinterpret_cast<const float *>(a.x) + e * P3, sX);
             }
@@ -830,9 +887,19 @@ __device__ __forceinline__ void ax_mfma_body(const AxArgs<float> &a, const Basis
         // plain operators, precomputed G most, keep launch order
         const int64_t ev0 =
             (FUSED && ntiles % vgrid == 0) ? xcd_first_tile(vb, vgrid) : vb;
+        // the first element's data flies while the scalars are formed
         if (ev0 < ntiles) {
             if constexpr (kDma) stage(ev0);
         }
+        if constexpr (FUSED && RHO) {
+            cgo = rho_open.finish(a, vb, 64);
+            if (!cgo.run) {
+                __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);   // no load into LDS outlives the block
+                return;
+            }
+        }
+        const T beta = cgo.beta, aprev = cgo.aprev;
+        const bool xlag = cgo.xlag;
 
         double acc = 0.0;
         for (int64_t e = ev0; e < ntiles; e += vgrid) {
@@ -844,7 +911,7 @@ __device__ __forceinline__ void ax_mfma_body(const AxArgs<float> &a, const Basis
             // vector-memory operations (its w stores, issued after the
             // staging loads; vector-memory operations complete in order)
             if constexpr (kDma) {
-                if (e == vb) __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+                if (e == ev0) __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
                 else __builtin_amdgcn_s_waitcnt(kWaitVmcnt8);
                 __asm__ volatile("" ::: "memory");
             }
@@ -992,7 +1059,7 @@ __device__ __forceinline__ void mfma_apply10(const float (&m)[kP], const float (
     }
 }
 
-template <bool OTF, bool FUSED, bool NT = false>
+template <bool OTF, bool FUSED, bool NT = false, bool RHO = false>
 __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const BasisK<float> &bk,
                                                int64_t ntiles, int64_t vb, int64_t vgrid) {
     if constexpr (kP == 10) {
@@ -1007,16 +1074,15 @@ __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const Bas
         __shared__ __align__(16) float sX[FUSED ? P3 : 4];   // next element's x
         __shared__ __align__(16) float sV[FUSED ? 32 : 4];   // next element's vertices
 
-        // the CG state in one round of loads: stop, beta, the lagged x step
-        T beta = T(0);
-        bool xlag = false;
-        T aprev = T(0);
-        if constexpr (FUSED) {
-            const int stopped = a.st->stop;
-            beta = (T)a.st->beta;
-            xlag = a.x != nullptr && a.st->x_lag != 0;
-            aprev = (T)a.st->alpha;
-            if (stopped) return;
+        // the CG scalars: final (a stopped state ends the block), or formed
+        // below while the first tile's data flies
+        CgOpen<T> cgo{T(0), T(0), false, true};
+        CgOpenRho<T> rho_open;
+        if constexpr (FUSED && RHO) {
+            rho_open.read(a, 128);
+        } else if constexpr (FUSED) {
+            cgo = cg_open<T>(a);
+            if (!cgo.run) return;        // uniform: the whole grid exits
         }
         const int t = threadIdx.x;
         const bool active = t < P2;
@@ -1047,7 +1113,7 @@ __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const Bas
             if constexpr (kDma) {
                 dma_to_lds(reinterpret_cast<const float *>(a.u) + e * P3, sR, P3, 2);
                 dma_to_lds_nt<strm>(reinterpret_cast<const float *>(a.p) + e * P3, sP, P3, 2);
-                if (xlag)
+                if (RHO ? a.x != nullptr : cgo.xlag)
                     dma_to_lds_nt<strm>(reinterpret_cast<const float *>(a.x) + e * P3, sX, P3, 2);
             }
         };
@@ -1063,6 +1129,15 @@ __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const Bas
                 stage_vert(vb);
             }
         }
+        if constexpr (FUSED && RHO) {
+            cgo = rho_open.finish(a, vb, 128);
+            if (!cgo.run) {
+                __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);   // no load into LDS outlives the block
+                return;
+            }
+        }
+        const T beta = cgo.beta, aprev = cgo.aprev;
+        const bool xlag = cgo.xlag;
 
         double acc = 0.0;
         for (int64_t e = vb; e < ntiles; e += vgrid) {
@@ -1199,46 +1274,47 @@ __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const Bas
 constexpr int kMfmaThreads = kP == 10 ? 128 : 64;
 constexpr int kMfmaWaves = kP == 10 ? 3 : 4;
 
-template <bool OTF, bool FUSED, bool NT>
+template <bool OTF, bool FUSED, bool NT, bool RHO>
 __device__ __forceinline__ void ax_mfma_any(const AxArgs<float> &a, const BasisK<float> &bk,
                                             int64_t ntiles, int64_t vb, int64_t vgrid) {
-    if constexpr (kP == 10) ax_mfma10_body<OTF, FUSED, NT>(a, bk, ntiles, vb, vgrid);
-    else ax_mfma_body<OTF, FUSED, NT>(a, bk, ntiles, vb, vgrid);
+    if constexpr (kP == 10) ax_mfma10_body<OTF, FUSED, NT, RHO>(a, bk, ntiles, vb, vgrid);
+    else ax_mfma_body<OTF, FUSED, NT, RHO>(a, bk, ntiles, vb, vgrid);
 }
 
-// NT: the CG-fused form with p and x non-temporal (AxArgs::stream)
-template <bool OTF, bool FUSED, bool NT = false>
+// NT: the CG-fused form with p and x non-temporal (AxArgs::stream); RHO: the
+// CG-fused form that forms rho first (AxArgs::st_out)
+template <bool OTF, bool FUSED, bool NT = false, bool RHO = false>
 __global__ void __launch_bounds__(kMfmaThreads, kMfmaWaves)
 ax_mfma_kernel(const AxArgs<float> a, const BasisK<float> bk, int64_t ntiles) {
-    ax_mfma_any<OTF, FUSED, NT>(a, bk, ntiles, blockIdx.x, gridDim.x);
+    ax_mfma_any<OTF, FUSED, NT, RHO>(a, bk, ntiles, blockIdx.x, gridDim.x);
 }
 
-template <bool OTF, bool NT = false>
+template <bool OTF, bool NT = false, bool RHO = false>
 __global__ void __launch_bounds__(kMfmaThreads, kMfmaWaves)
 ax_mfma_batch_kernel(const AxArgs<float> *__restrict__ descs, const int2 *__restrict__ blk,
                      const BasisK<float> bk) {
     const int2 pv = blk[blockIdx.x];
     const AxArgs<float> a = descs[pv.x];
-    ax_mfma_any<OTF, true, NT>(a, bk, a.E, pv.y, a.vgrid);
+    ax_mfma_any<OTF, true, NT, RHO>(a, bk, a.E, pv.y, a.vgrid);
 }
 
-template <typename T, bool OTF, bool FUSED, bool NT = false>
+template <typename T, bool OTF, bool FUSED, bool NT = false, bool RHO = false>
 __global__ void __launch_bounds__(512, (ax_min_waves<T, OTF>()))
 ax_kernel(const AxArgs<T> a, const BasisK<T> bk, int64_t ntiles) {
-    ax_body<T, OTF, FUSED, NT>(a, bk, ntiles, blockIdx.x, gridDim.x);
+    ax_body<T, OTF, FUSED, NT, RHO>(a, bk, ntiles, blockIdx.x, gridDim.x);
 }
 
 // Many problems of this order in one launch: block b runs virtual block
 // blk[b].y of problem blk[b].x, exactly the block that problem's own launch
 // would run, so every problem's partials (and results) are bitwise those
 // of its solo solve.
-template <typename T, bool OTF, bool NT = false>
+template <typename T, bool OTF, bool NT = false, bool RHO = false>
 __global__ void __launch_bounds__(512, (ax_min_waves<T, OTF>()))
 ax_batch_kernel(const AxArgs<T> *__restrict__ descs, const int2 *__restrict__ blk,
                 const BasisK<T> bk) {
     const int2 pv = blk[blockIdx.x];
     const AxArgs<T> a = descs[pv.x];
-    ax_body<T, OTF, true, NT>(a, bk, (a.E + a.epb - 1) / a.epb, pv.y, a.vgrid);
+    ax_body<T, OTF, true, NT, RHO>(a, bk, (a.E + a.epb - 1) / a.epb, pv.y, a.vgrid);
 }
 
 template <typename T>
@@ -1252,31 +1328,32 @@ BasisK<T> make_basis(const double *D, const double *xi, const double *w) {
     return b;
 }
 
-template <typename T, bool OTF, bool FUSED>
+template <typename T, bool OTF, bool FUSED, bool NT, bool RHO>
 void launch(const AxArgs<T> &a, const BasisK<T> &bk, int64_t grid, hipStream_t s) {
-    constexpr bool kMayStream = FUSED;
-    const bool nt = kMayStream && a.stream != 0;
     if constexpr (sizeof(T) == 4 && (kP == 8 || kP == 10)) {
         if (a.mfma) {
             // one element per block (one wave at N = 7, two at N = 9)
-            if (nt)
-                hipLaunchKernelGGL((ax_mfma_kernel<OTF, FUSED, kMayStream>), dim3((unsigned)grid),
-                                   dim3(kMfmaThreads), 0, s, a, bk, a.E);
-            else
-                hipLaunchKernelGGL((ax_mfma_kernel<OTF, FUSED>), dim3((unsigned)grid),
-                                   dim3(kMfmaThreads), 0, s, a, bk, a.E);
+            hipLaunchKernelGGL((ax_mfma_kernel<OTF, FUSED, NT, RHO>), dim3((unsigned)grid),
+                               dim3(kMfmaThreads), 0, s, a, bk, a.E);
             return;
         }
     }
     const int threads = ((a.epb * kP * kP + 63) / 64) * 64;
     const size_t lds = ax_lds_bytes<T, OTF, FUSED>(a.epb);
     const int64_t ntiles = (a.E + a.epb - 1) / a.epb;
-    if (nt)
-        hipLaunchKernelGGL((ax_kernel<T, OTF, FUSED, kMayStream>), dim3((unsigned)grid),
-                           dim3(threads), lds, s, a, bk, ntiles);
-    else
-        hipLaunchKernelGGL((ax_kernel<T, OTF, FUSED>), dim3((unsigned)grid), dim3(threads), lds,
-                           s, a, bk, ntiles);
+    hipLaunchKernelGGL((ax_kernel<T, OTF, FUSED, NT, RHO>), dim3((unsigned)grid), dim3(threads),
+                       lds, s, a, bk, ntiles);
+}
+
+template <typename T, bool OTF>
+void launch_fused(const AxArgs<T> &a, const BasisK<T> &bk, int64_t grid, hipStream_t s) {
+    if (a.st_out) {
+        if (a.stream) launch<T, OTF, true, true, true>(a, bk, grid, s);
+        else launch<T, OTF, true, false, true>(a, bk, grid, s);
+    } else {
+        if (a.stream) launch<T, OTF, true, true, false>(a, bk, grid, s);
+        else launch<T, OTF, true, false, false>(a, bk, grid, s);
+    }
 }
 
 }  // namespace
@@ -1290,25 +1367,25 @@ static void ax_entry(bool otf, AxMode mode, const AxArgs<T> &a, const double *D,
     const BasisK<T> bk = make_basis<T>(D, xi, w);
     const bool fused = mode == AxMode::CgFused;
     if (otf) {
-        if (fused) launch<T, true, true>(a, bk, grid, s);
-        else launch<T, true, false>(a, bk, grid, s);
+        if (fused) launch_fused<T, true>(a, bk, grid, s);
+        else launch<T, true, false, false, false>(a, bk, grid, s);
     } else {
-        if (fused) launch<T, false, true>(a, bk, grid, s);
-        else launch<T, false, false>(a, bk, grid, s);
+        if (fused) launch_fused<T, false>(a, bk, grid, s);
+        else launch<T, false, false, false, false>(a, bk, grid, s);
     }
 }
 
-template <typename T, bool NT>
+template <typename T, bool NT, bool RHO>
 static void ax_batch_launch(bool otf, bool mfma, const AxArgs<T> *descs, const int2 *blk,
                             int64_t nblk, int epb, const BasisK<T> &bk, hipStream_t s) {
     if constexpr (sizeof(T) == 4 && (kP == 8 || kP == 10)) {
         if (mfma) {
             // static LDS only
             if (otf)
-                hipLaunchKernelGGL((ax_mfma_batch_kernel<true, NT>), dim3((unsigned)nblk),
+                hipLaunchKernelGGL((ax_mfma_batch_kernel<true, NT, RHO>), dim3((unsigned)nblk),
                                    dim3(kMfmaThreads), 0, s, descs, blk, bk);
             else
-                hipLaunchKernelGGL((ax_mfma_batch_kernel<false, NT>), dim3((unsigned)nblk),
+                hipLaunchKernelGGL((ax_mfma_batch_kernel<false, NT, RHO>), dim3((unsigned)nblk),
                                    dim3(kMfmaThreads), 0, s, descs, blk, bk);
             return;
         }
@@ -1317,28 +1394,33 @@ static void ax_batch_launch(bool otf, bool mfma, const AxArgs<T> *descs, const i
     const size_t lds_otf = ax_lds_bytes<T, true, true>(epb);
     const size_t lds_pre = ax_lds_bytes<T, false, true>(epb);
     if (otf)
-        hipLaunchKernelGGL((ax_batch_kernel<T, true, NT>), dim3((unsigned)nblk), dim3(threads),
+        hipLaunchKernelGGL((ax_batch_kernel<T, true, NT, RHO>), dim3((unsigned)nblk), dim3(threads),
                            lds_otf, s, descs, blk, bk);
     else
-        hipLaunchKernelGGL((ax_batch_kernel<T, false, NT>), dim3((unsigned)nblk), dim3(threads),
+        hipLaunchKernelGGL((ax_batch_kernel<T, false, NT, RHO>), dim3((unsigned)nblk), dim3(threads),
                            lds_pre, s, descs, blk, bk);
 }
 
 template <typename T>
-static void ax_batch_entry(bool otf, bool mfma, bool stream, const AxArgs<T> *descs,
+static void ax_batch_entry(bool otf, bool mfma, bool stream, bool rho, const AxArgs<T> *descs,
                            const int2 *blk, int64_t nblk, int epb, const double *D,
                            const double *xi, const double *w, hipStream_t s) {
     const BasisK<T> bk = make_basis<T>(D, xi, w);
-    if (stream) ax_batch_launch<T, true>(otf, mfma, descs, blk, nblk, epb, bk, s);
-    else ax_batch_launch<T, false>(otf, mfma, descs, blk, nblk, epb, bk, s);
+    if (rho) {
+        if (stream) ax_batch_launch<T, true, true>(otf, mfma, descs, blk, nblk, epb, bk, s);
+        else ax_batch_launch<T, false, true>(otf, mfma, descs, blk, nblk, epb, bk, s);
+    } else {
+        if (stream) ax_batch_launch<T, true, false>(otf, mfma, descs, blk, nblk, epb, bk, s);
+        else ax_batch_launch<T, false, false>(otf, mfma, descs, blk, nblk, epb, bk, s);
+    }
 }
 
-void SEM_CAT3(ax_batch_order_, SEM_ORDER, _f32)(bool otf, bool mfma, bool stream,
+void SEM_CAT3(ax_batch_order_, SEM_ORDER, _f32)(bool otf, bool mfma, bool stream, bool rho,
                                                  const AxArgs<float> *descs, const int2 *blk,
                                                  int64_t nblk, int epb, const double *D,
                                                  const double *xi, const double *w,
                                                  hipStream_t s) {
-    ax_batch_entry<float>(otf, mfma, stream, descs, blk, nblk, epb, D, xi, w, s);
+    ax_batch_entry<float>(otf, mfma, stream, rho, descs, blk, nblk, epb, D, xi, w, s);
 }
 
 void SEM_CAT3(ax_order_, SEM_ORDER, _f32)(bool otf, AxMode mode, const AxArgs<float> &a,

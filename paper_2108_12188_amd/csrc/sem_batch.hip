@@ -50,8 +50,11 @@ struct GsumBatchDesc {
     int64_t io0;
     const float *src;
     float *out;
-    const CgState *st;
+    CgState *st;
     int mmin;
+    const CgStep *step;         // three-launch problems: alpha goes from step to st
+    const double *part_ax;
+    int n_ax;
 };
 
 // update with gather of one problem (see launch_update_gather)
@@ -65,6 +68,7 @@ struct UpdGBatchDesc {
     CgState *st;
     double *partial;
     int64_t vgrid;
+    DirectArgs<float> dir;      // st_in null: the four-launch form
 };
 
 // update with the table-free gather of one problem (see launch_update_struct)
@@ -76,6 +80,7 @@ struct UpdSBatchDesc {
     CgState *st;
     double *partial;
     int64_t vgrid;
+    DirectArgs<float> dir;      // st_in null: the four-launch form
 };
 
 struct FinBatchDesc {
@@ -84,6 +89,7 @@ struct FinBatchDesc {
     int64_t n_ax;
     const double *part_vec;
     int n_vec;
+    int nthr;                   // threads of the problem's operator blocks
 };
 
 __global__ void __launch_bounds__(gsb::kGsThreads)
@@ -104,7 +110,11 @@ __global__ void __launch_bounds__(gsb::kGsThreads)
 group_sums_batch_kernel(const GsumBatchDesc *__restrict__ d, const int2 *__restrict__ blk) {
     const int2 pv = blk[blockIdx.x];
     const GsumBatchDesc g = d[pv.x];
-    if (g.st->stop) return;
+    if (pv.y < 0) {             // the problem's alpha block
+        vecb::alpha_block_body(g.st, g.step, g.part_ax, g.n_ax);
+        return;
+    }
+    if (g.step ? g.step->stop : g.st->stop) return;
     gsb::gs_sums_logical_block<float>(*g.cls, pv.y, g.idx, g.io0, g.src, g.out, g.mmin);
 }
 
@@ -116,25 +126,43 @@ update_batch_kernel(const UpdBatchDesc *__restrict__ d, const int2 *__restrict__
                                     pv.y, u.vgrid);
 }
 
+template <bool DIRECT>
 __global__ void __launch_bounds__(vecb::kVecThreads)
 update_gather_batch_kernel(const UpdGBatchDesc *__restrict__ d, const int2 *__restrict__ blk) {
     const int2 pv = blk[blockIdx.x];
     const UpdGBatchDesc u = d[pv.x];
-    vecb::update_gather_body<float>(u.n, u.r, u.w, u.gsum, u.mcode, u.gm, u.st, u.partial, pv.y,
-                                    u.vgrid);
+    if constexpr (DIRECT)
+        vecb::update_direct_body<float, false, false, 2>(u.n, u.r, u.w, u.mcode, u.gm,
+                                                      vecb::StructMap{}, u.st, u.partial, pv.y,
+                                                      u.vgrid, PcArgs<float>{}, u.dir);
+    else
+        vecb::update_gather_body<float>(u.n, u.r, u.w, u.gsum, u.mcode, u.gm, u.st, u.partial,
+                                        pv.y, u.vgrid);
 }
 
+template <bool DIRECT>
 __global__ void __launch_bounds__(vecb::kVecThreads)
 update_struct_batch_kernel(const UpdSBatchDesc *__restrict__ d, const int2 *__restrict__ blk) {
     const int2 pv = blk[blockIdx.x];
     const UpdSBatchDesc u = d[pv.x];
-    vecb::update_struct_body<float>(u.n, u.r, u.wg, u.sm, u.st, u.partial, pv.y, u.vgrid);
+    if constexpr (DIRECT)
+        vecb::update_direct_body<float, false, true, 2>(u.n, u.r, u.wg, nullptr, vecb::GatherMap{},
+                                                     u.sm, u.st, u.partial, pv.y, u.vgrid,
+                                                     PcArgs<float>{}, u.dir);
+    else
+        vecb::update_struct_body<float>(u.n, u.r, u.wg, u.sm, u.st, u.partial, pv.y, u.vgrid);
 }
 
 __global__ void __launch_bounds__(kFinalizeThreads)
 finalize_rho_batch_kernel(const FinBatchDesc *__restrict__ d) {
     const FinBatchDesc f = d[blockIdx.x];
     vecb::finalize_rho_body(f.st, f.part_vec, f.n_vec);
+}
+
+__global__ void __launch_bounds__(kMaxAxThreads)
+close_rho_batch_kernel(const FinBatchDesc *__restrict__ d) {
+    const FinBatchDesc f = d[blockIdx.x];
+    vecb::close_rho_body(f.st, f.part_vec, nullptr, f.n_vec, f.nthr);
 }
 
 // What the host reads of every problem's CG state after a chunk of batched
@@ -146,11 +174,11 @@ struct StateRow {
     double rho0;     // <r0, r0, c>
 };
 
-__global__ void gather_states_kernel(const FinBatchDesc *__restrict__ d, int count,
+__global__ void gather_states_kernel(const CgState *const *__restrict__ d, int count,
                                      StateRow *out) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q < count) {
-        const CgState *st = d[q].st;
+        const CgState *st = d[q];
         out[q] = StateRow{st->stop, st->iter, st->rr, st->rho0};
     }
 }
@@ -182,6 +210,7 @@ struct BatchImpl {
         int N;
         int epb;
         bool mfma = false;
+        bool rho = false;                            // its problems form rho in the operator
         int2 *blk = nullptr;
         int64_t nblk = 0;
     };
@@ -191,7 +220,7 @@ struct BatchImpl {
         int2 *blk = nullptr;
         size_t cap = 0;
     };
-    std::map<int, BlkTable> blk_tab[2];              // per order; owns the group tables
+    std::map<std::pair<int, bool>, BlkTable> blk_tab[2];   // per (order, rho); owns the group tables
     AxArgs<float> *d_ax[2] = {nullptr, nullptr};   // [precomputed, on the fly]
     GsClasses *d_cls = nullptr;
     GsBatchDesc *d_gs = nullptr;
@@ -200,21 +229,27 @@ struct BatchImpl {
     UpdBatchDesc *d_upd = nullptr;
     int2 *d_upd_blk = nullptr;
     int64_t n_upd_blk = 0;
-    GsumBatchDesc *d_gsum = nullptr;
+    GsumBatchDesc *d_gsum[2] = {nullptr, nullptr};   // [precomputed, on the fly]
     int2 *d_gsum_blk = nullptr;
     int64_t n_gsum_blk = 0;
-    UpdGBatchDesc *d_updg = nullptr;
+    // updates with gather, [precomputed, on the fly]; the block tables hold
+    // the problems of two-launch iterations last
+    UpdGBatchDesc *d_updg[2] = {nullptr, nullptr};
     int2 *d_updg_blk = nullptr;
-    int64_t n_updg_blk = 0;
-    UpdSBatchDesc *d_upds = nullptr;
+    int64_t n_updg_blk = 0, n_updg_direct = 0;
+    UpdSBatchDesc *d_upds[2] = {nullptr, nullptr};
     int2 *d_upds_blk = nullptr;
-    int64_t n_upds_blk = 0;
-    FinBatchDesc *d_fin[2] = {nullptr, nullptr};   // [precomputed, on the fly]
+    int64_t n_upds_blk = 0, n_upds_direct = 0;
+    // [precomputed, on the fly]: the problems of four-launch iterations first
+    FinBatchDesc *d_fin[2] = {nullptr, nullptr};
+    int n_fin = 0;                                  // four-launch problems
+    const CgState **d_stp = nullptr;                // every member's state
     StateRow *d_states = nullptr;
     StateRow *h_states = nullptr;                    // pinned
     size_t cap_ax[2] = {0, 0}, cap_fin[2] = {0, 0}, cap_cls = 0, cap_gs = 0, cap_gs_blk = 0,
-           cap_upd = 0, cap_upd_blk = 0, cap_gsum = 0, cap_gsum_blk = 0, cap_updg = 0,
-           cap_updg_blk = 0, cap_upds = 0, cap_upds_blk = 0, cap_states = 0, cap_h_states = 0;
+           cap_upd = 0, cap_upd_blk = 0, cap_gsum[2] = {0, 0}, cap_gsum_blk = 0, cap_updg[2] = {0, 0},
+           cap_updg_blk = 0, cap_upds[2] = {0, 0}, cap_upds_blk = 0, cap_stp = 0, cap_states = 0,
+           cap_h_states = 0;
     hipStream_t stream = nullptr;
     hipEvent_t ev = nullptr;
     std::map<GraphKey, hipGraphExec_t> graphs;
@@ -228,9 +263,8 @@ struct BatchImpl {
             for (auto &kv : blk_tab[f])
                 if (kv.second.blk) (void)hipFree(kv.second.blk);
         void *ptrs[] = {d_ax[0],   d_ax[1], d_cls,      d_gs,   d_gs_blk,   d_upd,
-                        d_upd_blk, d_gsum,  d_gsum_blk, d_updg, d_updg_blk, d_upds, d_upds_blk,
-                        d_fin[0],
-                        d_fin[1],  d_states};
+                        d_upd_blk, d_gsum[0], d_gsum[1], d_gsum_blk, d_updg[0], d_updg[1], d_updg_blk,
+                        d_upds[0], d_upds[1], d_upds_blk, d_fin[0], d_fin[1], d_stp, d_states};
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
         if (h_states) (void)hipHostFree(h_states);
@@ -247,7 +281,7 @@ struct BatchImpl {
         if (count() == 0) return;
         const int f = otf ? 1 : 0;
         for (const auto &g : groups[f]) {
-            launch_ax_batch(g.N, otf, g.mfma, stream_vectors, d_ax[f], g.blk, g.nblk, g.epb,
+            launch_ax_batch(g.N, otf, g.mfma, stream_vectors, g.rho, d_ax[f], g.blk, g.nblk, g.epb,
                             order_D[g.N].data(), order_xi[g.N].data(), order_w[g.N].data(), s);
         }
         if (n_gs_blk > 0)
@@ -255,20 +289,32 @@ struct BatchImpl {
                                s, d_gs, d_gs_blk);
         if (n_gsum_blk > 0)
             hipLaunchKernelGGL(group_sums_batch_kernel, dim3((unsigned)n_gsum_blk),
-                               dim3(gsb::kGsThreads), 0, s, d_gsum, d_gsum_blk);
-        hipLaunchKernelGGL(finalize_alpha_batch_kernel, dim3(count()), dim3(kFinalizeThreads), 0,
-                           s, d_fin[f]);
+                               dim3(gsb::kGsThreads), 0, s, d_gsum[f], d_gsum_blk);
+        if (n_fin > 0)
+            hipLaunchKernelGGL(finalize_alpha_batch_kernel, dim3(n_fin), dim3(kFinalizeThreads),
+                               0, s, d_fin[f]);
         if (n_upd_blk > 0)
             hipLaunchKernelGGL(update_batch_kernel, dim3((unsigned)n_upd_blk),
                                dim3(vecb::kVecThreads), 0, s, d_upd, d_upd_blk);
-        if (n_updg_blk > 0)
-            hipLaunchKernelGGL(update_gather_batch_kernel, dim3((unsigned)n_updg_blk),
-                               dim3(vecb::kVecThreads), 0, s, d_updg, d_updg_blk);
-        if (n_upds_blk > 0)
-            hipLaunchKernelGGL(update_struct_batch_kernel, dim3((unsigned)n_upds_blk),
-                               dim3(vecb::kVecThreads), 0, s, d_upds, d_upds_blk);
-        hipLaunchKernelGGL(finalize_rho_batch_kernel, dim3(count()), dim3(kFinalizeThreads), 0, s,
-                           d_fin[f]);
+        if (n_updg_blk > n_updg_direct)
+            hipLaunchKernelGGL((update_gather_batch_kernel<false>),
+                               dim3((unsigned)(n_updg_blk - n_updg_direct)),
+                               dim3(vecb::kVecThreads), 0, s, d_updg[f], d_updg_blk);
+        if (n_upds_blk > n_upds_direct)
+            hipLaunchKernelGGL((update_struct_batch_kernel<false>),
+                               dim3((unsigned)(n_upds_blk - n_upds_direct)),
+                               dim3(vecb::kVecThreads), 0, s, d_upds[f], d_upds_blk);
+        if (n_updg_direct > 0)
+            hipLaunchKernelGGL((update_gather_batch_kernel<true>), dim3((unsigned)n_updg_direct),
+                               dim3(vecb::kVecThreads), 0, s, d_updg[f],
+                               d_updg_blk + (n_updg_blk - n_updg_direct));
+        if (n_upds_direct > 0)
+            hipLaunchKernelGGL((update_struct_batch_kernel<true>), dim3((unsigned)n_upds_direct),
+                               dim3(vecb::kVecThreads), 0, s, d_upds[f],
+                               d_upds_blk + (n_upds_blk - n_upds_direct));
+        if (n_fin > 0)
+            hipLaunchKernelGGL(finalize_rho_batch_kernel, dim3(n_fin), dim3(kFinalizeThreads), 0,
+                               s, d_fin[f]);
         check_hip(hipGetLastError(), "batched iteration launch");
     }
 
@@ -300,16 +346,21 @@ struct BatchImpl {
         SEM_HIP(hipGraphLaunch(it->second, stream));
     }
 
-    // the state of every member into the pinned h_states (stream-ordered)
-    void enqueue_read_states() {
+    // the state of every member into the pinned h_states (stream-ordered);
+    // iterations that leave rho to the operator are closed first
+    void enqueue_read_states(bool otf) {
+        if (count() > n_fin)
+            hipLaunchKernelGGL(close_rho_batch_kernel, dim3(count() - n_fin), dim3(kMaxAxThreads),
+                               0, stream, d_fin[otf ? 1 : 0] + n_fin);
         hipLaunchKernelGGL(gather_states_kernel, dim3((count() + 255) / 256), dim3(256), 0, stream,
-                           d_fin[0], count(), d_states);
+                           d_stp, count(), d_states);
+        check_hip(hipGetLastError(), "batched state launch");
         SEM_HIP(hipMemcpyAsync(h_states, d_states, sizeof(StateRow) * count(), hipMemcpyDeviceToHost,
                                stream));
     }
     // ... and wait for it
-    void read_states() {
-        enqueue_read_states();
+    void read_states(bool otf) {
+        enqueue_read_states(otf);
         SEM_HIP(hipStreamSynchronize(stream));
     }
 
@@ -366,18 +417,24 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
     std::vector<GsClasses> cls;
     std::vector<GsBatchDesc> gsd;
     std::vector<UpdBatchDesc> upd;
-    std::vector<GsumBatchDesc> gsumd;
-    std::vector<UpdGBatchDesc> updg;
-    std::vector<UpdSBatchDesc> upds;
-    std::vector<FinBatchDesc> fin[2];
-    std::vector<int2> gs_blk, upd_blk, gsum_blk, updg_blk, upds_blk;
-    std::map<int, std::vector<int2>> order_blk[2];
+    std::vector<GsumBatchDesc> gsumd[2];
+    std::vector<UpdGBatchDesc> updg[2];
+    std::vector<UpdSBatchDesc> upds[2];
+    std::vector<FinBatchDesc> fin[2], fin_direct[2];
+    std::vector<const CgState *> stp;
+    std::vector<int2> gs_blk, upd_blk, gsum_blk, updg_blk, upds_blk, updg_direct, upds_direct;
+    std::map<std::pair<int, bool>, std::vector<int2>> order_blk[2];
     std::map<int, int> order_epb[2];
     std::map<int, bool> order_mfma[2];
     ensure_cap(d_cls, cap_cls, count, bytes);
     // one batched iteration touches every member's vectors
     int64_t footprint = 0;
     for (int q = 0; q < count; ++q) footprint += cg_footprint(*ms[q], 4, ms[q]->gs_struct);
+    // two-launch iterations while they pay for all members together (the same
+    // sums in the same order as with three launches)
+    int64_t npts = 0;
+    for (int q = 0; q < count; ++q) npts += ms[q]->n;
+    const bool two = npts <= kDirectMaxPoints;
     const int stream = cg_streams_vectors(footprint) ? 1 : 0;
     stream_vectors = stream != 0;
     for (int q = 0; q < count; ++q) {
@@ -393,7 +450,13 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
             a.st = ws.st;
             a.partial = ws.part_ax;
             a.x = static_cast<float *>(ws.x);
-            a.wedge = (m.gsum_wedge || m.gs_struct) ? static_cast<float *>(ws.wedge) : nullptr;
+            a.wedge = (m.gsum_wedge || m.gs_struct || m.direct) ? static_cast<float *>(ws.wedge)
+                                                                 : nullptr;
+            if (m.inline32) {
+                a.st_out = ws.step;
+                a.rho_part = ws.part_vec;
+                a.n_rho = update_blocks(m, false);
+            }
             ax[otf].push_back(a);
         }
         for (int f = 0; f < 2; ++f) {
@@ -401,7 +464,7 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
             order_epb[f][m.N] = af.epb;
             order_mfma[f][m.N] = af.mfma != 0;
             for (int64_t vb = 0; vb < af.vgrid; ++vb)
-                order_blk[f][m.N].push_back(make_int2(q, (int)vb));
+                order_blk[f][{m.N, m.inline32}].push_back(make_int2(q, (int)vb));
         }
         if (!order_D.count(m.N)) {
             order_D[m.N] = m.h_D;
@@ -410,38 +473,59 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
         }
         cls.push_back(m.gs_struct ? m.ecls : m.gs);
         const int64_t nlb = m.n_groups > 0 ? gs_logical_blocks(m) : 0;
-        const int nv = vec_blocks(m.n);
+        const int nv = update_blocks(m, false);
+        const bool direct = two && m.direct;
+        // the single-mesh schedule of each problem: the same logical and
+        // virtual blocks
+        const bool compact = m.gsum_wedge;
+        const float *const wedge = static_cast<const float *>(ws.wedge);
+        const CgStep *const step = m.inline32 ? ws.step : nullptr;
+        DirectArgs<float> dir[2] = {};
+        if (direct)
+            for (int f = 0; f < 2; ++f)
+                dir[f] = direct_args<float>(m, ws.step, wedge, ws.part_ax, (int)ax[f].back().vgrid);
         if (m.gs_struct) {
-            // the single-mesh schedule with the table-free gather: sums of
-            // every edge-node group after w, then the update
+            // table-free gather; unless the update sums them itself, the
+            // sums of every edge-node group go after w first
             float *wg = static_cast<float *>(ws.w);
-            gsumd.push_back({d_cls + q, m.ewedge_idx, (int64_t)0,
-                             static_cast<const float *>(ws.wedge), wg + m.n, ws.st, 2});
-            const int64_t nelb = gs_total_blocks(m.ecls);
-            for (int64_t lb = 0; lb < nelb; ++lb)
-                gsum_blk.push_back(make_int2((int)gsumd.size() - 1, (int)lb));
+            if (!direct) {
+                for (int f = 0; f < 2; ++f)
+                    gsumd[f].push_back({d_cls + q, m.ewedge_idx, (int64_t)0, wedge, wg + m.n,
+                                        ws.st, 2, step, ws.part_ax, (int)ax[f].back().vgrid});
+                const int64_t nelb = gs_total_blocks(m.ecls);
+                for (int64_t lb = step ? -1 : 0; lb < nelb; ++lb)
+                    gsum_blk.push_back(make_int2((int)gsumd[0].size() - 1, (int)lb));
+            }
             const vecb::StructMap sm{m.erec, m.pos_tab, m.P3, 6 + edge_slots(m.N), m.p3_magic,
                                      m.p3_shift};
-            upds.push_back({m.n, static_cast<float *>(ws.r), wg, sm, ws.st, ws.part_vec, nv});
+            for (int f = 0; f < 2; ++f)
+                upds[f].push_back({m.n, static_cast<float *>(ws.r), wg, sm, ws.st, ws.part_vec,
+                                   nv, dir[f]});
             for (int vb = 0; vb < nv; ++vb)
-                upds_blk.push_back(make_int2((int)upds.size() - 1, vb));
+                (direct ? upds_direct : upds_blk)
+                    .push_back(make_int2((int)upds[0].size() - 1, vb));
         } else if (m.gs_in_update) {
-            // the single-mesh schedule: group sums of the edge and vertex
-            // groups, update with gather (the same logical and virtual blocks)
-            const bool compact = m.gsum_wedge;
-            gsumd.push_back({d_cls + q, compact ? m.wedge_idx : m.gs_idx,
-                             compact ? m.wedge_io0 : (int64_t)0,
-                             compact ? static_cast<const float *>(ws.wedge)
-                                     : static_cast<const float *>(ws.w),
-                             static_cast<float *>(ws.gsum), ws.st, 3});
-            for (int64_t lb = m.gs_blk_multi; lb < nlb; ++lb)
-                gsum_blk.push_back(make_int2((int)gsumd.size() - 1, (int)lb));
-            const vecb::GatherMap gm{m.gsrc};
-            updg.push_back({m.n, static_cast<float *>(ws.r), static_cast<const float *>(ws.w),
-                            static_cast<const float *>(ws.gsum), m.mcode, gm, ws.st, ws.part_vec,
-                            nv});
+            // per-point table; the same for the groups of more than two copies
+            if (!direct) {
+                for (int f = 0; f < 2; ++f)
+                    gsumd[f].push_back({d_cls + q, compact ? m.wedge_idx : m.gs_idx,
+                                        compact ? m.wedge_io0 : (int64_t)0,
+                                        compact ? wedge : static_cast<const float *>(ws.w),
+                                        static_cast<float *>(ws.gsum), ws.st, 3, step,
+                                        ws.part_ax, (int)ax[f].back().vgrid});
+                if (step) gsum_blk.push_back(make_int2((int)gsumd[0].size() - 1, -1));
+                for (int64_t lb = m.gs_blk_multi; lb < nlb; ++lb)
+                    gsum_blk.push_back(make_int2((int)gsumd[0].size() - 1, (int)lb));
+            }
+            const vecb::GatherMap gm{direct ? m.gsrc_direct : m.gsrc};
+            for (int f = 0; f < 2; ++f)
+                updg[f].push_back({m.n, static_cast<float *>(ws.r),
+                                   static_cast<const float *>(ws.w),
+                                   static_cast<const float *>(ws.gsum), m.mcode, gm, ws.st,
+                                   ws.part_vec, nv, dir[f]});
             for (int vb = 0; vb < nv; ++vb)
-                updg_blk.push_back(make_int2((int)updg.size() - 1, vb));
+                (direct ? updg_direct : updg_blk)
+                    .push_back(make_int2((int)updg[0].size() - 1, vb));
         } else {
             gsd.push_back({d_cls + q, m.gs_idx, static_cast<float *>(ws.w), ws.st});
             for (int64_t lb = 0; lb < nlb; ++lb)
@@ -452,8 +536,18 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
                 upd_blk.push_back(make_int2((int)upd.size() - 1, vb));
         }
         for (int f = 0; f < 2; ++f)
-            fin[f].push_back({ws.st, ws.part_ax, ax[f].back().vgrid, ws.part_vec, nv});
+            (m.inline32 ? fin_direct[f] : fin[f])
+                .push_back({ws.st, ws.part_ax, ax[f].back().vgrid, ws.part_vec, nv,
+                            ax_threads(m.N, false, f != 0)});
+        stp.push_back(ws.st);
     }
+    n_fin = (int)fin[0].size();
+    for (int f = 0; f < 2; ++f)
+        fin[f].insert(fin[f].end(), fin_direct[f].begin(), fin_direct[f].end());
+    n_updg_direct = (int64_t)updg_direct.size();
+    n_upds_direct = (int64_t)upds_direct.size();
+    updg_blk.insert(updg_blk.end(), updg_direct.begin(), updg_direct.end());
+    upds_blk.insert(upds_blk.end(), upds_direct.begin(), upds_direct.end());
     for (int otf = 0; otf < 2; ++otf) {
         ensure_cap(d_ax[otf], cap_ax[otf], count, bytes);
         upload_sync(d_ax[otf], ax[otf]);
@@ -463,13 +557,15 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
     upload_sync(d_gs, gsd);
     ensure_cap(d_upd, cap_upd, count, bytes);
     upload_sync(d_upd, upd);
-    ensure_cap(d_gsum, cap_gsum, count, bytes);
-    upload_sync(d_gsum, gsumd);
-    ensure_cap(d_updg, cap_updg, count, bytes);
-    upload_sync(d_updg, updg);
-    ensure_cap(d_upds, cap_upds, count, bytes);
-    upload_sync(d_upds, upds);
+    ensure_cap(d_stp, cap_stp, count, bytes);
+    upload_sync(d_stp, stp);
     for (int f = 0; f < 2; ++f) {
+        ensure_cap(d_gsum[f], cap_gsum[f], count, bytes);
+        upload_sync(d_gsum[f], gsumd[f]);
+        ensure_cap(d_updg[f], cap_updg[f], count, bytes);
+        upload_sync(d_updg[f], updg[f]);
+        ensure_cap(d_upds[f], cap_upds[f], count, bytes);
+        upload_sync(d_upds[f], upds[f]);
         ensure_cap(d_fin[f], cap_fin[f], count, bytes);
         upload_sync(d_fin[f], fin[f]);
     }
@@ -504,9 +600,10 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
             ensure_cap(t.blk, t.cap, kv.second.size(), bytes);
             upload_sync(t.blk, kv.second);
             OrderGroup g;
-            g.N = kv.first;
-            g.epb = order_epb[f][kv.first];
-            g.mfma = order_mfma[f][kv.first];
+            g.N = kv.first.first;
+            g.rho = kv.first.second;
+            g.epb = order_epb[f][g.N];
+            g.mfma = order_mfma[f][g.N];
             g.nblk = (int64_t)kv.second.size();
             g.blk = t.blk;
             groups[f].push_back(g);
@@ -546,7 +643,7 @@ void iterate_all(BatchImpl &B, bool otf, int chunk, bool use_graph, int max_iter
     int64_t last_sum = -1;
     const int64_t guard = (int64_t)max_iter / std::max(chunk, 1) + 8;
     for (int64_t round = 0;; ++round) {
-        B.read_states();
+        B.read_states(otf);
         int running = 0;
         int64_t sum = 0;
         for (int q = 0; q < B.count(); ++q) {
@@ -898,7 +995,7 @@ int server_step(ServerImpl &sv, int64_t *tags, sem_cg_result *results, int cap, 
             sv.batch_uids = inner_uids;
         }
         for (int c = 0; c < sv.round_iters; ++c) sv.batch.enqueue_iteration(otf, s);
-        sv.batch.enqueue_read_states();
+        sv.batch.enqueue_read_states(otf);
         SEM_HIP(hipEventRecord(sv.ev_round, s));
         sv.round_uids = inner_uids;
         sv.round_in_flight = true;

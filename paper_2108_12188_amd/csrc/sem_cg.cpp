@@ -19,6 +19,12 @@
 // itself: a face node adds its partner's w, an edge or vertex node takes its
 // group's sum.  The summed w is never written back, and the results are
 // bitwise those of the three-pass form.
+// Meshes of up to 4 M points (FP64: 2 M) leave rho to the next operator
+// launch, whose blocks each sum the update's partials, and up to 1 M points
+// the update's blocks also each sum alpha and the groups they need: three and
+// two launches per iteration (DirectArgs; the schedule is the mesh's, batches
+// included, and the sums keep one order, so a batch of either schedule gives
+// the bits of the solo solve).
 // The CG scalars never leave the device.  Iterations are enqueued in chunks
 // (replayed HIP graphs by default); after each chunk the host reads the
 // state once.  Kernels of iterations past convergence exit at their first
@@ -39,7 +45,7 @@ void ws_free(Workspace *ws) {
     for (auto &kv : ws->graphs) (void)hipGraphExecDestroy(kv.second);
     void *dev[] = {ws->x,       ws->r,        ws->p,  ws->w,    ws->b,   ws->gsum,
                    ws->wedge,   ws->part_ax,  ws->part_vec, ws->z, ws->part_vec2, ws->st,
-                   ws->hist,    ws->dval};
+                   ws->step,    ws->hist,    ws->dval};
     for (void *q : dev)
         if (q) (void)hipFree(q);
     if (ws->h_st) (void)hipHostFree(ws->h_st);
@@ -78,7 +84,7 @@ Workspace *ws_create(const Mesh &m, bool fp64) {
         ws->b = ws_alloc<char>(*ws, nv);
         if (m.gs_in_update)
             ws->gsum = ws_alloc<char>(*ws, (size_t)m.n_groups_multi * tsz);
-        if (m.gsum_wedge || m.gs_struct)
+        if (m.gsum_wedge || m.gs_struct || m.direct)
             ws->wedge = ws_alloc<char>(*ws, (size_t)m.E * edge_slots(m.N) * tsz);
         // the smallest shape (1 element per block) bounds the Ax partial count
         ws->cap_ax = m.E;
@@ -86,6 +92,7 @@ Workspace *ws_create(const Mesh &m, bool fp64) {
         ws->part_ax = ws_alloc<double>(*ws, ws->cap_ax);
         ws->part_vec = ws_alloc<double>(*ws, ws->cap_vec);
         ws->st = ws_alloc<CgState>(*ws, 1);
+        ws->step = ws_alloc<CgStep>(*ws, 1);
         ws->dval = ws_alloc<double>(*ws, 8);
         SEM_HIP(hipHostMalloc((void **)&ws->h_st, sizeof(CgState)));
         SEM_HIP(hipHostMalloc((void **)&ws->h_val, 8 * sizeof(double)));
@@ -186,8 +193,15 @@ void enqueue_iteration(const Mesh &m, Workspace &ws, bool otf, bool pc, hipStrea
     a.w = w;
     a.st = ws.st;
     a.partial = ws.part_ax;
-    a.wedge = (m.gsum_wedge || m.gs_struct_solo) ? wedge : nullptr;
+    a.wedge = (m.gsum_wedge || m.gs_struct_solo || m.direct) ? wedge : nullptr;
     a.x = x;
+    const CgStep *const step = m.inline_scalars(sizeof(T) == 8) ? ws.step : nullptr;
+    if (step) {
+        a.st_out = ws.step;
+        a.rho_part = ws.part_vec;
+        a.rr_part = pa.partial2;
+        a.n_rho = update_blocks(m, sizeof(T) == 8);
+    }
     a.stream = ((sizeof(T) == 4 || otf) &&
                 cg_streams_vectors(cg_footprint(m, (int)sizeof(T), m.gs_struct_solo)))
                    ? 1
@@ -196,16 +210,31 @@ void enqueue_iteration(const Mesh &m, Workspace &ws, bool otf, bool pc, hipStrea
     launch_ax<T>(m, otf, AxMode::CgFused, a, s);
     if (ev) SEM_HIP(hipEventRecord(ev[1], s));
     const int64_t nax = ax_blocks(m, sizeof(T) == 8, otf, 0);
+    if (m.direct) {
+        if (ev) SEM_HIP(hipEventRecord(ev[2], s));
+        launch_update_direct<T>(m, m.gs_struct_solo, r, w, wedge, ws.st, ws.step, ws.part_ax,
+                                (int)nax, ws.part_vec, s, pa);
+        if (ev) SEM_HIP(hipEventRecord(ev[3], s));
+        return;
+    }
     if (m.gs_struct_solo)
-        launch_edge_sums_cg<T>(m, wedge, w + m.n, ws.st, ws.part_ax, (int)nax, s);
+        launch_edge_sums_cg<T>(m, wedge, w + m.n, ws.st, step, ws.part_ax, (int)nax, s);
     else if (m.gs_in_update)
-        launch_group_sums_cg<T>(m, w, wedge, gsum, ws.st, ws.part_ax, (int)nax, s);
+        launch_group_sums_cg<T>(m, w, wedge, gsum, ws.st, step, ws.part_ax, (int)nax, s);
     else launch_gs_cg<T>(m, w, ws.st, ws.part_ax, (int)nax, s);
     if (ev) SEM_HIP(hipEventRecord(ev[2], s));
     if (m.gs_struct_solo) launch_update_struct<T>(m, r, w, ws.st, ws.part_vec, s, pa);
     else if (m.gs_in_update) launch_update_gather<T>(m, r, w, gsum, ws.st, ws.part_vec, s, pa);
     else launch_update<T>(m, r, w, ws.st, ws.part_vec, s, pa);
     if (ev) SEM_HIP(hipEventRecord(ev[3], s));
+}
+
+// After the last of a run of iterations: the state as the host reads it.
+template <typename T>
+void enqueue_close(const Mesh &m, Workspace &ws, bool otf, bool pc, hipStream_t s) {
+    if (!m.inline_scalars(sizeof(T) == 8)) return;
+    launch_close_rho(ws.st, ws.part_vec, pc ? ws.part_vec2 : nullptr, update_blocks(m, sizeof(T) == 8),
+                     ax_threads(m.N, sizeof(T) == 8, otf), s);
 }
 
 struct KernelTimes {
@@ -223,6 +252,7 @@ void run_chunk_timed(const Mesh &m, Workspace &ws, bool otf, bool pc, int chunk,
         ws.tev.push_back(e);
     }
     for (int c = 0; c < chunk; ++c) enqueue_iteration<T>(m, ws, otf, pc, s, &ws.tev[4 * c]);
+    enqueue_close<T>(m, ws, otf, pc, s);
     SEM_HIP(hipMemcpyAsync(ws.h_st, ws.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
     SEM_HIP(hipStreamSynchronize(s));
     const int done = std::min(chunk, ws.h_st->iter - iter_before);
@@ -240,6 +270,7 @@ void run_chunk(const Mesh &m, Workspace &ws, bool otf, bool pc, int chunk, bool 
     hipStream_t s = ws.stream;
     if (!use_graph) {
         for (int c = 0; c < chunk; ++c) enqueue_iteration<T>(m, ws, otf, pc, s);
+        enqueue_close<T>(m, ws, otf, pc, s);
         return;
     }
     const GraphKey key{otf, chunk, ax_shape_generation(), pc};
@@ -249,6 +280,7 @@ void run_chunk(const Mesh &m, Workspace &ws, bool otf, bool pc, int chunk, bool 
         SEM_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
         try {
             for (int c = 0; c < chunk; ++c) enqueue_iteration<T>(m, ws, otf, pc, s);
+            enqueue_close<T>(m, ws, otf, pc, s);
         } catch (...) {
             hipGraph_t junk = nullptr;
             (void)hipStreamEndCapture(s, &junk);

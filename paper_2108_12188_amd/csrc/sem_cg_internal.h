@@ -37,6 +37,7 @@ struct Workspace {
     int64_t cap_ax = 0;
     int cap_vec = 0;
     CgState *st = nullptr;          // device state of this workspace's solves
+    CgStep *step = nullptr;         // its other copy in two-launch iterations
     CgState *h_st = nullptr;        // pinned mirror
     double *hist = nullptr;         // device histories: rho [cap], alpha [cap]
     int hist_cap = 0;

@@ -47,18 +47,20 @@ gs_kernel(const GsClasses cls, int64_t lb0, int64_t nb_logical, const int32_t *_
 
 // Group sums of the classes with M >= mmin: logical blocks lb0 .. lb0 +
 // nb_logical - 1 of the class list's block numbering; the last block forms
-// alpha from the operator's partials.
+// alpha from the operator's partials (three-launch iterations: step -> st).
 template <typename T>
 __global__ void __launch_bounds__(kGsThreads)
 group_sums_kernel(const GsClasses cls, int64_t lb0, int64_t nb_logical,
                   const int32_t *__restrict__ idx, int64_t io0, const T *__restrict__ src,
-                  T *__restrict__ out, CgState *st, const double *part_ax, int64_t n_ax,
-                  int mmin) {
-    if (st->stop) return;
+                  T *__restrict__ out, CgState *st, const CgStep *step, const double *part_ax,
+                  int64_t n_ax, int mmin) {
     if (blockIdx.x == gridDim.x - 1) {
-        vecb::finalize_alpha_body(st, part_ax, n_ax);
+        if (step) vecb::alpha_block_body(st, step, part_ax, (int)n_ax);
+        else vecb::finalize_alpha_body(st, part_ax, n_ax);
         return;
     }
+    // three-launch iterations: st is being written by the alpha block
+    if (step ? step->stop : st->stop) return;
     const int64_t b = logical_block(blockIdx.x, gridDim.x - 1);
     if (b < nb_logical) gs_sums_logical_block<T>(cls, lb0 + b, idx, io0, src, out, mmin);
 }
@@ -114,15 +116,21 @@ void launch_gs_cg(const Mesh &m, T *w, CgState *st, const double *ax_partial, in
 
 template <typename T>
 void launch_group_sums_cg(const Mesh &m, const T *w, const T *wedge, T *gsum, CgState *st,
-                          const double *ax_partial, int n_ax_partial, hipStream_t s) {
+                          const CgStep *step, const double *ax_partial, int n_ax_partial, hipStream_t s) {
     const int64_t nlb = gs_logical_blocks(m) - m.gs_blk_multi;
     if (nlb > 0) {
         const bool compact = m.gsum_wedge;
         hipLaunchKernelGGL((group_sums_kernel<T>), dim3(gs_phys_blocks(nlb) + 1),
                            dim3(kGsThreads), 0, s, m.gs, m.gs_blk_multi, nlb,
                            compact ? m.wedge_idx : m.gs_idx, compact ? m.wedge_io0 : (int64_t)0,
-                           compact ? wedge : w, gsum, st, ax_partial, (int64_t)n_ax_partial, 3);
+                           compact ? wedge : w, gsum, st, step, ax_partial, (int64_t)n_ax_partial, 3);
         check_hip(hipGetLastError(), "group sums kernel launch");
+    } else if (step) {
+        hipLaunchKernelGGL((group_sums_kernel<T>), dim3(1), dim3(kGsThreads), 0, s, m.gs,
+                           (int64_t)0, (int64_t)0, (const int32_t *)nullptr, (int64_t)0,
+                           (const T *)nullptr, gsum, st, step, ax_partial,
+                           (int64_t)n_ax_partial, 0);
+        check_hip(hipGetLastError(), "alpha kernel launch");
     } else {
         launch_finalize_alpha(st, ax_partial, n_ax_partial, s);
     }
@@ -130,13 +138,19 @@ void launch_group_sums_cg(const Mesh &m, const T *w, const T *wedge, T *gsum, Cg
 
 template <typename T>
 void launch_edge_sums_cg(const Mesh &m, const T *wedge, T *gsum, CgState *st,
-                         const double *ax_partial, int n_ax_partial, hipStream_t s) {
+                         const CgStep *step, const double *ax_partial, int n_ax_partial, hipStream_t s) {
     const int64_t nlb = gs_total_blocks(m.ecls);
     if (nlb > 0) {
         hipLaunchKernelGGL((group_sums_kernel<T>), dim3(gs_phys_blocks(nlb) + 1),
                            dim3(kGsThreads), 0, s, m.ecls, (int64_t)0, nlb, m.ewedge_idx,
-                           (int64_t)0, wedge, gsum, st, ax_partial, (int64_t)n_ax_partial, 2);
+                           (int64_t)0, wedge, gsum, st, step, ax_partial, (int64_t)n_ax_partial, 2);
         check_hip(hipGetLastError(), "edge sums kernel launch");
+    } else if (step) {
+        hipLaunchKernelGGL((group_sums_kernel<T>), dim3(1), dim3(kGsThreads), 0, s, m.gs,
+                           (int64_t)0, (int64_t)0, (const int32_t *)nullptr, (int64_t)0,
+                           (const T *)nullptr, gsum, st, step, ax_partial,
+                           (int64_t)n_ax_partial, 0);
+        check_hip(hipGetLastError(), "alpha kernel launch");
     } else {
         launch_finalize_alpha(st, ax_partial, n_ax_partial, s);
     }
@@ -151,13 +165,16 @@ template void launch_gs_cg<float>(const Mesh &, float *, CgState *, const double
 template void launch_gs_cg<double>(const Mesh &, double *, CgState *, const double *, int,
                                    hipStream_t);
 template void launch_edge_sums_cg<float>(const Mesh &, const float *, float *, CgState *,
+                                         const CgStep *,
                                          const double *, int, hipStream_t);
 template void launch_edge_sums_cg<double>(const Mesh &, const double *, double *, CgState *,
+                                         const CgStep *,
                                           const double *, int, hipStream_t);
 template void launch_group_sums_cg<float>(const Mesh &, const float *, const float *, float *,
-                                          CgState *, const double *, int, hipStream_t);
+                                          CgState *, const CgStep *, const double *, int,
+                                          hipStream_t);
 template void launch_group_sums_cg<double>(const Mesh &, const double *, const double *,
-                                           double *, CgState *, const double *, int,
-                                           hipStream_t);
+                                           double *, CgState *, const CgStep *,
+                                           const double *, int, hipStream_t);
 
 }  // namespace sem

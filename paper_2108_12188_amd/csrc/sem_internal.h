@@ -18,6 +18,28 @@ constexpr int kMaxMultiplicity = 127;
 constexpr uint8_t kDirichletBit = 0x80;
 constexpr uint8_t kMultMask = 0x7F;
 constexpr int kMaxP = kMaxOrder + 1;
+// Schedules of a CG iteration on a conforming mesh (see DirectArgs): up to
+// kDirectMaxPoints local points two launches, up to kInlineMaxPoints (FP64:
+// half of it) three, beyond it four.  On the fly, us per iteration with four
+// launches and with the schedule taken here: FP32 N = 7 0.11 M points 15.3 /
+// 12.3, 0.88 M 21.8 / 18.9 (two launches; 1.7 M with two: 27.8 / 30.6, the
+// group sums formed once per copy), 4.1 M 45.2 / 43.2 (three; 8 M N = 5 76.1 /
+// 79.1), N = 9 2.2 M 40.5 / 36.0, 4.1 M 52.6 / 46.4; FP64 N = 9 0.5 M 29.8 /
+// 26.4, N = 8 2 M 54.9 / 51.5 (4.1 M N = 9 with three: 91.8 / 94.6).  N = 7
+// in FP32 keeps four launches between 2^20 and 2^21 points, where each of its
+// one-wave blocks would sum the partials for one element (1.4 M: 25.0 / 25.6,
+// 1.7 M 27.7 / 29.0).
+constexpr int64_t kDirectMaxPoints = int64_t(1) << 20;
+constexpr int64_t kInlineMaxPoints = int64_t(1) << 22;
+inline bool takes_inline_scalars(int N, int64_t n, bool fp64) {
+    if (n <= kDirectMaxPoints) return true;
+    if (fp64) return n <= kInlineMaxPoints / 2;
+    return n <= kInlineMaxPoints && (N != 7 || n >= kInlineMaxPoints / 2);
+}
+// most blocks of the update there, in equal steps: every operator block sums
+// their partials (FP32 N = 7 4.1 M points: 1000 blocks 43.2 us, 2000 45.7;
+// N = 8 1.6 M: 781 blocks 29.7, 1562 31.0)
+constexpr int kInlineVecBlocks = 1280;
 // local points from which a mesh takes the table-free gather by default
 // (below it, where a CG iteration is mostly launch latency, the table form
 // measured up to 8% faster; from it on the table-free form is as fast or
@@ -50,6 +72,11 @@ __host__ __device__ inline int edge_slot(int N, int i, int j, int k) {
     const bool corner = (i == 0 || i == N) && (j == 0 || j == N);
     return corner ? cb + 1 + k : -1;
 }
+// Number (0..7) of the element corner at an edge slot, -1 for other slots.
+__host__ __device__ inline int corner_of_slot(int N, int s) {
+    const int P = N + 1, c = s / P, k = s - c * P;
+    return (c < 4 && k < 2) ? 2 * c + k : -1;
+}
 
 // Distance of two elements' tiles in the local operator's LDS, in values
 // (see the tile layout in sem_ax_order.hip).
@@ -73,24 +100,34 @@ void check_hip(hipError_t e, const char *what);
 // the kernels that follow in stream order.
 // ---------------------------------------------------------------------------
 struct CgState {
+    // what changes from iteration to iteration
     double rho;        // rho_{i-1}: <r, r, c> of the current residual (<r, z, c>
                        // with a preconditioner)
     double rr;         // <r, r, c> of the current residual
-    double rho0;       // <r0, r0, c>
     double alpha;      // alpha_i
     double beta;       // beta_{i-1} used by the next p-update
     double pw;         // <p, w, c> of the current iteration
-    double thresh;     // stop when rr <= thresh (= tol^2 rho_0)
     int iter;          // completed iterations
-    int max_iter;      // iteration cap
     int stop;          // 0 running, 1 converged, 2 cap reached, 3 breakdown
-    int fixed;         // 1: no convergence test
     int x_lag;         // 1: x still lacks alpha_i p_i of the last completed
                        // update (single-mesh solves apply it in the next
                        // operator launch, or in the closing flush)
+    int rho_pending;   // 1: the partials of the last update hold the next rho,
+                       // not summed yet (two-launch iterations, see DirectArgs)
+    // fixed during a solve
+    double rho0;       // <r0, r0, c>
+    double thresh;     // stop when rr <= thresh (= tol^2 rho_0)
+    int max_iter;      // iteration cap
+    int fixed;         // 1: no convergence test
     int hist_len;      // capacity of the history arrays
+    int pad_;
     double *hist_rho;  // device history (may be null)
     double *hist_alpha;
+};
+// The part that the two copies of a two-launch iteration pass back and forth.
+struct CgStep {
+    double rho, rr, alpha, beta, pw;
+    int iter, stop, x_lag, rho_pending;
 };
 
 // ---------------------------------------------------------------------------
@@ -206,6 +243,22 @@ struct Mesh {
     int32_t *ewedge_idx = nullptr;
     uint32_t p3_magic = 0;
     int p3_shift = 0;
+    // Two-launch CG iterations (n <= kDirectMaxPoints, every group of more
+    // than two copies made of edge and corner nodes): the update sums those
+    // groups itself from the operator's compact edge array.  elist[e * MS +
+    // s] (MS = edge_slots(N)): the positions in that array of the copies of
+    // the node at edge slot s of element e, ascending, -1 past the last; the
+    // fifth to eighth copy of a corner node in elist_hi[8 e + corner] (see
+    // corner_of_slot).  More copies than that: {-2, offset into egen, count,
+    // 0}.  gsrc_direct is gsrc with e * MS + s for the points of groups of
+    // more than two copies.
+    bool inline32 = false, inline64 = false;   // two or three launches, per precision
+    bool inline_scalars(bool fp64) const { return fp64 ? inline64 : inline32; }
+    bool direct = false;
+    int4 *elist = nullptr;         // [E][MS]
+    int4 *elist_hi = nullptr;      // [E][8]
+    int32_t *egen = nullptr;
+    int32_t *gsrc_direct = nullptr;   // [n]
     // Jacobi preconditioner (built on first use): 1 / diag(A) on the free
     // points, 0 on the Dirichlet points, local form
     double *minv64 = nullptr;
@@ -259,7 +312,14 @@ struct HostTables {
     std::vector<int32_t> ewedge_idx;
     uint32_t p3_magic = 0;
     int p3_shift = 0;
+    // two-launch iterations, see Mesh::direct (build_direct_tables)
+    bool direct = false;
+    std::vector<int4> elist, elist_hi;
+    std::vector<int32_t> egen;
+    std::vector<int32_t> gsrc_direct;   // gsrc with the edge slots of larger groups
 };
+// Fills the tables of the two-launch iteration where it applies.
+void build_direct_tables(int64_t E, int N, HostTables &t);
 // Validates glob_id / dirichlet (fail() on error) and fills t.
 void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, HostTables &t);
 
@@ -300,7 +360,49 @@ struct AxArgs {
                                 // N = 7; one element per wave-sized block)
     int stream;                 // CgFused FP32: p and x accesses non-temporal
                                 // (cg_streams_vectors of the iteration's footprint)
+    // Two- and three-launch iterations (null / 0: the state is final when this runs):
+    // every block sums the last update's rho partials itself and block 0
+    // writes the new state to st_out, which nothing else of this launch reads.
+    CgStep *st_out;
+    const double *rho_part;     // partials of <r, r, c>, or of <r, z, c>
+    const double *rr_part;      // preconditioned: partials of <r, r, c>
+    int n_rho;
 };
+
+// Two- and three-launch CG iterations.  The four-launch form spends a launch
+// on the one-block sum of rho and a dependent launch on the group sums (and
+// alpha).  With three launches the operator's blocks each sum the rho
+// partials of the last update; with two the update's blocks also each sum the
+// operator's partials to alpha, and the edge-node groups they need; the state passes from the solve's CgState through the operator
+// to a CgStep beside it and through the update back, each launch reading one
+// copy while its block 0 writes the other.
+constexpr int kMaxAxThreads = 512;      // largest operator block
+template <typename T>
+struct DirectArgs {
+    const CgStep *st_in;        // the step the operator left
+    const double *part_ax;      // the operator's partials of <p, w, c>
+    int n_ax;
+    const T *wedge;             // the operator's compact edge array
+    const int4 *elist, *elist_hi;
+    const int32_t *egen;
+    int N;
+    uint32_t p3_magic;          // l / P^3 = (l * p3_magic) >> p3_shift for l < 2^31
+    int p3_shift;
+    uint32_t ms_magic;          // k / MS = (k * ms_magic) >> 20 for k < 1024
+};
+
+// step: the CgStep beside a workspace's state
+template <typename T>
+DirectArgs<T> direct_args(const Mesh &m, const CgStep *step, const T *wedge,
+                          const double *part_ax, int n_ax) {
+    // l * (magic P^3 - 2^shift) < 2^31 * 2^lg <= 2^shift, and the same for MS <= 128
+    int lg = 0;
+    while ((1 << lg) < m.P3) ++lg;
+    const int shift = 31 + lg;
+    return {step, part_ax, n_ax, wedge, m.elist, m.elist_hi, m.egen, m.N,
+            (uint32_t)(((uint64_t)1 << shift) / (uint64_t)m.P3 + 1), shift,
+            (1u << 20) / (uint32_t)edge_slots(m.N) + 1};
+}
 
 // Jacobi preconditioning in the CG update (preconditioned CG, Sec. 3.2;
 // Algorithm 1 is its unpreconditioned case): z = minv r is written, and the block partials of
@@ -328,6 +430,8 @@ constexpr int kAxEngineDefault = 0, kAxEngineValu = 1, kAxEngineMfma = 2;
 bool ax_mfma_available(int N, bool fp64);
 void ax_engine_set(int N, bool fp64, bool otf, int engine);
 int ax_shape_generation();
+// threads of a block of the CG-fused operator
+int ax_threads(int N, bool fp64, bool otf);
 
 // Fills the basis / geometry pointers and the shape from the mesh; the
 // caller sets u, p, w, mcode, st, partial (and epb to force a shape).
@@ -356,7 +460,8 @@ void ax_batch_desc(const Mesh &m, bool otf, AxArgs<float> &a);
 // One FP32 CG-fused operator launch over many problems of order N:
 // blk[b] = (descriptor index, virtual block).
 // stream: p and x non-temporal (cg_streams_vectors of the batch's footprint)
-void launch_ax_batch(int N, bool otf, bool mfma, bool stream, const AxArgs<float> *descs,
+// rho: every problem's rho is formed first (AxArgs::st_out set in all of them)
+void launch_ax_batch(int N, bool otf, bool mfma, bool stream, bool rho, const AxArgs<float> *descs,
                      const int2 *blk, int64_t nblk, int epb, const double *D, const double *xi,
                      const double *w,
                      hipStream_t s);
@@ -375,16 +480,19 @@ void launch_gs_cg(const Mesh &m, T *w, CgState *st, const double *ax_partial, in
 // k-th group with m > 2 (ascending local index; read from wedge, the
 // operator's compact copy of the edge and corner nodes, when m.gsum_wedge,
 // else from w; neither is modified), and alpha.
+// step (may be null): a three-launch iteration, alpha goes from step to st.
 template <typename T>
 void launch_group_sums_cg(const Mesh &m, const T *w, const T *wedge, T *gsum, CgState *st,
-                          const double *ax_partial, int n_ax_partial, hipStream_t s);
+                          const CgStep *step, const double *ax_partial, int n_ax_partial,
+                          hipStream_t s);
 // The same for the table-free gather (needs m.gs_struct): gsum[k] = sum of
 // the copies of the k-th edge or corner group of two or more copies
 // (ascending local index, read from wedge, the operator's compact edge
 // array), then alpha.
 template <typename T>
 void launch_edge_sums_cg(const Mesh &m, const T *wedge, T *gsum, CgState *st,
-                         const double *ax_partial, int n_ax_partial, hipStream_t s);
+                         const CgStep *step, const double *ax_partial, int n_ax_partial,
+                         hipStream_t s);
 int gs_cg_blocks(const Mesh &m);
 int64_t gs_logical_blocks(const Mesh &m);
 
@@ -392,6 +500,8 @@ int64_t gs_logical_blocks(const Mesh &m);
 // partial per block (`partial`, at least vec_blocks(n) entries) and a
 // one-block finalize kernel sums them in index order.
 int vec_blocks(int64_t n);
+// blocks (and partials) of the CG update of a mesh
+int update_blocks(const Mesh &m, bool fp64);
 // r -= alpha mask(w); rho = <r, r, c>; then beta, convergence, history (x is
 // advanced by the next operator launch or launch_x_flush)
 template <typename T>
@@ -412,6 +522,16 @@ void launch_update_gather(const Mesh &m, T *r, const T *w, const T *gsum, CgStat
 template <typename T>
 void launch_update_struct(const Mesh &m, T *r, const T *wg, CgState *st, double *partial,
                           hipStream_t s, PcArgs<T> pc = PcArgs<T>{});
+// The same two forms leave rho to the next operator launch when
+// m.inline_scalars().  In a two-launch iteration (m.direct): step -> st.
+template <typename T>
+void launch_update_direct(const Mesh &m, bool table_free, T *r, const T *w, const T *wedge,
+                          CgState *st, const CgStep *step, const double *part_ax, int n_ax, double *partial,
+                          hipStream_t s, PcArgs<T> pc = PcArgs<T>{});
+// Ends a run of two-launch iterations: the pending rho, as the next operator
+// launch (nthr threads a block) would form it.
+void launch_close_rho(CgState *st, const double *partial, const double *partial2, int cnt,
+                      int nthr, hipStream_t s);
 // r = b - w (w may be null: r = b); p = 0; rho_0 = <r, r, c>; initial state.
 // With pc.minv: z = minv r, rho = <r, z, c>, and the threshold and the
 // reported residual use <r, r, c>.

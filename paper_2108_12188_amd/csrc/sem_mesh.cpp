@@ -40,7 +40,8 @@ void free_mesh_arrays(Mesh *m) {
     void *ptrs[] = {m->vert64,     m->vert32,  m->edge32,  m->G32,     m->G64,       m->B64,
                     m->mcode,      m->gs_idx,  m->gs_lb_order, m->dir_idx, m->gsrc,
                     m->wedge_idx,  m->basis_blob, m->scratch, m->state,   m->minv64,
-                    m->minv32,     m->erec,    m->pos_tab, m->ewedge_idx};
+                    m->minv32,     m->erec,    m->pos_tab, m->ewedge_idx, m->elist, m->elist_hi,
+                    m->egen,       m->gsrc_direct};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -77,6 +78,8 @@ size_t mesh_footprint(int64_t E, int N, uint32_t flags, sem_precision prec) {
         const size_t ms = (size_t)edge_slots(N);
         b += (size_t)E * (6 + ms) * 8 + ((size_t)E * ms + 8 * kMaxGsClasses) * 4 + P3 * 4;
     }
+    if (n <= (size_t)kDirectMaxPoints)             // two-launch iteration: edge lists
+        b += (size_t)E * ((edge_slots(N) + 8) * 16 + edge_slots(N) * 4) + n * 4;
     if (flags & SEM_MESH_G_FP32) b += n * 24;
     if (flags & SEM_MESH_G_FP64) b += n * 48;
     b += ((size_t)vec_blocks((int64_t)n) + 16) * 8 + sizeof(CgState) + 4096;
@@ -129,6 +132,10 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
         t.gsum_wedge = false;
         t.gs_struct = false;
     }
+    build_direct_tables(E, N, t);
+    m->direct = t.direct;
+    m->inline32 = t.gs_in_update && takes_inline_scalars(N, n, false);
+    m->inline64 = t.gs_in_update && takes_inline_scalars(N, n, true);
     m->n_glob = t.n_glob;
     m->gs = t.gs;
     m->n_groups = t.n_groups;
@@ -169,8 +176,18 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
         m->gs_idx = dev_alloc<int32_t>(*m, t.gs_idx.size());
         m->gs_lb_order = dev_alloc<int32_t>(*m, t.gs_lb_order.size());
         m->dir_idx = dev_alloc<int32_t>(*m, t.dir_idx.size());
-        if (t.gs_in_update && !m->gs_struct_solo) m->gsrc = dev_alloc<int32_t>(*m, t.gsrc.size());
+        // a mesh that runs two launches alone and the table-free form in
+        // batches needs no group ranks
+        const bool table = t.gs_in_update && !m->gs_struct_solo;
+        if (table && !(m->direct && m->gs_struct))
+            m->gsrc = dev_alloc<int32_t>(*m, t.gsrc.size());
+        if (table && m->direct) m->gsrc_direct = dev_alloc<int32_t>(*m, t.gsrc_direct.size());
         if (t.gsum_wedge) m->wedge_idx = dev_alloc<int32_t>(*m, t.wedge_idx.size());
+        if (m->direct) {
+            m->elist = dev_alloc<int4>(*m, t.elist.size());
+            m->elist_hi = dev_alloc<int4>(*m, t.elist_hi.size());
+            m->egen = dev_alloc<int32_t>(*m, t.egen.size());   // null: none
+        }
         if (m->gs_struct) {
             m->erec = dev_alloc<ElemRec>(*m, t.erec.size());
             m->pos_tab = dev_alloc<uint32_t>(*m, t.pos_tab.size());
@@ -226,7 +243,13 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
         upload(m->gs_lb_order, t.gs_lb_order.data(), t.gs_lb_order.size(), s);
         if (SEM_GS_BLOCK_ORDER) m->gs.lb_order = m->gs_lb_order;
         upload(m->dir_idx, t.dir_idx.data(), t.dir_idx.size(), s);
-        if (t.gs_in_update && !m->gs_struct_solo) upload(m->gsrc, t.gsrc.data(), t.gsrc.size(), s);
+        if (m->gsrc) upload(m->gsrc, t.gsrc.data(), t.gsrc.size(), s);
+        if (m->gsrc_direct) upload(m->gsrc_direct, t.gsrc_direct.data(), t.gsrc_direct.size(), s);
+        if (m->direct) {
+            upload(m->elist, t.elist.data(), t.elist.size(), s);
+            upload(m->elist_hi, t.elist_hi.data(), t.elist_hi.size(), s);
+            upload(m->egen, t.egen.data(), t.egen.size(), s);
+        }
         if (t.gsum_wedge) upload(m->wedge_idx, t.wedge_idx.data(), t.wedge_idx.size(), s);
         if (m->gs_struct) {
             upload(m->erec, t.erec.data(), t.erec.size(), s);

@@ -399,4 +399,54 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     t.gs_struct = ok && build_struct_tables(E, N, mcode, plink, cnt, start, byid, t);
 }
 
+void build_direct_tables(int64_t E, int N, HostTables &t) {
+    const int MS = edge_slots(N);
+    const int64_t n = E * (N + 1) * (N + 1) * (N + 1);
+    t.direct = false;
+    if (!t.gs_in_update || n > kDirectMaxPoints) return;
+    if (t.n_groups_multi > 0 && !t.gsum_wedge) return;
+    // every slot its own value, then the groups: of more than two copies
+    // (the per-point table adds pairs by their partner's index), or with the
+    // table-free gather every edge-node group off the Dirichlet boundary
+    t.elist.resize((size_t)(E * MS));
+    for (int64_t g = 0; g < E * MS; ++g) t.elist[(size_t)g] = make_int4((int)g, -1, -1, -1);
+    t.elist_hi.assign((size_t)(E * 8), make_int4(-1, -1, -1, -1));
+    t.egen.clear();
+    const auto add_group = [&](const int32_t *pos, int M) {
+        const int gen = (int)t.egen.size();
+        for (int q = 0; q < M; ++q) {
+            const int64_t g = pos[q], e = g / MS;
+            const int cn = M > 4 ? corner_of_slot(N, (int)(g - e * MS)) : -1;
+            if (M > (cn >= 0 ? 8 : 4)) {
+                if ((int)t.egen.size() == gen) t.egen.insert(t.egen.end(), pos, pos + M);
+                t.elist[(size_t)g] = make_int4(-2, gen, M, 0);
+                continue;
+            }
+            t.elist[(size_t)g] = make_int4(pos[0], M > 1 ? pos[1] : -1, M > 2 ? pos[2] : -1,
+                                           M > 3 ? pos[3] : -1);
+            if (M > 4)
+                t.elist_hi[(size_t)(8 * e + cn)] =
+                    make_int4(pos[4], M > 5 ? pos[5] : -1, M > 6 ? pos[6] : -1,
+                              M > 7 ? pos[7] : -1);
+        }
+    };
+    if (t.gs_struct) {
+        for (int c = 0; c < t.ecls.ncls; ++c)
+            for (int64_t k = 0; k < t.ecls.ng[c]; ++k)
+                add_group(t.ewedge_idx.data() + t.ecls.io[c] + k * t.ecls.M[c], t.ecls.M[c]);
+    }
+    t.gsrc_direct = t.gsrc;
+    for (int c = 0; c < t.gs.ncls; ++c) {
+        const int M = t.gs.M[c];
+        if (M <= 2) continue;
+        for (int64_t k = 0; k < t.gs.ng[c]; ++k) {
+            const int32_t *ix = t.gs_idx.data() + t.gs.io[c] + k * M;
+            const int32_t *pos = t.wedge_idx.data() + (t.gs.io[c] - t.wedge_io0) + k * M;
+            for (int q = 0; q < M; ++q) t.gsrc_direct[(size_t)ix[q]] = pos[q];
+            if (!t.gs_struct) add_group(pos, M);
+        }
+    }
+    t.direct = true;
+}
+
 }  // namespace sem

@@ -48,6 +48,29 @@ update_struct_kernel(int64_t n, T *__restrict__ r, const T *__restrict__ wg,
     update_struct_body<T, PC>(n, r, wg, sm, st, partial, blockIdx.x, gridDim.x, pc);
 }
 
+template <typename T, bool PC, int TASKS>
+__global__ void __launch_bounds__(kVecThreads)
+update_gather_direct_kernel(int64_t n, T *__restrict__ r, const T *__restrict__ w,
+                            const uint8_t *__restrict__ mcode, const GatherMap gm, CgState *st,
+                            double *partial, PcArgs<T> pc, const DirectArgs<T> dir) {
+    update_direct_body<T, PC, false, TASKS>(n, r, w, mcode, gm, StructMap{}, st, partial,
+                                            blockIdx.x, gridDim.x, pc, dir);
+}
+
+template <typename T, bool PC, int TASKS>
+__global__ void __launch_bounds__(kVecThreads)
+update_struct_direct_kernel(int64_t n, T *__restrict__ r, const T *__restrict__ w,
+                            const StructMap sm, CgState *st, double *partial, PcArgs<T> pc,
+                            const DirectArgs<T> dir) {
+    update_direct_body<T, PC, true, TASKS>(n, r, w, nullptr, GatherMap{}, sm, st, partial,
+                                           blockIdx.x, gridDim.x, pc, dir);
+}
+
+__global__ void __launch_bounds__(kMaxAxThreads)
+close_rho_kernel(CgState *st, const double *partial, const double *partial2, int cnt, int nthr) {
+    close_rho_body(st, partial, partial2, cnt, nthr);
+}
+
 __global__ void __launch_bounds__(kFinalizeThreads)
 finalize_rho_kernel(CgState *st, const double *partial, int cnt, const double *partial2) {
     finalize_rho_body(st, partial, cnt, partial2);
@@ -118,6 +141,7 @@ finalize_init_kernel(CgState *st, const double *partial, int cnt, const double *
         st->beta = 0.0;
         st->alpha = 0.0;
         st->x_lag = 0;
+        st->rho_pending = 0;
         st->iter = 0;
         if (st->hist_rho && st->hist_len > 0) st->hist_rho[0] = rho0;
         int stop = 0;
@@ -218,6 +242,13 @@ int vec_blocks(int64_t n) {
     return (int)(b > 0 ? b : 1);
 }
 
+int update_blocks(const Mesh &m, bool fp64) {
+    const int b = vec_blocks(m.n);
+    if (!m.inline_scalars(fp64) || b <= kInlineVecBlocks) return b;
+    const int steps = (b + kInlineVecBlocks - 1) / kInlineVecBlocks;   // equal steps, as above
+    return (b + steps - 1) / steps;
+}
+
 template <typename T>
 void launch_update(const Mesh &m, T *r, const T *w, CgState *st, double *partial,
                    hipStream_t s, PcArgs<T> pc) {
@@ -254,14 +285,15 @@ void launch_update_gather(const Mesh &m, T *r, const T *w, const T *gsum, CgStat
         fail(SEM_EUNSUPPORTED, "mesh shares points inside elements: no gather in the update");
     if (!m.gsrc) fail(SEM_EUNSUPPORTED, "mesh holds no per-point gather table");
     const GatherMap gm{m.gsrc};
-    const int nb = vec_blocks(m.n);
+    const int nb = update_blocks(m, sizeof(T) == 8);
     if (pc.minv)
         hipLaunchKernelGGL((update_gather_kernel<T, true>), dim3(nb), dim3(kVecThreads), 0, s,
                            m.n, r, w, gsum, m.mcode, gm, st, partial, pc);
     else
         hipLaunchKernelGGL((update_gather_kernel<T, false>), dim3(nb), dim3(kVecThreads), 0, s,
                            m.n, r, w, gsum, m.mcode, gm, st, partial, pc);
-    hipLaunchKernelGGL(finalize_rho_kernel, dim3(1), dim3(kFinalizeThreads), 0, s, st,
+    if (!m.inline_scalars(sizeof(T) == 8))
+        hipLaunchKernelGGL(finalize_rho_kernel, dim3(1), dim3(kFinalizeThreads), 0, s, st,
                        (const double *)partial, nb, (const double *)pc.partial2);
     check_hip(hipGetLastError(), "update kernel launch");
 }
@@ -272,16 +304,61 @@ void launch_update_struct(const Mesh &m, T *r, const T *wg, CgState *st, double 
     if (!m.gs_struct) fail(SEM_EUNSUPPORTED, "mesh has no table-free gather");
     if (m.P3 > kMaxPosTab || m.n % 4) fail(SEM_EUNSUPPORTED, "table-free gather: bad order");
     const StructMap sm{m.erec, m.pos_tab, m.P3, 6 + edge_slots(m.N), m.p3_magic, m.p3_shift};
-    const int nb = vec_blocks(m.n);
+    const int nb = update_blocks(m, sizeof(T) == 8);
     if (pc.minv)
         hipLaunchKernelGGL((update_struct_kernel<T, true>), dim3(nb), dim3(kVecThreads), 0, s,
                            m.n, r, wg, sm, st, partial, pc);
     else
         hipLaunchKernelGGL((update_struct_kernel<T, false>), dim3(nb), dim3(kVecThreads), 0, s,
                            m.n, r, wg, sm, st, partial, pc);
-    hipLaunchKernelGGL(finalize_rho_kernel, dim3(1), dim3(kFinalizeThreads), 0, s, st,
+    if (!m.inline_scalars(sizeof(T) == 8))
+        hipLaunchKernelGGL(finalize_rho_kernel, dim3(1), dim3(kFinalizeThreads), 0, s, st,
                        (const double *)partial, nb, (const double *)pc.partial2);
     check_hip(hipGetLastError(), "update kernel launch");
+}
+
+namespace {
+template <typename T, bool PC, int TASKS>
+void update_direct_form(const Mesh &m, bool table_free, T *r, const T *w, CgState *st,
+                        double *partial, hipStream_t s, const PcArgs<T> &pc,
+                        const DirectArgs<T> &dir) {
+    const int nb = update_blocks(m, sizeof(T) == 8);
+    if (table_free) {
+        const StructMap sm{m.erec, m.pos_tab, m.P3, 6 + edge_slots(m.N), m.p3_magic, m.p3_shift};
+        hipLaunchKernelGGL((update_struct_direct_kernel<T, PC, TASKS>), dim3(nb),
+                           dim3(kVecThreads), 0, s, m.n, r, w, sm, st, partial, pc, dir);
+    } else {
+        hipLaunchKernelGGL((update_gather_direct_kernel<T, PC, TASKS>), dim3(nb),
+                           dim3(kVecThreads), 0, s, m.n, r, w, m.mcode, GatherMap{m.gsrc_direct}, st,
+                           partial, pc, dir);
+    }
+}
+}  // namespace
+
+template <typename T>
+void launch_update_direct(const Mesh &m, bool table_free, T *r, const T *w, const T *wedge,
+                          CgState *st, const CgStep *step, const double *part_ax, int n_ax,
+                          double *partial, hipStream_t s, PcArgs<T> pc) {
+    if (!m.direct) fail(SEM_EUNSUPPORTED, "mesh has no tables of the two-launch iteration");
+    if (table_free ? (!m.gs_struct || m.n % 4 != 0) : !m.gsrc_direct)
+        fail(SEM_EUNSUPPORTED, "mesh has no tables of this gather");
+    const DirectArgs<T> dir = direct_args<T>(m, step, wedge, part_ax, n_ax);
+    const bool one = direct_tasks(m.N) == 1;
+    if (pc.minv) {
+        if (one) update_direct_form<T, true, 1>(m, table_free, r, w, st, partial, s, pc, dir);
+        else update_direct_form<T, true, 2>(m, table_free, r, w, st, partial, s, pc, dir);
+    } else {
+        if (one) update_direct_form<T, false, 1>(m, table_free, r, w, st, partial, s, pc, dir);
+        else update_direct_form<T, false, 2>(m, table_free, r, w, st, partial, s, pc, dir);
+    }
+    check_hip(hipGetLastError(), "update kernel launch");
+}
+
+void launch_close_rho(CgState *st, const double *partial, const double *partial2, int cnt,
+                      int nthr, hipStream_t s) {
+    hipLaunchKernelGGL(close_rho_kernel, dim3(1), dim3(nthr), 0, s, st, partial, partial2, cnt,
+                       nthr);
+    check_hip(hipGetLastError(), "rho kernel launch");
 }
 
 template <typename T>
@@ -359,6 +436,14 @@ template void launch_update_struct<float>(const Mesh &, float *, const float *, 
                                           double *, hipStream_t, PcArgs<float>);
 template void launch_update_struct<double>(const Mesh &, double *, const double *, CgState *,
                                            double *, hipStream_t, PcArgs<double>);
+template void launch_update_direct<float>(const Mesh &, bool, float *, const float *,
+                                          const float *, CgState *, const CgStep *,
+                                          const double *, int, double *, hipStream_t,
+                                          PcArgs<float>);
+template void launch_update_direct<double>(const Mesh &, bool, double *, const double *,
+                                           const double *, CgState *, const CgStep *,
+                                           const double *, int, double *, hipStream_t,
+                                           PcArgs<double>);
 template void launch_cg_init<float>(const Mesh &, const float *, const float *, float *, float *,
                                     CgState *, double *, hipStream_t, PcArgs<float>);
 template void launch_cg_init<double>(const Mesh &, const double *, const double *, double *,

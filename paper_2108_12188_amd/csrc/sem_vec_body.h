@@ -437,6 +437,334 @@ __device__ __forceinline__ void update_struct_body(int64_t n, T *__restrict__ r,
     }
 }
 
+// alpha_i = rho_{i-1} / <p, w, c> on the step the operator left; false: the
+// update does not run (stopped before, or CG broke down).
+__device__ __forceinline__ bool alpha_step(CgStep &h, double pw) {
+    if (h.stop) return false;
+    h.alpha = h.rho / pw;
+    h.pw = pw;
+    const bool ok = pw > 0.0 && isfinite(h.alpha);
+    h.x_lag = h.rho_pending = ok ? 1 : 0;
+    h.stop = ok ? 0 : 3;
+    return ok;
+}
+// hist_alpha, hist_len: the state's, read by the caller with its other loads
+__device__ __forceinline__ void store_alpha_step(CgState *st, const CgStep &h, bool was_stopped,
+                                                 double *hist_alpha, int hist_len) {
+    store_step(st, h);
+    if (!was_stopped && hist_alpha && h.iter + 1 < hist_len) hist_alpha[h.iter + 1] = h.alpha;
+}
+// The alpha block (256 threads) of a three-launch iteration: the same sum in
+// the same order as the update of a two-launch one.
+__device__ __forceinline__ void alpha_block_body(CgState *st, const CgStep *step,
+                                                 const double *part_ax, int n_ax) {
+    __shared__ double red[16];
+    CgStep h = *step;
+    const bool stopped = h.stop != 0;
+    double *const hist_alpha = st->hist_alpha;
+    const int hist_len = st->hist_len;
+    const double pw = sum_partials_all(part_ax, n_ax, kVecThreads, red);
+    alpha_step(h, pw);
+    if (threadIdx.x == 0) store_alpha_step(st, h, stopped, hist_alpha, hist_len);
+}
+
+// ---------------------------------------------------------------------------
+// The update of a two-launch iteration (DirectArgs): alpha from the
+// operator's partials, the edge-node groups' sums, the gather, r and the
+// partials of rho, in one launch.
+//
+// Bound by latency: a block takes one step of 256 packs, so what counts is
+// the number of dependent rounds of loads.  They are laid out by hand: (1)
+// the tables (edge lists; the packs' gather sources, or positions), the
+// operator's partials, r and w; (2) the edge copies and the gathered values
+// (table-free: the element records first, one round more); alpha is summed
+// while (2) flies.  FP32 CG, N = 7, 210 elements: four launches 15.6 us an
+// iteration, two 9.9.
+// ---------------------------------------------------------------------------
+
+// Edge slots of the elements a block step of 256 packs touches: at most
+// 1024 at every order (N = 1: 128 elements of 8 slots).
+constexpr int kMaxStepSlots = 1024;
+// Slots a thread of 256 loads ahead: 1 where a step's elements have at most
+// 256 (N = 7, 10, 11), else 2 (the rest of N = 1 and 2 is looped over).
+__host__ __device__ constexpr int direct_tasks(int N) { return N == 7 || N >= 10 ? 1 : 2; }
+
+// The positions (in the operator's edge array) of one slot's copies, and
+// their values: a missing copy reads position 0, one line for the whole wave
+// (and is not added).
+// Every load is unconditional: under a condition the compiler waits for it
+// where the paths join.
+template <typename T>
+struct SlotCopies {
+    int4 lo, hi;
+    T v[8];
+    __device__ __forceinline__ void load_list(const DirectArgs<T> &d, int64_t g, int64_t corner) {
+        lo = d.elist[g];
+        hi = d.elist_hi[corner < 0 ? 0 : corner];
+        if (corner < 0) hi = make_int4(-1, -1, -1, -1);
+    }
+    __device__ __forceinline__ void load_values(const DirectArgs<T> &d) {
+        v[0] = d.wedge[lo.x < 0 ? 0 : lo.x];
+        v[1] = d.wedge[lo.y < 0 ? 0 : lo.y];
+        v[2] = d.wedge[lo.z < 0 ? 0 : lo.z];
+        v[3] = d.wedge[lo.w < 0 ? 0 : lo.w];
+        v[4] = d.wedge[hi.x < 0 ? 0 : hi.x];
+        v[5] = d.wedge[hi.y < 0 ? 0 : hi.y];
+        v[6] = d.wedge[hi.z < 0 ? 0 : hi.z];
+        v[7] = d.wedge[hi.w < 0 ? 0 : hi.w];
+    }
+    // the group's sum in ascending local index
+    __device__ __forceinline__ T sum(const DirectArgs<T> &d) const {
+        T s = v[0];
+        s = lo.y >= 0 ? s + v[1] : s;
+        s = lo.z >= 0 ? s + v[2] : s;
+        s = lo.w >= 0 ? s + v[3] : s;
+        s = hi.x >= 0 ? s + v[4] : s;
+        s = hi.y >= 0 ? s + v[5] : s;
+        s = hi.z >= 0 ? s + v[6] : s;
+        s = hi.w >= 0 ? s + v[7] : s;
+        if (d.egen && lo.x == -2) {            // more copies than the lists hold
+            const int32_t *ix = d.egen + lo.y;
+            s = d.wedge[ix[0]];
+            for (int t = 1; t < lo.z; ++t) s += d.wedge[ix[t]];
+        }
+        return s;
+    }
+};
+__host__ __device__ __forceinline__ int corner_of_slot_fast(int P, int s) {
+    const int c = (s >= P) + (s >= 2 * P) + (s >= 3 * P);
+    return s < 4 * P && s - c * P < 2 ? 2 * c + (s - c * P) : -1;
+}
+
+__device__ __forceinline__ void load_fence() { __asm__ volatile("" ::: "memory"); }
+
+// Virtual block vb of vgrid.  STRUCT: the table-free gather (sm), else the
+// per-point table (mcode, gm).  TASKS: edge slots a thread loads ahead
+// (direct_tasks of the order).  st: the state this update completes, written
+// by block 0; dir.st_in: the state the operator left.
+template <typename T, bool PC, bool STRUCT, int TASKS>
+__device__ __forceinline__ void update_direct_body(int64_t n, T *__restrict__ r,
+                                                   const T *__restrict__ w,
+                                                   const uint8_t *__restrict__ mcode,
+                                                   const GatherMap &gm, const StructMap &sm,
+                                                   CgState *st, double *partial, int64_t vb,
+                                                   int64_t vgrid, const PcArgs<T> &pc,
+                                                   const DirectArgs<T> &dir) {
+    __shared__ double cw[kVecThreads];
+    __shared__ double red[16], red_pw[4];   // two: no barrier lies between their uses
+    __shared__ T es[kMaxStepSlots];
+    const int P = dir.N + 1, MS = edge_slots(dir.N);
+    const int64_t n4 = n >> 2;
+    const int64_t stride = vgrid * kVecThreads;
+    const int t0 = (int)threadIdx.x;
+    const int64_t qb = xcd_block(vb, vgrid) * kVecThreads;      // the block's first pack
+    double acc = 0.0, acc2 = 0.0;
+    T a = T(0);
+    CgStep h = *dir.st_in;
+    const bool stopped = h.stop != 0;
+    double *const hist_alpha = st->hist_alpha;
+    const int hist_len = st->hist_len;
+    // the weights' table (read after the first barrier)
+    {
+        const int m = t0 & kMultMask;
+        cw[t0] = m ? 1.0 / (double)m : 0.0;
+    }
+    // a block's threads step together; packs past the end repeat the last
+    // one, store nothing and add nothing
+    bool first = true;
+    for (int64_t q0 = qb; first || q0 < n4; q0 += stride) {
+        const bool live = q0 + t0 < n4;
+        const int64_t q = live ? q0 + t0 : n4 - 1;
+        // ---- round 1 -------------------------------------------------------
+        const int64_t l0 = 4 * (q0 < n4 ? q0 : n4 - 1);
+        const int64_t lend = l0 + 4 * kVecThreads < n ? l0 + 4 * kVecThreads : n;
+        const int64_t e0 = (int64_t)(((uint64_t)l0 * dir.p3_magic) >> dir.p3_shift);
+        const int nel = (int)((int64_t)(((uint64_t)(lend - 1) * dir.p3_magic) >> dir.p3_shift) -
+                              e0) + 1;
+        const int nslots = nel * MS;
+        const int64_t g0 = e0 * MS;
+        auto slot_corner = [&](int k) -> int64_t {
+            const int el = (int)(((uint32_t)k * dir.ms_magic) >> 20);
+            const int c = corner_of_slot_fast(P, k - el * MS);
+            return c < 0 ? -1 : 8 * (e0 + el) + c;
+        };
+        SlotCopies<T> sc[TASKS];
+#pragma unroll
+        for (int u = 0; u < TASKS; ++u) {
+            // threads without a slot load the last one's
+            const int k = t0 + u * kVecThreads < nslots ? t0 + u * kVecThreads : nslots - 1;
+            sc[u].load_list(dir, g0 + k, slot_corner(k));
+        }
+        int64_t e = 0;
+        uint4 pe = make_uint4(0, 0, 0, 0);
+        int4 g4 = make_int4(0, 0, 0, 0);
+        Code4 mv{};
+        if constexpr (STRUCT) {
+            e = struct_elem(sm, 4 * q);
+            pe = reinterpret_cast<const uint4 *>(sm.pos_tab)[(4 * q - e * sm.p3) >> 2];
+        } else {
+            g4 = reinterpret_cast<const int4 *>(gm.gsrc)[q];
+            mv = reinterpret_cast<const Code4 *>(mcode)[q];
+        }
+        Pack4<T> rv = reinterpret_cast<const Pack4<T> *>(r)[q];
+        const Pack4<T> wv = reinterpret_cast<const Pack4<T> *>(w)[q];
+        Pack4<T> mi{}, zv{};
+        if constexpr (PC) mi = reinterpret_cast<const Pack4<T> *>(pc.minv)[q];
+        load_fence();
+        // ---- round 2 -------------------------------------------------------
+#pragma unroll
+        for (int u = 0; u < TASKS; ++u) sc[u].load_values(dir);
+        uint32_t pv[4];
+        ElemRec rc[4];
+        int32_t lk[4];
+        uint8_t cd[4];
+        bool ed[4];
+        T src[4];
+        if constexpr (STRUCT) {
+            pv[0] = pe.x, pv[1] = pe.y, pv[2] = pe.z, pv[3] = pe.w;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) rc[t] = struct_record(sm, e, pv[t]);
+        } else {
+            lk[0] = g4.x, lk[1] = g4.y, lk[2] = g4.z, lk[3] = g4.w;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                cd[t] = mv.v[t];
+                ed[t] = is_group_code(cd[t]);
+                src[t] = w[ed[t] ? (int32_t)(4 * q + t) : lk[t]];
+            }
+        }
+        load_fence();
+        if (first) {
+            // <p, w, c>: the sum of sum_partials_all, its loads behind (2)'s
+            constexpr int kBatch = 8;
+            double v = 0.0;
+            for (int k0 = 0; k0 < dir.n_ax; k0 += kBatch * kVecThreads) {
+                double x[kBatch];
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    const int k = k0 + u * kVecThreads + t0;
+                    x[u] = dir.part_ax[k < dir.n_ax ? k : dir.n_ax - 1];
+                }
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u)
+                    v += k0 + u * kVecThreads + t0 < dir.n_ax ? x[u] : 0.0;
+            }
+            v = wave_sum_f64(v);
+            if ((t0 & 63) == 0) red_pw[t0 >> 6] = v;
+        }
+        // ---- the gathered values of the table-free form, the group sums ------
+        if constexpr (STRUCT) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const StructSrc ss = struct_source(sm, n, 4 * q + t, pv[t], rc[t]);
+                cd[t] = ss.code;
+                ed[t] = ss.edge;
+                src[t] = w[ss.edge ? (int32_t)(4 * q + t) : ss.idx];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < TASKS; ++u) {
+            const T v = sc[u].sum(dir);
+            if (t0 + u * kVecThreads < nslots) es[t0 + u * kVecThreads] = v;
+        }
+        for (int k = t0 + TASKS * kVecThreads; k < nslots; k += kVecThreads) {
+            SlotCopies<T> c;
+            c.load_list(dir, g0 + k, slot_corner(k));
+            c.load_values(dir);
+            es[k] = c.sum(dir);
+        }
+        lds_barrier();
+        if (first) {
+            first = false;
+            // alpha_i = rho_{i-1} / <p, w, c>; block 0 writes the state
+            double pw = 0.0;
+            for (int u = 0; u < kVecThreads / 64; ++u) pw += red_pw[u];
+            const bool ok = alpha_step(h, pw);
+            a = (T)h.alpha;
+            if (vb == 0 && t0 == 0) store_alpha_step(st, h, stopped, hist_alpha, hist_len);
+            if (!ok) return;                                  // uniform
+        }
+        // ---- r, and its weighted square --------------------------------------
+        const T *ese = es;
+        if constexpr (STRUCT) ese = es + (int)(e * MS - g0) - 6;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            // every lane reads LDS: other lanes at the first slot
+            T wg;
+            if constexpr (STRUCT) {
+                const T ev = *(ed[t] ? ese + (pv[t] >> 12) : es);
+                wg = struct_sum<T>(wv.v[t], cd[t], ed[t], ed[t] ? ev : src[t]);
+            } else {
+                const T ev = es[ed[t] ? (int)(lk[t] - g0) : 0];
+                wg = copies_sum<T>(wv.v[t], cd[t], ed[t] ? ev : src[t]);
+            }
+            rv.v[t] -= a * wg;
+            const double rd = (double)rv.v[t];
+            if constexpr (PC) {
+                zv.v[t] = mi.v[t] * rv.v[t];
+                acc += live ? rd * (double)zv.v[t] * cw[cd[t]] : 0.0;
+                acc2 += live ? rd * rd * cw[cd[t]] : 0.0;
+            } else {
+                acc += live ? rd * rd * cw[cd[t]] : 0.0;
+            }
+        }
+        if (live) {
+            reinterpret_cast<Pack4<T> *>(r)[q] = rv;
+            if constexpr (PC) reinterpret_cast<Pack4<T> *>(pc.z)[q] = zv;
+        }
+        if (q0 + stride < n4) lds_barrier();                   // the next step rewrites es
+    }
+    // the last n mod 4 points (even orders)
+    if constexpr (!STRUCT) {
+        for (int64_t l = 4 * n4 + qb + t0; l < n; l += stride) {
+            const uint8_t c = mcode[l];
+            const int32_t lk = gm.gsrc[l];
+            T src;
+            if (is_group_code(c)) {
+                const int cn = corner_of_slot(dir.N, lk % MS);
+                SlotCopies<T> sl;
+                sl.load_list(dir, lk, cn < 0 ? -1 : 8 * (int64_t)(lk / MS) + cn);
+                sl.load_values(dir);
+                src = sl.sum(dir);
+            } else {
+                src = w[lk];
+            }
+            const T rn = r[l] - a * copies_sum<T>(w[l], c, src);
+            r[l] = rn;
+            if constexpr (PC) {
+                const T zn = pc.minv[l] * rn;
+                pc.z[l] = zn;
+                acc += (double)rn * (double)zn * cw[c];
+                acc2 += (double)rn * (double)rn * cw[c];
+            } else {
+                acc += (double)rn * (double)rn * cw[c];
+            }
+        }
+    }
+    const double s = block_sum_f64(acc, red);
+    if (t0 == 0) partial[vb] = s;
+    if constexpr (PC) {
+        const double s2 = block_sum_f64(acc2, red);
+        if (t0 == 0) pc.partial2[vb] = s2;
+    }
+}
+
+// Closes a run of two-launch iterations: one block applies the rho step the
+// next operator launch would (same sums in the same order).
+__device__ __forceinline__ void close_rho_body(CgState *st, const double *partial,
+                                               const double *partial2, int cnt, int nthr) {
+    __shared__ double red[16];
+    if (st->stop || !st->rho_pending) return;    // uniform
+    const double rho = sum_partials_all(partial, cnt, nthr, red);
+    const double rr = partial2 ? sum_partials_all(partial2, cnt, nthr, red) : rho;
+    if (threadIdx.x == 0) {
+        CgStep h = load_step(st);
+        rho_step(h, rho, rr, st->thresh, st->max_iter, st->fixed);
+        if (st->hist_rho && h.iter < st->hist_len) st->hist_rho[h.iter] = rr;
+        store_step(st, h);
+    }
+}
+
 // rho_i = sum of the update partials; beta_i = rho_i / rho_{i-1}; the
 // iteration count, the history and the stopping test (Algorithm 1, last
 // two steps).  One block.
