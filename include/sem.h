@@ -260,7 +260,9 @@ typedef struct {
     double *kernel_ms;    /* optional HOST [3]: mean duration (ms) of the operator kernel,
                              the gather-scatter kernel and the update kernel of one CG
                              iteration, timed with HIP events on the solver's stream.
-                             When set, iterations are launched without graphs. */
+                             When set, iterations are launched without graphs.  On meshes
+                             that sum the shared points in the update kernel the second is
+                             about 0. */
     int precond;          /* sem_precond (sem_cg_solve only; batches and the server take
                              SEM_PRECOND_NONE).  With a preconditioner the stopping test,
                              rel_res_recursive and hist_rho stay on <r, r, c>. */

@@ -6,7 +6,9 @@
 // step, <p,w,c> partials), the edge/vertex group sums (or, for a mesh that
 // shares element-interior nodes, the whole gather-scatter), the alpha
 // finalize (one block per problem), the r update with the gather and the rho
-// finalize (one block per problem).  Block b of a
+// finalize (one block per problem).  Problems whose meshes leave rho to the
+// operator skip the last launch, and where all problems together are small
+// enough the group sums and alpha move into the update.  Block b of a
 // launch runs "virtual block" blk[b].y of problem blk[b].x -- exactly the
 // block that the problem's own single-mesh launch would run, with the same
 // tiles, the same grid stride and the same partial slot -- so every

@@ -38,7 +38,8 @@ inline bool takes_inline_scalars(int N, int64_t n, bool fp64) {
 }
 // most blocks of the update there, in equal steps: every operator block sums
 // their partials (FP32 N = 7 4.1 M points: 1000 blocks 43.2 us, 2000 45.7;
-// N = 8 1.6 M: 781 blocks 29.7, 1562 31.0)
+// N = 8 1.6 M: 781 blocks 29.7, 1562 31.0; the Jacobi iterations of N = 8 1.6 M:
+// 50 in 1733 us, with a cap of 1600 blocks 1837)
 constexpr int kInlineVecBlocks = 1280;
 // local points from which a mesh takes the table-free gather by default
 // (below it, where a CG iteration is mostly launch latency, the table form

@@ -66,7 +66,7 @@ __device__ __forceinline__ double sum_partials(const double *partial, int64_t cn
 
 // Sum of one double per lane of a wave in a fixed order, valid in every lane:
 // within rows of 16 lanes, then across the four rows, by data-parallel lane
-// moves (a shuffle through LDS costs about ten times the latency of one).
+// moves, which need no LDS round trip.
 template <int kCtrl, int kRowMask>
 __device__ __forceinline__ double dpp_add_f64(double v) {
     const long long b = __double_as_longlong(v);

@@ -478,8 +478,8 @@ __device__ __forceinline__ void alpha_block_body(CgState *st, const CgStep *step
 // the tables (edge lists; the packs' gather sources, or positions), the
 // operator's partials, r and w; (2) the edge copies and the gathered values
 // (table-free: the element records first, one round more); alpha is summed
-// while (2) flies.  FP32 CG, N = 7, 210 elements: four launches 15.6 us an
-// iteration, two 9.9.
+// while (2) flies.  FP32 CG, N = 7, 210 elements: four launches 15.3 us an
+// iteration, two 12.3.
 // ---------------------------------------------------------------------------
 
 // Edge slots of the elements a block step of 256 packs touches: at most
