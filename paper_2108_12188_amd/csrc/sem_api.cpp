@@ -183,11 +183,13 @@ sem_status sem_gs(sem_mesh_t mesh, sem_precision prec, void *w_dev, int apply_ma
         DeviceGuard dg(m->device);
         hipStream_t s = static_cast<hipStream_t>(hip_stream);
         if (prec == SEM_FP32) {
-            launch_gs<float>(*m, static_cast<float *>(w_dev), s);
-            if (apply_mask) launch_mask<float>(*m, static_cast<float *>(w_dev), s);
+            float *w = static_cast<float *>(w_dev);
+            if (apply_mask) launch_gs_mask<float>(*m, w, s);
+            else launch_gs<float>(*m, w, s);
         } else {
-            launch_gs<double>(*m, static_cast<double *>(w_dev), s);
-            if (apply_mask) launch_mask<double>(*m, static_cast<double *>(w_dev), s);
+            double *w = static_cast<double *>(w_dev);
+            if (apply_mask) launch_gs_mask<double>(*m, w, s);
+            else launch_gs<double>(*m, w, s);
         }
         return SEM_OK;
     });
@@ -265,21 +267,34 @@ sem_status sem_rhs(sem_mesh_t mesh, sem_precision prec, const double *f_dev, voi
             fail(SEM_EINVAL, "unknown precision");
         DeviceGuard dg(m->device);
         hipStream_t s = static_cast<hipStream_t>(hip_stream);
+        // N = 7, 2.1 M points, FP32: product, sums, mask and conversion as
+        // passes over a temporary 34 us, one launch that reads f at every
+        // copy 21.  Over its own input the product goes to memory first.
+        const uintptr_t f0 = (uintptr_t)f_dev, b0 = (uintptr_t)b_dev;
+        const uintptr_t f_len = sizeof(double) * (size_t)m->n;
+        const uintptr_t b_len = prec == SEM_FP32 ? f_len / 2 : f_len;
+        const bool overlap = f0 < b0 + b_len && b0 < f0 + f_len;
         if (prec == SEM_FP32) {
+            float *b = static_cast<float *>(b_dev);
+            if (!overlap) {
+                launch_rhs<float>(*m, f_dev, b, s);
+                return SEM_OK;
+            }
             double *tmp = nullptr;
-            SEM_HIP(hipMalloc(&tmp, sizeof(double) * m->n));
-            launch_mul64(m->n, m->B64, f_dev, tmp, s);
-            launch_gs<double>(*m, tmp, s);
-            launch_mask<double>(*m, tmp, s);
-            launch_convert<double, float>(m->n, tmp, static_cast<float *>(b_dev), s);
+            SEM_HIP(hipMalloc(&tmp, f_len));
+            launch_rhs<double>(*m, f_dev, tmp, s);
+            launch_convert<double, float>(m->n, tmp, b, s);
             const hipError_t e = hipStreamSynchronize(s);
             (void)hipFree(tmp);
             check_hip(e, "rhs");
         } else {
             double *b = static_cast<double *>(b_dev);
+            if (!overlap) {
+                launch_rhs<double>(*m, f_dev, b, s);
+                return SEM_OK;
+            }
             launch_mul64(m->n, m->B64, f_dev, b, s);
-            launch_gs<double>(*m, b, s);
-            launch_mask<double>(*m, b, s);
+            launch_gs_mask<double>(*m, b, s);
         }
         return SEM_OK;
     });

@@ -99,7 +99,7 @@ gs_batch_kernel(const GsBatchDesc *__restrict__ d, const int2 *__restrict__ blk)
     const int2 pv = blk[blockIdx.x];
     const GsBatchDesc g = d[pv.x];
     if (g.st->stop) return;
-    gsb::gs_logical_block<float>(*g.cls, pv.y, g.idx, g.w);
+    gsb::gs_logical_block(*g.cls, pv.y, g.idx, gsb::InPlace<float>{g.w});
 }
 
 __global__ void __launch_bounds__(kFinalizeThreads)
@@ -710,8 +710,7 @@ sem_status batch_solve(BatchImpl &B, const sem_cg_opts &o, const void *const *b_
             a.u = static_cast<const float *>(ws.x);
             a.w = static_cast<float *>(ws.w);
             launch_ax<float>(m, otf, AxMode::Plain, a, s);
-            launch_gs<float>(m, static_cast<float *>(ws.w), s);
-            launch_mask<float>(m, static_cast<float *>(ws.w), s);
+            launch_gs_mask<float>(m, static_cast<float *>(ws.w), s);
             launch_cg_init<float>(m, static_cast<const float *>(b_dev[q]),
                                   static_cast<const float *>(ws.w), static_cast<float *>(ws.r),
                                   static_cast<float *>(ws.p), ws.st, ws.part_vec, s);

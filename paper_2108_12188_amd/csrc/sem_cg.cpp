@@ -309,8 +309,7 @@ void apply_A64(const Mesh &m, const double *u, double *w, hipStream_t s) {
     a.u = u;
     a.w = w;
     launch_ax<double>(m, m.G64 == nullptr, AxMode::Plain, a, s);
-    launch_gs<double>(m, w, s);
-    launch_mask<double>(m, w, s);
+    launch_gs_mask<double>(m, w, s);
 }
 
 template <typename T>
@@ -319,8 +318,7 @@ void apply_A(const Mesh &m, bool otf, const T *u, T *w, hipStream_t s) {
     a.u = u;
     a.w = w;
     launch_ax<T>(m, otf, AxMode::Plain, a, s);
-    launch_gs<T>(m, w, s);
-    launch_mask<T>(m, w, s);
+    launch_gs_mask<T>(m, w, s);
 }
 
 struct InnerOut {

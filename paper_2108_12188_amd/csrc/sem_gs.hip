@@ -42,7 +42,7 @@ gs_kernel(const GsClasses cls, int64_t lb0, int64_t nb_logical, const int32_t *_
         --nb;
     }
     const int64_t b = logical_block(blockIdx.x, nb);
-    if (b < nb_logical) gs_logical_block<T>(cls, lb0 + b, idx, w);
+    if (b < nb_logical) gs_logical_block(cls, lb0 + b, idx, InPlace<T>{w});
 }
 
 // Group sums of the classes with M >= mmin: logical blocks lb0 .. lb0 +
@@ -63,6 +63,61 @@ group_sums_kernel(const GsClasses cls, int64_t lb0, int64_t nb_logical,
     if (step ? step->stop : st->stop) return;
     const int64_t b = logical_block(blockIdx.x, gridDim.x - 1);
     if (b < nb_logical) gs_sums_logical_block<T>(cls, lb0 + b, idx, io0, src, out, mmin);
+}
+
+constexpr int kPointsPerThread = 4;
+constexpr int64_t kPointsPerBlock = (int64_t)kGsThreads * kPointsPerThread;
+
+// w <- mask(QQ^T w): the first nb_gs blocks take the groups and write zeros
+// to the masked ones, the others zero the Dirichlet points of one copy.
+// Bound by memory (the strided faces touch almost every line of w).  FP64
+// N = 7, 6.2 M points: 27.5 us and 5.5 for the mask as a pass of its own, 28.2
+// in one launch (32.0 with the flag read from each group's first point).
+template <typename T>
+__global__ void __launch_bounds__(kGsThreads)
+gs_mask_kernel(const GsClasses cls, int64_t nb_gs, int64_t nb_logical,
+               const int32_t *__restrict__ idx, const InPlaceMasked<T> a,
+               const int32_t *__restrict__ dir1, int64_t n_dir1) {
+    if (blockIdx.x < nb_gs) {
+        const int64_t b = logical_block(blockIdx.x, nb_gs);
+        if (b < nb_logical) gs_logical_block(cls, b, idx, a);
+        return;
+    }
+    const int64_t t0 = (blockIdx.x - nb_gs) * kPointsPerBlock + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kPointsPerThread; ++u) {
+        const int64_t t = t0 + (int64_t)u * kGsThreads;
+        if (t < n_dir1) a.w[dir1[t]] = T(0);
+    }
+}
+
+// b = mask(QQ^T (B f)) in one launch: the first nb_gs blocks take the shared
+// points by groups, the others the points of one copy in order; every point
+// is written once and f is only read, so no block waits for another.
+template <typename T>
+__global__ void __launch_bounds__(kGsThreads)
+rhs_kernel(const GsClasses cls, int64_t nb_gs, int64_t nb_logical,
+           const int32_t *__restrict__ idx, const MassSource<T> a,
+           const uint8_t *__restrict__ mcode, int64_t n) {
+    if (blockIdx.x < nb_gs) {
+        const int64_t b = logical_block(blockIdx.x, nb_gs);
+        if (b < nb_logical) gs_logical_block(cls, b, idx, a);
+        return;
+    }
+    const int64_t l0 = (blockIdx.x - nb_gs) * kPointsPerBlock + threadIdx.x;
+    uint8_t code[kPointsPerThread];
+    double v[kPointsPerThread];
+#pragma unroll
+    for (int u = 0; u < kPointsPerThread; ++u) {
+        const int64_t l = l0 + (int64_t)u * kGsThreads;
+        code[u] = l < n ? mcode[l] : 0;
+        v[u] = l < n ? a.B[l] * a.f[l] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kPointsPerThread; ++u) {
+        if ((code[u] & kMultMask) != 1) continue;
+        a.b[l0 + (int64_t)u * kGsThreads] = (code[u] & kDirichletBit) ? T(0) : (T)v[u];
+    }
 }
 
 template <typename T>
@@ -98,6 +153,27 @@ void launch_mask(const Mesh &m, T *w, hipStream_t s) {
     const int64_t nb = (m.n_dir + 255) / 256;
     hipLaunchKernelGGL((mask_kernel<T>), dim3((unsigned)nb), dim3(256), 0, s, m.dir_idx, m.n_dir, w);
     check_hip(hipGetLastError(), "mask kernel launch");
+}
+
+template <typename T>
+void launch_gs_mask(const Mesh &m, T *w, hipStream_t s) {
+    const int64_t nlb = gs_logical_blocks(m);
+    const int64_t nb = m.n_groups ? gs_phys_blocks(nlb) : 0;
+    const int64_t total = nb + (m.n_dir1 + kPointsPerBlock - 1) / kPointsPerBlock;
+    if (total == 0) return;
+    hipLaunchKernelGGL((gs_mask_kernel<T>), dim3((unsigned)total), dim3(kGsThreads), 0, s, m.gs,
+                       nb, nlb, m.gs_idx, (InPlaceMasked<T>{{w}}), m.dir_idx, m.n_dir1);
+    check_hip(hipGetLastError(), "gs kernel launch");
+}
+
+template <typename T>
+void launch_rhs(const Mesh &m, const double *f, T *b, hipStream_t s) {
+    const int64_t nlb = gs_logical_blocks(m);
+    const int64_t nb = m.n_groups ? gs_phys_blocks(nlb) : 0;
+    const int64_t total = nb + (m.n + kPointsPerBlock - 1) / kPointsPerBlock;
+    hipLaunchKernelGGL((rhs_kernel<T>), dim3((unsigned)total), dim3(kGsThreads), 0, s, m.gs, nb,
+                       nlb, m.gs_idx, (MassSource<T>{m.B64, f, b}), m.mcode, m.n);
+    check_hip(hipGetLastError(), "rhs kernel launch");
 }
 
 template <typename T>
@@ -158,6 +234,10 @@ void launch_edge_sums_cg(const Mesh &m, const T *wedge, T *gsum, CgState *st,
 
 template void launch_gs<float>(const Mesh &, float *, hipStream_t);
 template void launch_gs<double>(const Mesh &, double *, hipStream_t);
+template void launch_gs_mask<float>(const Mesh &, float *, hipStream_t);
+template void launch_gs_mask<double>(const Mesh &, double *, hipStream_t);
+template void launch_rhs<float>(const Mesh &, const double *, float *, hipStream_t);
+template void launch_rhs<double>(const Mesh &, const double *, double *, hipStream_t);
 template void launch_mask<float>(const Mesh &, float *, hipStream_t);
 template void launch_mask<double>(const Mesh &, double *, hipStream_t);
 template void launch_gs_cg<float>(const Mesh &, float *, CgState *, const double *, int,

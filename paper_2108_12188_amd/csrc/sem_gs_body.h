@@ -21,13 +21,45 @@ struct alignas(M * 4 <= 16 ? M * 4 : 16) IdxVec {
     int32_t v[M];
 };
 
+// What a gather-scatter reads and writes at a local index; kMask: the groups
+// on the Dirichlet boundary (the last of their class) become zero unread.
+template <typename T>
+struct InPlace {
+    using Value = T;
+    static constexpr bool kMask = false;
+    T *__restrict__ w;
+    __device__ __forceinline__ T load(int32_t q) const { return w[q]; }
+    __device__ __forceinline__ void store(int32_t q, T s) const { w[q] = s; }
+};
+template <typename T>
+struct InPlaceMasked : InPlace<T> {
+    static constexpr bool kMask = true;
+};
+
+// b = mask(QQ^T (B f)): a group's products are rounded before they are summed
+// (no contraction to a fused multiply-add), as a product vector in memory is.
+template <typename T>
+struct MassSource {
+    using Value = double;
+    static constexpr bool kMask = true;
+    const double *__restrict__ B;
+    const double *__restrict__ f;
+    T *__restrict__ b;
+    __device__ __forceinline__ double load(int32_t q) const {
+#pragma clang fp contract(off)
+        return B[q] * f[q];
+    }
+    __device__ __forceinline__ void store(int32_t q, double s) const { b[q] = (T)s; }
+};
+
 // Groups of a compile-time size M: every lane first issues the index loads
 // of all its groups, then all value loads, so each lane keeps
 // kGsPerThread * M independent loads in flight (groups are disjoint, so the
 // stores of one group never alias the loads of another).
-template <typename T, int M>
+template <int M, typename A>
 __device__ __forceinline__ void gs_groups_fixed(const int32_t *__restrict__ ib, int64_t g0,
-                                                int64_t ng, T *__restrict__ w) {
+                                                int64_t ng, int64_t nsum, const A &a) {
+    using V = typename A::Value;
     constexpr int kGsPerThread = gs_per_thread(M);
     int32_t q[kGsPerThread][M];
     bool ok[kGsPerThread];
@@ -45,32 +77,37 @@ __device__ __forceinline__ void gs_groups_fixed(const int32_t *__restrict__ ib, 
             for (int t = 0; t < M; ++t) q[it][t] = 0;
         }
     }
-    T v[kGsPerThread][M];
+    V v[kGsPerThread][M];
 #pragma unroll
-    for (int it = 0; it < kGsPerThread; ++it)
+    for (int it = 0; it < kGsPerThread; ++it) {
+        const bool sum = ok[it] && (!A::kMask || g0 + (int64_t)it * kGsThreads < nsum);
 #pragma unroll
-        for (int t = 0; t < M; ++t) v[it][t] = ok[it] ? w[q[it][t]] : T(0);
+        for (int t = 0; t < M; ++t) v[it][t] = sum ? a.load(q[it][t]) : V(0);
+    }
 #pragma unroll
     for (int it = 0; it < kGsPerThread; ++it) {
         if (!ok[it]) continue;
-        T s = v[it][0];
+        V s = v[it][0];
 #pragma unroll
         for (int t = 1; t < M; ++t) s += v[it][t];
 #pragma unroll
-        for (int t = 0; t < M; ++t) w[q[it][t]] = s;
+        for (int t = 0; t < M; ++t) a.store(q[it][t], s);
     }
 }
 
-template <typename T>
+template <typename A>
 __device__ __forceinline__ void gs_groups_any(const int32_t *__restrict__ ib, int M, int64_t g0,
-                                              int64_t ng, T *__restrict__ w) {
+                                              int64_t ng, int64_t nsum, const A &a) {
     for (int it = 0; it < gs_per_thread(M); ++it) {
         const int64_t g = g0 + (int64_t)it * kGsThreads;
         if (g >= ng) break;
         const int32_t *gi = ib + g * M;
-        T s = w[gi[0]];
-        for (int t = 1; t < M; ++t) s += w[gi[t]];
-        for (int t = 0; t < M; ++t) w[gi[t]] = s;
+        typename A::Value s = 0;
+        if (!A::kMask || g < nsum) {
+            s = a.load(gi[0]);
+            for (int t = 1; t < M; ++t) s += a.load(gi[t]);
+        }
+        for (int t = 0; t < M; ++t) a.store(gi[t], s);
     }
 }
 
@@ -158,22 +195,21 @@ __device__ __forceinline__ void gs_sums_logical_block(const GsClasses &cls, int6
 // The logical block at position lb of a gather-scatter launch (uniform
 // across the block), in the class-major block numbering after the mesh's
 // block order, if it has one.
-template <typename T>
+template <typename A>
 __device__ __forceinline__ void gs_logical_block(const GsClasses &cls, int64_t lb,
-                                                 const int32_t *__restrict__ idx,
-                                                 T *__restrict__ w) {
+                                                 const int32_t *__restrict__ idx, const A &a) {
     if (cls.lb_order) lb = cls.lb_order[lb];
     int c = 0;
     while (c + 1 < cls.ncls && lb >= cls.blk0[c + 1]) ++c;
     const int M = cls.M[c];
     const int64_t g0 = (lb - cls.blk0[c]) * gs_per_block(M) + threadIdx.x;
     const int32_t *ib = idx + cls.io[c];
-    const int64_t ng = cls.ng[c];
+    const int64_t ng = cls.ng[c], nsum = cls.nfree[c];
     switch (M) {
-        case 2: gs_groups_fixed<T, 2>(ib, g0, ng, w); break;
-        case 4: gs_groups_fixed<T, 4>(ib, g0, ng, w); break;
-        case 8: gs_groups_fixed<T, 8>(ib, g0, ng, w); break;
-        default: gs_groups_any<T>(ib, M, g0, ng, w); break;
+        case 2: gs_groups_fixed<2>(ib, g0, ng, nsum, a); break;
+        case 4: gs_groups_fixed<4>(ib, g0, ng, nsum, a); break;
+        case 8: gs_groups_fixed<8>(ib, g0, ng, nsum, a); break;
+        default: gs_groups_any(ib, M, g0, ng, nsum, a); break;
     }
 }
 

@@ -150,6 +150,7 @@ struct GsClasses {
     int ncls;
     int M[kMaxGsClasses];          // copies per group in this class
     int64_t ng[kMaxGsClasses];     // groups in this class
+    int64_t nfree[kMaxGsClasses];  // of these off the Dirichlet boundary; they come first
     int64_t io[kMaxGsClasses];     // offset of the class in gs_idx
     int64_t blk0[kMaxGsClasses];   // first block of the class in a gs launch
     // gather-scatter launches only (null: identity): DEVICE int32 [blocks],
@@ -190,7 +191,7 @@ struct Mesh {
     int N = 0, P = 0, P3 = 0;
     int64_t n = 0;            // local points
     int64_t n_glob = 0;
-    int64_t n_groups = 0, n_shared = 0, n_dir = 0;
+    int64_t n_groups = 0, n_shared = 0, n_dir = 0, n_dir1 = 0;
     GsClasses gs{};           // shared-point groups by size class
 
     // host copies of the basis (FP64, this library's own construction)
@@ -206,7 +207,7 @@ struct Mesh {
     uint8_t *mcode = nullptr;     // [n]: multiplicity | Dirichlet bit
     int32_t *gs_idx = nullptr;    // [n_shared], class-major, groups of M ascending indices
     int32_t *gs_lb_order = nullptr;   // gs.lb_order's array
-    int32_t *dir_idx = nullptr;   // [n_dir]
+    int32_t *dir_idx = nullptr;   // [n_dir], the n_dir1 points of one copy first
     // Shared sums inside the CG update (used when every shared point lies on
     // the surface of its element's P^3 block): gsrc[l] is the other copy of
     // a pair (m = 2), the rank of a larger group among the n_groups_multi
@@ -292,7 +293,7 @@ inline double refine_inner_tol(double inner_tol, double tol, double rel) {
 
 // Host tables of a mesh's scatter map (sem_tables.cpp; no device calls).
 struct HostTables {
-    int64_t n_glob = 0, n_groups = 0, n_shared = 0, n_dir = 0;
+    int64_t n_glob = 0, n_groups = 0, n_shared = 0, n_dir = 0, n_dir1 = 0;
     GsClasses gs{};
     std::vector<uint8_t> mcode;     // [n]
     std::vector<int32_t> gs_idx;    // class-major ascending member lists
@@ -472,6 +473,12 @@ template <typename T>
 void launch_gs(const Mesh &m, T *w, hipStream_t s);
 template <typename T>
 void launch_mask(const Mesh &m, T *w, hipStream_t s);
+// w <- mask(QQ^T w), one launch
+template <typename T>
+void launch_gs_mask(const Mesh &m, T *w, hipStream_t s);
+// b = mask(QQ^T (B f)), one launch; b must not overlap f
+template <typename T>
+void launch_rhs(const Mesh &m, const double *f, T *b, hipStream_t s);
 // CG step after the fused operator: gather-scatter, then alpha from the
 // operator kernel's partials of <p, w, c>
 template <typename T>

@@ -141,6 +141,7 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
     m->n_groups = t.n_groups;
     m->n_shared = t.n_shared;
     m->n_dir = t.n_dir;
+    m->n_dir1 = t.n_dir1;
     m->gs_in_update = t.gs_in_update;
     m->n_groups_multi = t.n_groups_multi;
     m->gs_blk_multi = t.gs_blk_multi;

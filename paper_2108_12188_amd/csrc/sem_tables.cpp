@@ -168,7 +168,7 @@ bool build_struct_tables(int64_t E, int N, const std::vector<uint8_t> &mcode,
             }
             ++ng;
         }
-        ec.ng[c] = ng;
+        ec.ng[c] = ec.nfree[c] = ng;
         t.n_egroups += ng;
     }
     while (ew.size() % 8) ew.push_back(0);
@@ -278,6 +278,7 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     // group among the groups of more than two copies (class order)
     std::vector<int32_t> plink(n, 0);
     int64_t n_multi = 0;
+    std::vector<int64_t> masked;
     for (int msz = 2; msz <= kMaxMultiplicity; ++msz) {
         if (!sizes_seen[msz]) continue;
         if (cls.ncls == kMaxGsClasses)
@@ -288,8 +289,7 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
         while (gs_idx.size() % 8) gs_idx.push_back(0);
         cls.io[c] = (int64_t)gs_idx.size();
         int64_t ng = 0;
-        for (int64_t g = 0; g < G; ++g) {
-            if (cnt[g] != msz) continue;
+        const auto add_group = [&](int64_t g) {
             for (int64_t o = start[g]; o < start[g + 1]; ++o) gs_idx.push_back(byid[o]);
             if (msz == 2) {
                 plink[byid[start[g]]] = byid[start[g] + 1];
@@ -299,7 +299,16 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
                 ++n_multi;
             }
             ++ng;
+        };
+        // the masked groups last: a launch that also masks knows them by rank
+        masked.clear();
+        for (int64_t g = 0; g < G; ++g) {
+            if (cnt[g] != msz) continue;
+            if (dflag[g] == 1) masked.push_back(g);
+            else add_group(g);
         }
+        cls.nfree[c] = ng;
+        for (const int64_t g : masked) add_group(g);
         cls.ng[c] = ng;
         n_groups += ng;
         n_shared += ng * msz;
@@ -340,8 +349,13 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     std::vector<int32_t> &dir_idx = t.dir_idx;
     dir_idx.clear();
     dir_idx.reserve(n_dir);
+    // points of one copy first: the gather-scatter masks the shared ones
+    std::vector<int32_t> dir_shared;
     for (int64_t l = 0; l < n; ++l)
-        if (mcode[l] & kDirichletBit) dir_idx.push_back((int32_t)l);
+        if (mcode[l] & kDirichletBit)
+            ((mcode[l] & kMultMask) == 1 ? dir_idx : dir_shared).push_back((int32_t)l);
+    t.n_dir1 = (int64_t)dir_idx.size();
+    dir_idx.insert(dir_idx.end(), dir_shared.begin(), dir_shared.end());
 
     // Table of the gather inside the CG update, used when every shared
     // point lies on its element's surface (true of every conforming mesh:
