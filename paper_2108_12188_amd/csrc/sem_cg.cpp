@@ -297,11 +297,21 @@ void run_chunk(const Mesh &m, Workspace &ws, bool otf, bool pc, int chunk, bool 
     SEM_HIP(hipGraphLaunch(it->second, s));
 }
 
+// A fixed count runs in equal chunks of at most 50: the launches of iterations
+// past it cost 1.5 to 2 us each although they do nothing (64 iterations as two
+// chunks of 50 ran 36 of them).
 int auto_chunk(int64_t n, int fixed) {
-    int c = n < (1 << 20) ? 32 : (n < (1 << 23) ? 16 : 8);
-    if (fixed > 0) c = std::min(std::max(fixed, 1), 50);
-    return c;
+    if (fixed > 0) {
+        const int chunks = (fixed - 1) / 50 + 1;
+        return (fixed - 1) / chunks + 1;
+    }
+    return n < (1 << 20) ? 32 : (n < (1 << 23) ? 16 : 8);
 }
+
+// Chunks of a fixed-count solve between two reads of the state: the host has
+// nothing to decide in them (each read leaves the GPU idle for about 10 us),
+// but a solve that breaks down should not run on for long.
+constexpr int kFixedChunksPerPoll = 2;
 
 // FP64 operator w = mask(QQ^T A_L u): precomputed G64 if present, else on the fly
 void apply_A64(const Mesh &m, const double *u, double *w, hipStream_t s) {
@@ -330,10 +340,11 @@ struct InnerOut {
 // Runs Algorithm 1 on ws (x, r, p, w) for right-hand side b_dev (device, T).
 // x0_zero: the initial guess is zero (r0 = b, no operator application).
 // pc: Jacobi-preconditioned (ensure_jacobi has run for m and ws).
+// The caller has seen to it that no copy from or to ws.h_st is in flight.
 template <typename T>
 InnerOut cg_core(const Mesh &m, Workspace &ws, const T *b_dev, bool x0_zero, bool otf, bool pc,
-                 double tol, int max_iter, int fixed, int chunk, bool use_graph, int hist_len,
-                 KernelTimes *kt = nullptr) {
+                 double tol, int max_iter, int fixed, int chunk, int per_poll, bool use_graph,
+                 int hist_len, KernelTimes *kt = nullptr) {
     hipStream_t s = ws.stream;
     CgState h{};
     h.thresh = tol * tol;
@@ -345,7 +356,6 @@ InnerOut cg_core(const Mesh &m, Workspace &ws, const T *b_dev, bool x0_zero, boo
         h.hist_rho = ws.hist;
         h.hist_alpha = ws.hist + ws.hist_cap;
     }
-    SEM_HIP(hipStreamSynchronize(s));   // h_st may still be the target of a copy
     *ws.h_st = h;
     SEM_HIP(hipMemcpyAsync(ws.st, ws.h_st, sizeof(CgState), hipMemcpyHostToDevice, s));
     T *x = static_cast<T *>(ws.x), *r = static_cast<T *>(ws.r);
@@ -363,6 +373,12 @@ InnerOut cg_core(const Mesh &m, Workspace &ws, const T *b_dev, bool x0_zero, boo
     // stops; a chunk that does not advance it means the device state is
     // inconsistent, which ends the loop with an error instead of spinning
     int last_iter = -1;
+    // a fixed count needs no read of the state before its first chunks
+    if (h.fixed && !kt) {
+        const int chunks = (fixed - 1) / chunk + 1;
+        for (int k = 0; k < std::min(chunks, per_poll); ++k)
+            run_chunk<T>(m, ws, otf, pc, chunk, use_graph);
+    }
     for (;;) {
         SEM_HIP(hipMemcpyAsync(ws.h_st, ws.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
         SEM_HIP(hipStreamSynchronize(s));
@@ -371,8 +387,13 @@ InnerOut cg_core(const Mesh &m, Workspace &ws, const T *b_dev, bool x0_zero, boo
             fail(SEM_EDEVICE, "CG state did not advance (iteration " +
                                   std::to_string(ws.h_st->iter) + ")");
         last_iter = ws.h_st->iter;
-        if (kt) run_chunk_timed<T>(m, ws, otf, pc, chunk, last_iter, *kt);
-        else run_chunk<T>(m, ws, otf, pc, chunk, use_graph);
+        if (kt) {
+            run_chunk_timed<T>(m, ws, otf, pc, chunk, last_iter, *kt);
+            continue;
+        }
+        const int left = h.fixed ? (fixed - last_iter - 1) / chunk + 1 : 1;
+        for (int k = 0; k < std::min(left, per_poll); ++k)
+            run_chunk<T>(m, ws, otf, pc, chunk, use_graph);
     }
     // the last completed iteration's x step
     launch_x_flush<T>(m, x, p, ws.st, s);
@@ -433,6 +454,9 @@ static sem_status cg_plain(Mesh &m, const sem_cg_opts &o, const void *b_user, vo
     Workspace &ws = get_ws(m, fp64);
     const bool pc = o.precond == SEM_PRECOND_JACOBI;
     if (pc) ensure_jacobi(m, ws);
+    // before the stream has work: h_st may still be a copy's source or target
+    // if the last solve ended in an error
+    SEM_HIP(hipStreamSynchronize(ws.stream));
     SEM_HIP(hipEventRecord(ws.ev, user_s));
     SEM_HIP(hipStreamWaitEvent(ws.stream, ws.ev, 0));
     const T *b = static_cast<const T *>(b_user);
@@ -440,8 +464,9 @@ static sem_status cg_plain(Mesh &m, const sem_cg_opts &o, const void *b_user, vo
     const int chunk = o.poll_every > 0 ? o.poll_every : auto_chunk(m.n, o.fixed_iters);
     const int hist_len = (o.hist_rho || o.hist_alpha) ? o.hist_len : 0;
     KernelTimes kt;
+    const int per_poll = o.poll_every > 0 ? 1 : kFixedChunksPerPoll;
     InnerOut io = cg_core<T>(m, ws, b, false, otf, pc, o.tol, o.max_iter, o.fixed_iters, chunk,
-                             o.use_graph != 0, hist_len, o.kernel_ms ? &kt : nullptr);
+                             per_poll, o.use_graph != 0, hist_len, o.kernel_ms ? &kt : nullptr);
     if (o.kernel_ms)
         for (int k = 0; k < 3; ++k) o.kernel_ms[k] = kt.count ? kt.ms[k] / kt.count : 0.0;
     SEM_HIP(hipMemcpyAsync(x_user, ws.x, sizeof(T) * m.n, hipMemcpyDeviceToDevice, ws.stream));
@@ -476,6 +501,7 @@ static sem_status cg_mixed(Mesh &m, const sem_cg_opts &o, const double *b, doubl
     Workspace &w32 = get_ws(m, false);
     const bool pc = o.precond == SEM_PRECOND_JACOBI;
     if (pc) ensure_jacobi(m, w32);
+    SEM_HIP(hipStreamSynchronize(w32.stream));   // as in cg_plain
     SEM_HIP(hipEventRecord(w64.ev, user_s));
     SEM_HIP(hipStreamWaitEvent(w64.stream, w64.ev, 0));
     hipStream_t s = w64.stream;
@@ -514,7 +540,7 @@ static sem_status cg_mixed(Mesh &m, const sem_cg_opts &o, const double *b, doubl
         SEM_HIP(hipEventRecord(w64.ev, s));
         SEM_HIP(hipStreamWaitEvent(w32.stream, w64.ev, 0));
         InnerOut io = cg_core<float>(m, w32, b32, true, otf, pc,
-                                     refine_inner_tol(inner_tol, o.tol, rel), inner_cap, 0, chunk,
+                                     refine_inner_tol(inner_tol, o.tol, rel), inner_cap, 0, chunk, 1,
                                      o.use_graph != 0, 0, o.kernel_ms ? &kt : nullptr);
         total += io.iters;
         last_stop = io.stop;
