@@ -1272,7 +1272,16 @@ __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const Bas
 
 // Matrix-core kernels: N = 7 on single-wave blocks, N = 9 on two-wave blocks.
 constexpr int kMfmaThreads = kP == 10 ? 128 : 64;
-constexpr int kMfmaWaves = kP == 10 ? 3 : 4;
+// Waves per SIMD.  The fused N = 9 kernel is held to 3 by its LDS.  The plain
+// forms on the fly are bound by VALU issue, most of it the geometry (N = 9 with
+// 3 waves: the VALU busy 67% of the time, the matrix cores 26%), which one wave
+// more fills better: 8 M points, N = 9 41.5 us with 3 waves, 39.0 with 4 (with
+// 5, which spill, 75), N = 7 29.7 with 4, 28.0 with 5 (with 6 32.4).
+template <bool FUSED>
+constexpr int mfma_waves() {
+    if (FUSED) return kP == 10 ? 3 : 4;
+    return kP == 10 ? 4 : 5;
+}
 
 template <bool OTF, bool FUSED, bool NT, bool RHO>
 __device__ __forceinline__ void ax_mfma_any(const AxArgs<float> &a, const BasisK<float> &bk,
@@ -1284,13 +1293,13 @@ __device__ __forceinline__ void ax_mfma_any(const AxArgs<float> &a, const BasisK
 // NT: the CG-fused form with p and x non-temporal (AxArgs::stream); RHO: the
 // CG-fused form that forms rho first (AxArgs::st_out)
 template <bool OTF, bool FUSED, bool NT = false, bool RHO = false>
-__global__ void __launch_bounds__(kMfmaThreads, kMfmaWaves)
+__global__ void __launch_bounds__(kMfmaThreads, (mfma_waves<FUSED>()))
 ax_mfma_kernel(const AxArgs<float> a, const BasisK<float> bk, int64_t ntiles) {
     ax_mfma_any<OTF, FUSED, NT, RHO>(a, bk, ntiles, blockIdx.x, gridDim.x);
 }
 
 template <bool OTF, bool NT = false, bool RHO = false>
-__global__ void __launch_bounds__(kMfmaThreads, kMfmaWaves)
+__global__ void __launch_bounds__(kMfmaThreads, (mfma_waves<true>()))
 ax_mfma_batch_kernel(const AxArgs<float> *__restrict__ descs, const int2 *__restrict__ blk,
                      const BasisK<float> bk) {
     const int2 pv = blk[blockIdx.x];
