@@ -70,6 +70,7 @@ struct UpdGBatchDesc {
     CgState *st;
     double *partial;
     int64_t vgrid;
+    int packs;                  // per block step (step_packs; 256 without two-launch tables)
     DirectArgs<float> dir;      // st_in null: the four-launch form
 };
 
@@ -82,6 +83,7 @@ struct UpdSBatchDesc {
     CgState *st;
     double *partial;
     int64_t vgrid;
+    int packs;                  // per block step (step_packs; 256 without two-launch tables)
     DirectArgs<float> dir;      // st_in null: the four-launch form
 };
 
@@ -139,7 +141,7 @@ update_gather_batch_kernel(const UpdGBatchDesc *__restrict__ d, const int2 *__re
                                                       u.vgrid, PcArgs<float>{}, u.dir);
     else
         vecb::update_gather_body<float>(u.n, u.r, u.w, u.gsum, u.mcode, u.gm, u.st, u.partial,
-                                        pv.y, u.vgrid);
+                                        pv.y, u.vgrid, PcArgs<float>{}, u.packs);
 }
 
 template <bool DIRECT>
@@ -152,7 +154,8 @@ update_struct_batch_kernel(const UpdSBatchDesc *__restrict__ d, const int2 *__re
                                                      u.sm, u.st, u.partial, pv.y, u.vgrid,
                                                      PcArgs<float>{}, u.dir);
     else
-        vecb::update_struct_body<float>(u.n, u.r, u.wg, u.sm, u.st, u.partial, pv.y, u.vgrid);
+        vecb::update_struct_body<float>(u.n, u.r, u.wg, u.sm, u.st, u.partial, pv.y, u.vgrid,
+                                        PcArgs<float>{}, u.packs);
 }
 
 __global__ void __launch_bounds__(kFinalizeThreads)
@@ -477,6 +480,7 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
         const int64_t nlb = m.n_groups > 0 ? gs_logical_blocks(m) : 0;
         const int nv = update_blocks(m, false);
         const bool direct = two && m.direct;
+        const int packs = m.direct ? step_packs(m.N) : vecb::kVecThreads;
         // the single-mesh schedule of each problem: the same logical and
         // virtual blocks
         const bool compact = m.gsum_wedge;
@@ -502,7 +506,7 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
                                      m.p3_shift};
             for (int f = 0; f < 2; ++f)
                 upds[f].push_back({m.n, static_cast<float *>(ws.r), wg, sm, ws.st, ws.part_vec,
-                                   nv, dir[f]});
+                                   nv, packs, dir[f]});
             for (int vb = 0; vb < nv; ++vb)
                 (direct ? upds_direct : upds_blk)
                     .push_back(make_int2((int)upds[0].size() - 1, vb));
@@ -524,7 +528,7 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
                 updg[f].push_back({m.n, static_cast<float *>(ws.r),
                                    static_cast<const float *>(ws.w),
                                    static_cast<const float *>(ws.gsum), m.mcode, gm, ws.st,
-                                   ws.part_vec, nv, dir[f]});
+                                   ws.part_vec, nv, packs, dir[f]});
             for (int vb = 0; vb < nv; ++vb)
                 (direct ? updg_direct : updg_blk)
                     .push_back(make_int2((int)updg[0].size() - 1, vb));

@@ -88,7 +88,7 @@ Workspace *ws_create(const Mesh &m, bool fp64) {
             ws->wedge = ws_alloc<char>(*ws, (size_t)m.E * edge_slots(m.N) * tsz);
         // the smallest shape (1 element per block) bounds the Ax partial count
         ws->cap_ax = m.E;
-        ws->cap_vec = vec_blocks(m.n);
+        ws->cap_vec = std::max(vec_blocks(m.n), update_blocks(m, fp64));
         ws->part_ax = ws_alloc<double>(*ws, ws->cap_ax);
         ws->part_vec = ws_alloc<double>(*ws, ws->cap_vec);
         ws->st = ws_alloc<CgState>(*ws, 1);

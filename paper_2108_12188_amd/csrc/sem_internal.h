@@ -388,10 +388,23 @@ struct DirectArgs {
     const int4 *elist, *elist_hi;
     const int32_t *egen;
     int N;
+    int packs;                  // packs of 4 points per block step (step_packs)
     uint32_t p3_magic;          // l / P^3 = (l * p3_magic) >> p3_shift for l < 2^31
     int p3_shift;
     uint32_t ms_magic;          // k / MS = (k * ms_magic) >> 20 for k < 1024
 };
+
+// Packs of 4 points that a block of 256 threads takes per step on a mesh of
+// two-launch iterations: as many whole elements as fit (216 at N = 5, 250 at
+// N = 9, 256 at N = 1, 3 and 7), so that a step forms the edge sums of its own
+// elements only; 256 where an element is no whole number of packs or more than
+// 256.  On the fly, us per iteration with 256 and with this: N = 9 FP32 0.12 M
+// points 14.2 / 13.6, 1.0 M 23.0 / 22.4, FP64 1.0 M 35.0 / 32.2; N = 5 FP32
+// 0.11 M 14.1 / 13.5, 0.59 M 19.0 / 18.4.
+constexpr int step_packs(int N) {
+    const int p3 = (N + 1) * (N + 1) * (N + 1);
+    return p3 % 4 == 0 && p3 / 4 <= 256 ? 256 / (p3 / 4) * (p3 / 4) : 256;
+}
 
 // step: the CgStep beside a workspace's state
 template <typename T>
@@ -401,7 +414,7 @@ DirectArgs<T> direct_args(const Mesh &m, const CgStep *step, const T *wedge,
     int lg = 0;
     while ((1 << lg) < m.P3) ++lg;
     const int shift = 31 + lg;
-    return {step, part_ax, n_ax, wedge, m.elist, m.elist_hi, m.egen, m.N,
+    return {step, part_ax, n_ax, wedge, m.elist, m.elist_hi, m.egen, m.N, step_packs(m.N),
             (uint32_t)(((uint64_t)1 << shift) / (uint64_t)m.P3 + 1), shift,
             (1u << 20) / (uint32_t)edge_slots(m.N) + 1};
 }

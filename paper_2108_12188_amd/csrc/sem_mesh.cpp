@@ -86,8 +86,11 @@ size_t mesh_footprint(int64_t E, int N, uint32_t flags, sem_precision prec) {
     // 5 vectors, the group sums (at most n / 3 groups of more than two
     // copies), reduction partials
     const size_t we = (size_t)E * edge_slots(N);      // compact edge array
-    const size_t ws32 = n * 4 * 5 + n / 3 * 4 + we * 4 + (size_t)E * 8 + (size_t)vec_blocks((int64_t)n) * 8 + 1024;
-    const size_t ws64 = n * 8 * 5 + n / 3 * 8 + we * 8 + (size_t)E * 8 + (size_t)vec_blocks((int64_t)n) * 8 + 1024;
+    size_t nvec = (size_t)vec_blocks((int64_t)n);
+    if (n <= (size_t)kDirectMaxPoints)
+        nvec = std::max(nvec, n / (4 * (size_t)step_packs(N)) + 1);
+    const size_t ws32 = n * 4 * 5 + n / 3 * 4 + we * 4 + (size_t)E * 8 + nvec * 8 + 1024;
+    const size_t ws64 = n * 8 * 5 + n / 3 * 8 + we * 8 + (size_t)E * 8 + nvec * 8 + 1024;
     if (prec == SEM_FP32) b += ws32;
     else if (prec == SEM_FP64) b += ws64;
     else b += ws32 + ws64;

@@ -182,7 +182,8 @@ __device__ __forceinline__ void update_gather_body(int64_t n, T *__restrict__ r,
                                                    const uint8_t *__restrict__ mcode,
                                                    const GatherMap &gm, CgState *st,
                                                    double *partial, int64_t vb, int64_t vgrid,
-                                                   PcArgs<T> pc = PcArgs<T>{}) {
+                                                   PcArgs<T> pc = PcArgs<T>{},
+                                                   int packs = kVecThreads) {
     // the state's loads go out with the block's set-up; a stopped state
     // returns before the first store to global memory (uniform)
     const int stopped = st->stop;
@@ -193,8 +194,9 @@ __device__ __forceinline__ void update_gather_body(int64_t n, T *__restrict__ r,
     if (stopped) return;
     double acc = 0.0, acc2 = 0.0;
     const int64_t n4 = n >> 2;
-    const int64_t stride = vgrid * blockDim.x;
-    const int64_t tid = xcd_block(vb, vgrid) * blockDim.x + threadIdx.x;
+    // threads past the block's packs have none (then n is a multiple of 4)
+    const int64_t stride = vgrid * packs;
+    const int64_t tid = (int)threadIdx.x < packs ? xcd_block(vb, vgrid) * packs + threadIdx.x : n4;
     constexpr int K = kUpdPacks;
     for (int64_t q = tid; q < n4; q += K * stride) {
         int64_t qq[K];
@@ -346,7 +348,8 @@ __device__ __forceinline__ void update_struct_body(int64_t n, T *__restrict__ r,
                                                    const T *__restrict__ wg,
                                                    const StructMap &sm, CgState *st,
                                                    double *partial, int64_t vb, int64_t vgrid,
-                                                   PcArgs<T> pc = PcArgs<T>{}) {
+                                                   PcArgs<T> pc = PcArgs<T>{},
+                                                   int packs = kVecThreads) {
     // the state's loads go out with the block's set-up; a stopped state
     // returns before the first store to global memory (uniform)
     const int stopped = st->stop;
@@ -359,8 +362,9 @@ __device__ __forceinline__ void update_struct_body(int64_t n, T *__restrict__ r,
     if (stopped) return;
     double acc = 0.0, acc2 = 0.0;
     const int64_t n4 = n >> 2;
-    const int64_t stride = vgrid * blockDim.x;
-    const int64_t tid = xcd_block(vb, vgrid) * blockDim.x + threadIdx.x;
+    // threads past the block's packs have none (then n is a multiple of 4)
+    const int64_t stride = vgrid * packs;
+    const int64_t tid = (int)threadIdx.x < packs ? xcd_block(vb, vgrid) * packs + threadIdx.x : n4;
     constexpr int K = kUpdStructPacks;
     for (int64_t q = tid; q < n4; q += K * stride) {
         int64_t qq[K];
@@ -486,8 +490,10 @@ __device__ __forceinline__ void alpha_block_body(CgState *st, const CgStep *step
 // 1024 at every order (N = 1: 128 elements of 8 slots).
 constexpr int kMaxStepSlots = 1024;
 // Slots a thread of 256 loads ahead: 1 where a step's elements have at most
-// 256 (N = 7, 10, 11), else 2 (the rest of N = 1 and 2 is looped over).
-__host__ __device__ constexpr int direct_tasks(int N) { return N == 7 || N >= 10 ? 1 : 2; }
+// 256 (N = 5, 7, 9, 10, 11), else 2 (the rest of N = 1 and 2 is looped over).
+__host__ __device__ constexpr int direct_tasks(int N) {
+    return N == 5 || N == 7 || N >= 9 ? 1 : 2;
+}
 
 // The positions (in the operator's edge array) of one slot's copies, and
 // their values: a missing copy reads position 0, one line for the whole wave
@@ -555,9 +561,9 @@ __device__ __forceinline__ void update_direct_body(int64_t n, T *__restrict__ r,
     __shared__ T es[kMaxStepSlots];
     const int P = dir.N + 1, MS = edge_slots(dir.N);
     const int64_t n4 = n >> 2;
-    const int64_t stride = vgrid * kVecThreads;
+    const int64_t stride = vgrid * dir.packs;
     const int t0 = (int)threadIdx.x;
-    const int64_t qb = xcd_block(vb, vgrid) * kVecThreads;      // the block's first pack
+    const int64_t qb = xcd_block(vb, vgrid) * dir.packs;        // the block's first pack
     double acc = 0.0, acc2 = 0.0;
     T a = T(0);
     CgStep h = *dir.st_in;
@@ -573,11 +579,12 @@ __device__ __forceinline__ void update_direct_body(int64_t n, T *__restrict__ r,
     // one, store nothing and add nothing
     bool first = true;
     for (int64_t q0 = qb; first || q0 < n4; q0 += stride) {
-        const bool live = q0 + t0 < n4;
-        const int64_t q = live ? q0 + t0 : n4 - 1;
+        const int64_t qend = q0 + dir.packs < n4 ? q0 + dir.packs : n4;
+        const bool live = q0 + t0 < qend;
+        const int64_t q = live ? q0 + t0 : (q0 < n4 ? qend : n4) - 1;
         // ---- round 1 -------------------------------------------------------
         const int64_t l0 = 4 * (q0 < n4 ? q0 : n4 - 1);
-        const int64_t lend = l0 + 4 * kVecThreads < n ? l0 + 4 * kVecThreads : n;
+        const int64_t lend = l0 + 4 * dir.packs < n ? l0 + 4 * dir.packs : n;
         const int64_t e0 = (int64_t)(((uint64_t)l0 * dir.p3_magic) >> dir.p3_shift);
         const int nel = (int)((int64_t)(((uint64_t)(lend - 1) * dir.p3_magic) >> dir.p3_shift) -
                               e0) + 1;

@@ -129,3 +129,34 @@ def test_stop_inside_a_chunk(fp64):
     w, s = gm.cg_solve(b, geom=1, tol=1e-3)
     assert s["iters"] == r["iters"] and torch.equal(x, w)
     gm.close()
+
+
+@pytest.mark.parametrize("N", [1, 3, 5, 7, 9])
+def test_whole_element_steps(N):
+    """Orders whose update steps hold whole elements (128, 16, 4, 2 and 1 of
+    them): element counts around one step, alone, in a batch of two-launch
+    iterations and in one whose total size takes four.  The partition into
+    blocks is the mesh's, so all three give the same bits."""
+    import torch
+    import paper_2108_12188_amd as sem
+    say(f"whole-element steps N={N}")
+    per = {1: 128, 3: 16, 5: 4, 7: 2, 9: 1}[N]
+    shapes = [(2, 2, k) for k in sorted({1, max(1, per // 4), per // 4 + 1, per // 2 + 1})]
+    shapes.append((3, 3, 3))
+    boxes = [box_mesh(*s, N, perturb=0.1, seed=41 + q, permute=q % 2 == 1, reorient=q % 2 == 1)
+             for q, s in enumerate(shapes)]
+    filler = box_mesh(15, 14, 14, 6, perturb=0.1, seed=3)
+    assert filler.n_local > 1 << 19
+    meshes = [sem.Mesh.from_box(b) for b in boxes + [filler]]
+    second = sem.Mesh.from_box(filler)
+    bs = [to_dev(random_global_rhs(b, seed=5), torch.float32) for b in boxes + [filler, filler]]
+    alone = [m.cg_solve(b, geom=1, fixed_iters=3)[0] for m, b in zip(meshes, bs)]
+    k = len(boxes)
+    for members in (meshes[:k], meshes + [second]):
+        batch = sem.Batch(members)
+        xs, infos = batch.solve(bs[:len(members)], prec=sem.FP32, geom=1, fixed_iters=3)
+        for x, ref, shape in zip(xs, alone, shapes):
+            assert torch.equal(x, ref), (len(members), shape)
+        batch.close()
+    for m in meshes + [second]:
+        m.close()
