@@ -320,8 +320,9 @@ struct HostTables {
     std::vector<int32_t> egen;
     std::vector<int32_t> gsrc_direct;   // gsrc with the edge slots of larger groups
 };
-// Fills the tables of the two-launch iteration where it applies.
-void build_direct_tables(int64_t E, int N, HostTables &t);
+// Fills the tables of the two-launch iteration where it applies; points: also
+// the per-point table, which a mesh with the table-free gather need not have.
+void build_direct_tables(int64_t E, int N, HostTables &t, bool points = true);
 // Validates glob_id / dirichlet (fail() on error) and fills t.
 void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, HostTables &t);
 

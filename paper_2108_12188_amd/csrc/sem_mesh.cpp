@@ -135,8 +135,6 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
         t.gsum_wedge = false;
         t.gs_struct = false;
     }
-    build_direct_tables(E, N, t);
-    m->direct = t.direct;
     m->inline32 = t.gs_in_update && takes_inline_scalars(N, n, false);
     m->inline64 = t.gs_in_update && takes_inline_scalars(N, n, true);
     m->n_glob = t.n_glob;
@@ -157,6 +155,8 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
     m->gs_struct = t.gs_struct && !(flags & SEM_MESH_GATHER_TABLE);
     m->gs_struct_solo =
         m->gs_struct && ((flags & SEM_MESH_GATHER_TABLE_FREE) || n >= kTableFreeMinPoints);
+    build_direct_tables(E, N, t, !m->gs_struct_solo);
+    m->direct = t.direct;
     if (m->gs_struct) {
         m->ecls = t.ecls;
         m->n_egroups = t.n_egroups;

@@ -413,7 +413,7 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     t.gs_struct = ok && build_struct_tables(E, N, mcode, plink, cnt, start, byid, t);
 }
 
-void build_direct_tables(int64_t E, int N, HostTables &t) {
+void build_direct_tables(int64_t E, int N, HostTables &t, bool points) {
     const int MS = edge_slots(N);
     const int64_t n = E * (N + 1) * (N + 1) * (N + 1);
     t.direct = false;
@@ -449,6 +449,8 @@ void build_direct_tables(int64_t E, int N, HostTables &t) {
             for (int64_t k = 0; k < t.ecls.ng[c]; ++k)
                 add_group(t.ewedge_idx.data() + t.ecls.io[c] + k * t.ecls.M[c], t.ecls.M[c]);
     }
+    t.direct = true;
+    if (t.gs_struct && !points) return;
     t.gsrc_direct = t.gsrc;
     for (int c = 0; c < t.gs.ncls; ++c) {
         const int M = t.gs.M[c];
@@ -460,7 +462,6 @@ void build_direct_tables(int64_t E, int N, HostTables &t) {
             if (!t.gs_struct) add_group(pos, M);
         }
     }
-    t.direct = true;
 }
 
 }  // namespace sem
