@@ -10,6 +10,7 @@
 // B_q = w_q |J|.
 #include <type_traits>
 
+#include "sem_geom_body.h"
 #include "sem_internal.h"
 
 namespace sem {
@@ -129,11 +130,12 @@ struct Pencils {
 // and so on.  The factors come from the vertices (FP64), so the result
 // does not depend on which G form the mesh stores.
 //
-// Bound by FP64 arithmetic: a point's factors (the map's columns, one divide)
-// cost more than its 3 P line terms, so each point's are formed once; G11 and
-// G22 go through LDS, where the lines along i and j read them (rows padded to
-// an odd stride), G33 stays in the line's own thread.  N = 7, 2.1 M points:
-// 220 us with the factors formed anew for each line term, 19 so.
+// Bound by FP64 arithmetic: a point's factors (one divide) cost more than its
+// 3 P line terms, so each point's are formed once, from the column polynomials
+// that the operator uses; G11 and G22 go through LDS, where the lines along i
+// and j read them (rows padded to an odd stride), G33 stays in the line's own
+// thread.  N = 7, 2.1 M points: 220 us with the factors formed anew for each
+// line term, 19 once per point from the eight vertices, 15.7 so.
 template <int P>
 __global__ void __launch_bounds__(Pencils<P>::kThreads)
 diag_local_kernel(int64_t E, const double *__restrict__ vert, const double *__restrict__ xi,
@@ -149,15 +151,20 @@ diag_local_kernel(int64_t E, const double *__restrict__ vert, const double *__re
     double g33[P], s[P];
     if (act) {
         const double di = D[i * P + i], dj = D[j * P + j];
+        const ColumnGeom<double> cg =
+            column_geom<double>(vert + 24 * e, xi[i], xi[j], w[i] * w[j]);
 #pragma unroll
         for (int k = 0; k < P; ++k) {
-            double G[6];
-            gfactors(vert + 24 * e, xi, w, i, j, k, G);
-            g11[slot][k][j * kRowS + i] = G[0];
-            g22[slot][k][j * kRowS + i] = G[3];
-            g33[k] = G[5];
+            const double z = xi[k];
+            const Vec3<double> r0 = axpy3(z, cg.R01, cg.R00), r1 = axpy3(z, cg.R11, cg.R10);
+            const Vec3<double> r2 = axpy3(z, axpy3(z, cg.R22, cg.R21), cg.R20);
+            const double f = cg.wij * w[k] / (cg.d0 + z * (cg.d1 + z * cg.d2));
+            g11[slot][k][j * kRowS + i] = f * dot3(r0, r0);
+            g22[slot][k][j * kRowS + i] = f * dot3(r1, r1);
+            g33[k] = f * dot3(r2, r2);
             const double dk = D[k * P + k];
-            s[k] = 2.0 * di * dj * G[1] + 2.0 * di * dk * G[2] + 2.0 * dj * dk * G[4];
+            s[k] = 2.0 * di * dj * (f * dot3(r0, r1)) + 2.0 * di * dk * (f * dot3(r0, r2)) +
+                   2.0 * dj * dk * (f * dot3(r1, r2));
         }
     }
     __syncthreads();
