@@ -134,6 +134,7 @@ bool build_struct_tables(int64_t E, int N, const std::vector<uint8_t> &mcode,
     GsClasses ec{};
     std::vector<int32_t> &ew = t.ewedge_idx;
     ew.clear();
+    ew.reserve((size_t)(E * MS) + 8 * (kMaxGsClasses + 1));
     t.n_egroups = 0;
     int sizes_seen[256] = {0};
     for (int64_t g = 0; g < G; ++g) {
@@ -246,9 +247,10 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     }
     std::vector<uint8_t> &mcode = t.mcode;
     mcode.assign(n, 0);
-    int64_t n_dir = 0;
+    int64_t n_dir = 0, n_copies = 0;
     for (int64_t l = 0; l < n; ++l) {
         const int32_t c = cnt[cid[l]];
+        n_copies += c > 1;
         if (c > kMaxMultiplicity)
             fail(SEM_EINVAL, "more than 127 local copies of one global point");
         const bool d = dflag[cid[l]] == 1;
@@ -274,6 +276,7 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     int64_t n_shared = 0, n_groups = 0;
     std::vector<int32_t> &gs_idx = t.gs_idx;
     gs_idx.clear();
+    gs_idx.reserve((size_t)n_copies + 8 * (kMaxGsClasses + 1));
     // per local point: the other copy of a pair (m = 2), or the rank of its
     // group among the groups of more than two copies (class order)
     std::vector<int32_t> plink(n, 0);
