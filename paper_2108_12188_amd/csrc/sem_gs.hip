@@ -70,9 +70,13 @@ constexpr int64_t kPointsPerBlock = (int64_t)kGsThreads * kPointsPerThread;
 
 // w <- mask(QQ^T w): the first nb_gs blocks take the groups and write zeros
 // to the masked ones, the others zero the Dirichlet points of one copy.
-// Bound by memory (the strided faces touch almost every line of w).  FP64
-// N = 7, 6.2 M points: 27.5 us and 5.5 for the mask as a pass of its own, 28.2
-// in one launch (32.0 with the flag read from each group's first point).
+// Bound by memory (the strided faces touch almost every line of w).  Calls of
+// the gather-scatter with the mask as a pass of its own, in one launch, and
+// without a mask: FP64 N = 7 2.1 M points 15.0, 11.7, 11.8 us, 16.8 M 71.0,
+// 67.0, 66.7; FP32 12.5, 9.7, 9.8 and 43.1, 40.1, 39.9.  With the masked groups
+// last in their class (no bits) the plain pass lost 2 to 7% to its locality;
+// with the flag read from a group's first point, or the loads of masked groups
+// left out, the launch took longer than the two passes at 6 to 17 M points.
 template <typename T>
 __global__ void __launch_bounds__(kGsThreads)
 gs_mask_kernel(const GsClasses cls, int64_t nb_gs, int64_t nb_logical,
@@ -162,7 +166,7 @@ void launch_gs_mask(const Mesh &m, T *w, hipStream_t s) {
     const int64_t total = nb + (m.n_dir1 + kPointsPerBlock - 1) / kPointsPerBlock;
     if (total == 0) return;
     hipLaunchKernelGGL((gs_mask_kernel<T>), dim3((unsigned)total), dim3(kGsThreads), 0, s, m.gs,
-                       nb, nlb, m.gs_idx, (InPlaceMasked<T>{{w}}), m.dir_idx, m.n_dir1);
+                       nb, nlb, m.gs_idx, (InPlaceMasked<T>{{w}, m.gs_zero}), m.dir_idx, m.n_dir1);
     check_hip(hipGetLastError(), "gs kernel launch");
 }
 
@@ -172,7 +176,7 @@ void launch_rhs(const Mesh &m, const double *f, T *b, hipStream_t s) {
     const int64_t nb = m.n_groups ? gs_phys_blocks(nlb) : 0;
     const int64_t total = nb + (m.n + kPointsPerBlock - 1) / kPointsPerBlock;
     hipLaunchKernelGGL((rhs_kernel<T>), dim3((unsigned)total), dim3(kGsThreads), 0, s, m.gs, nb,
-                       nlb, m.gs_idx, (MassSource<T>{m.B64, f, b}), m.mcode, m.n);
+                       nlb, m.gs_idx, (MassSource<T>{m.B64, f, b, m.gs_zero}), m.mcode, m.n);
     check_hip(hipGetLastError(), "rhs kernel launch");
 }
 

@@ -22,7 +22,9 @@ struct alignas(M * 4 <= 16 ? M * 4 : 16) IdxVec {
 };
 
 // What a gather-scatter reads and writes at a local index; kMask: the groups
-// on the Dirichlet boundary (the last of their class) become zero unread.
+// on the Dirichlet boundary become zero.  A bit per group in group order marks
+// them; its word loads with the indices and only selects the result, so that no
+// load waits for it.
 template <typename T>
 struct InPlace {
     using Value = T;
@@ -34,6 +36,7 @@ struct InPlace {
 template <typename T>
 struct InPlaceMasked : InPlace<T> {
     static constexpr bool kMask = true;
+    const uint32_t *__restrict__ zero;
 };
 
 // b = mask(QQ^T (B f)): a group's products are rounded before they are summed
@@ -45,6 +48,7 @@ struct MassSource {
     const double *__restrict__ B;
     const double *__restrict__ f;
     T *__restrict__ b;
+    const uint32_t *__restrict__ zero;
     __device__ __forceinline__ double load(int32_t q) const {
 #pragma clang fp contract(off)
         return B[q] * f[q];
@@ -52,21 +56,29 @@ struct MassSource {
     __device__ __forceinline__ void store(int32_t q, double s) const { b[q] = (T)s; }
 };
 
+template <typename A>
+__device__ __forceinline__ uint32_t mask_word(const A &a, int64_t zo, int64_t g) {
+    if constexpr (A::kMask) return a.zero[zo + (g >> 5)];
+    else return 0;
+}
+
 // Groups of a compile-time size M: every lane first issues the index loads
 // of all its groups, then all value loads, so each lane keeps
 // kGsPerThread * M independent loads in flight (groups are disjoint, so the
 // stores of one group never alias the loads of another).
 template <int M, typename A>
 __device__ __forceinline__ void gs_groups_fixed(const int32_t *__restrict__ ib, int64_t g0,
-                                                int64_t ng, int64_t nsum, const A &a) {
+                                                int64_t ng, int64_t zo, const A &a) {
     using V = typename A::Value;
     constexpr int kGsPerThread = gs_per_thread(M);
     int32_t q[kGsPerThread][M];
     bool ok[kGsPerThread];
+    uint32_t zw[kGsPerThread];
 #pragma unroll
     for (int it = 0; it < kGsPerThread; ++it) {
         const int64_t g = g0 + (int64_t)it * kGsThreads;
         ok[it] = g < ng;
+        zw[it] = A::kMask ? mask_word(a, zo, ok[it] ? g : ng - 1) : 0;
         if (ok[it]) {
             const IdxVec<M> *src = reinterpret_cast<const IdxVec<M> *>(ib + g * M);
             const IdxVec<M> iv = *src;
@@ -80,9 +92,8 @@ __device__ __forceinline__ void gs_groups_fixed(const int32_t *__restrict__ ib, 
     V v[kGsPerThread][M];
 #pragma unroll
     for (int it = 0; it < kGsPerThread; ++it) {
-        const bool sum = ok[it] && (!A::kMask || g0 + (int64_t)it * kGsThreads < nsum);
 #pragma unroll
-        for (int t = 0; t < M; ++t) v[it][t] = sum ? a.load(q[it][t]) : V(0);
+        for (int t = 0; t < M; ++t) v[it][t] = ok[it] ? a.load(q[it][t]) : V(0);
     }
 #pragma unroll
     for (int it = 0; it < kGsPerThread; ++it) {
@@ -90,6 +101,8 @@ __device__ __forceinline__ void gs_groups_fixed(const int32_t *__restrict__ ib, 
         V s = v[it][0];
 #pragma unroll
         for (int t = 1; t < M; ++t) s += v[it][t];
+        // every group of a thread has the same bit (a step is 256 groups)
+        if (A::kMask && (zw[it] >> (g0 & 31) & 1)) s = V(0);
 #pragma unroll
         for (int t = 0; t < M; ++t) a.store(q[it][t], s);
     }
@@ -97,13 +110,13 @@ __device__ __forceinline__ void gs_groups_fixed(const int32_t *__restrict__ ib, 
 
 template <typename A>
 __device__ __forceinline__ void gs_groups_any(const int32_t *__restrict__ ib, int M, int64_t g0,
-                                              int64_t ng, int64_t nsum, const A &a) {
+                                              int64_t ng, int64_t zo, const A &a) {
     for (int it = 0; it < gs_per_thread(M); ++it) {
         const int64_t g = g0 + (int64_t)it * kGsThreads;
         if (g >= ng) break;
         const int32_t *gi = ib + g * M;
         typename A::Value s = 0;
-        if (!A::kMask || g < nsum) {
+        if (!(mask_word(a, zo, g) >> (g & 31) & 1)) {
             s = a.load(gi[0]);
             for (int t = 1; t < M; ++t) s += a.load(gi[t]);
         }
@@ -204,12 +217,12 @@ __device__ __forceinline__ void gs_logical_block(const GsClasses &cls, int64_t l
     const int M = cls.M[c];
     const int64_t g0 = (lb - cls.blk0[c]) * gs_per_block(M) + threadIdx.x;
     const int32_t *ib = idx + cls.io[c];
-    const int64_t ng = cls.ng[c], nsum = cls.nfree[c];
+    const int64_t ng = cls.ng[c], zo = cls.zo[c];
     switch (M) {
-        case 2: gs_groups_fixed<2>(ib, g0, ng, nsum, a); break;
-        case 4: gs_groups_fixed<4>(ib, g0, ng, nsum, a); break;
-        case 8: gs_groups_fixed<8>(ib, g0, ng, nsum, a); break;
-        default: gs_groups_any(ib, M, g0, ng, nsum, a); break;
+        case 2: gs_groups_fixed<2>(ib, g0, ng, zo, a); break;
+        case 4: gs_groups_fixed<4>(ib, g0, ng, zo, a); break;
+        case 8: gs_groups_fixed<8>(ib, g0, ng, zo, a); break;
+        default: gs_groups_any(ib, M, g0, ng, zo, a); break;
     }
 }
 

@@ -150,7 +150,7 @@ struct GsClasses {
     int ncls;
     int M[kMaxGsClasses];          // copies per group in this class
     int64_t ng[kMaxGsClasses];     // groups in this class
-    int64_t nfree[kMaxGsClasses];  // of these off the Dirichlet boundary; they come first
+    int64_t zo[kMaxGsClasses];     // first word of the class in gs_zero
     int64_t io[kMaxGsClasses];     // offset of the class in gs_idx
     int64_t blk0[kMaxGsClasses];   // first block of the class in a gs launch
     // gather-scatter launches only (null: identity): DEVICE int32 [blocks],
@@ -207,6 +207,7 @@ struct Mesh {
     uint8_t *mcode = nullptr;     // [n]: multiplicity | Dirichlet bit
     int32_t *gs_idx = nullptr;    // [n_shared], class-major, groups of M ascending indices
     int32_t *gs_lb_order = nullptr;   // gs.lb_order's array
+    uint32_t *gs_zero = nullptr;  // bit g & 31 of word zo + (g >> 5): group g is masked
     int32_t *dir_idx = nullptr;   // [n_dir], the n_dir1 points of one copy first
     // Shared sums inside the CG update (used when every shared point lies on
     // the surface of its element's P^3 block): gsrc[l] is the other copy of
@@ -298,6 +299,7 @@ struct HostTables {
     std::vector<uint8_t> mcode;     // [n]
     std::vector<int32_t> gs_idx;    // class-major ascending member lists
     std::vector<int32_t> gs_lb_order;  // see GsClasses::lb_order
+    std::vector<uint32_t> gs_zero;  // see Mesh::gs_zero
     std::vector<int32_t> dir_idx;   // Dirichlet local points
     bool gs_in_update = false;      // every shared point on its element's surface
     int64_t n_groups_multi = 0;     // groups with more than two copies

@@ -38,7 +38,7 @@ void upload(T *dst, const T *src, size_t count, hipStream_t s) {
 
 void free_mesh_arrays(Mesh *m) {
     void *ptrs[] = {m->vert64,     m->vert32,  m->edge32,  m->G32,     m->G64,       m->B64,
-                    m->mcode,      m->gs_idx,  m->gs_lb_order, m->dir_idx, m->gsrc,
+                    m->mcode,      m->gs_idx,  m->gs_lb_order, m->gs_zero, m->dir_idx, m->gsrc,
                     m->wedge_idx,  m->basis_blob, m->scratch, m->state,   m->minv64,
                     m->minv32,     m->erec,    m->pos_tab, m->ewedge_idx, m->elist, m->elist_hi,
                     m->egen,       m->gsrc_direct};
@@ -179,6 +179,7 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
         m->mcode = dev_alloc<uint8_t>(*m, (size_t)n);
         m->gs_idx = dev_alloc<int32_t>(*m, t.gs_idx.size());
         m->gs_lb_order = dev_alloc<int32_t>(*m, t.gs_lb_order.size());
+        m->gs_zero = dev_alloc<uint32_t>(*m, t.gs_zero.size());
         m->dir_idx = dev_alloc<int32_t>(*m, t.dir_idx.size());
         // a mesh that runs two launches alone and the table-free form in
         // batches needs no group ranks
@@ -246,6 +247,7 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
         upload(m->gs_idx, t.gs_idx.data(), t.gs_idx.size(), s);
         upload(m->gs_lb_order, t.gs_lb_order.data(), t.gs_lb_order.size(), s);
         if (SEM_GS_BLOCK_ORDER) m->gs.lb_order = m->gs_lb_order;
+        upload(m->gs_zero, t.gs_zero.data(), t.gs_zero.size(), s);
         upload(m->dir_idx, t.dir_idx.data(), t.dir_idx.size(), s);
         if (m->gsrc) upload(m->gsrc, t.gsrc.data(), t.gsrc.size(), s);
         if (m->gsrc_direct) upload(m->gsrc_direct, t.gsrc_direct.data(), t.gsrc_direct.size(), s);

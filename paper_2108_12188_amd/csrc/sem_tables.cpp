@@ -169,7 +169,7 @@ bool build_struct_tables(int64_t E, int N, const std::vector<uint8_t> &mcode,
             }
             ++ng;
         }
-        ec.ng[c] = ec.nfree[c] = ng;
+        ec.ng[c] = ng;
         t.n_egroups += ng;
     }
     while (ew.size() % 8) ew.push_back(0);
@@ -281,7 +281,7 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     // group among the groups of more than two copies (class order)
     std::vector<int32_t> plink(n, 0);
     int64_t n_multi = 0;
-    std::vector<int64_t> masked;
+    t.gs_zero.clear();
     for (int msz = 2; msz <= kMaxMultiplicity; ++msz) {
         if (!sizes_seen[msz]) continue;
         if (cls.ncls == kMaxGsClasses)
@@ -292,7 +292,11 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
         while (gs_idx.size() % 8) gs_idx.push_back(0);
         cls.io[c] = (int64_t)gs_idx.size();
         int64_t ng = 0;
-        const auto add_group = [&](int64_t g) {
+        cls.zo[c] = (int64_t)t.gs_zero.size();
+        for (int64_t g = 0; g < G; ++g) {
+            if (cnt[g] != msz) continue;
+            if (ng % 32 == 0) t.gs_zero.push_back(0);
+            if (dflag[g] == 1) t.gs_zero.back() |= 1u << (ng % 32);
             for (int64_t o = start[g]; o < start[g + 1]; ++o) gs_idx.push_back(byid[o]);
             if (msz == 2) {
                 plink[byid[start[g]]] = byid[start[g] + 1];
@@ -302,16 +306,7 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
                 ++n_multi;
             }
             ++ng;
-        };
-        // the masked groups last: a launch that also masks knows them by rank
-        masked.clear();
-        for (int64_t g = 0; g < G; ++g) {
-            if (cnt[g] != msz) continue;
-            if (dflag[g] == 1) masked.push_back(g);
-            else add_group(g);
         }
-        cls.nfree[c] = ng;
-        for (const int64_t g : masked) add_group(g);
         cls.ng[c] = ng;
         n_groups += ng;
         n_shared += ng * msz;
