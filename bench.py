@@ -77,8 +77,8 @@ def ax_flops_per_point(N: int, geom: str) -> float:
 # the sources of every kernel the committed counter summary describes (the
 # operator, the gathered update and its group sums, the stand-alone
 # gather-scatter)
-COUNTER_SOURCES = ("sem_ax_order.hip", "sem_vec.hip", "sem_vec_body.h", "sem_gs.hip",
-                   "sem_gs_body.h")
+COUNTER_SOURCES = ("sem_ax_order.hip", "sem_geom_body.h", "sem_vec.hip", "sem_vec_body.h",
+                   "sem_gs.hip", "sem_gs_body.h")
 
 
 def src_hash() -> str:
