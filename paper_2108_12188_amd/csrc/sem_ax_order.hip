@@ -196,6 +196,16 @@ struct CgOpenRho {
         hist_rho = a.st->hist_rho;
         sum.load(a.rho_part, a.n_rho, nthr, 0);
     }
+    // A launch past convergence: block 0 passes the state on and the block
+    // ends before its first tile is staged.  Asked behind the loads of read(),
+    // which a live iteration needs next anyway.  N = 7, 4.1 M points: 9.5 us
+    // an iteration past convergence, 16.3 with the tile staged and the
+    // partials summed first; live iterations 42.7 and 43.3.
+    __device__ __forceinline__ bool stopped(const AxArgs<T> &a, int64_t vb) const {
+        if (!h.stop) return false;
+        if (vb == 0 && threadIdx.x == 0) *a.st_out = h;
+        return true;
+    }
     __device__ __forceinline__ CgOpen<T> finish(const AxArgs<T> &a, int64_t vb, int nthr) {
         double *const red = kOneWave ? nullptr : block_red();
         const double rho = sum.finish(a.rho_part, a.n_rho, nthr, red);
@@ -373,6 +383,7 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
     CgOpenRho<T> rho_open;
     if constexpr (FUSED && RHO) {
         rho_open.read(a, nwave * 64);
+        if (rho_open.stopped(a, vb)) return;   // uniform
     } else if constexpr (FUSED) {
         cgo = cg_open<T>(a);
         if (!cgo.run) return;        // uniform: the whole grid exits
@@ -744,6 +755,7 @@ __device__ __forceinline__ void ax_mfma_body(const AxArgs<float> &a, const Basis
         CgOpenRho<T, true> rho_open;
         if constexpr (FUSED && RHO) {
             rho_open.read(a, 64);
+            if (rho_open.stopped(a, vb)) return;   // uniform
         } else if constexpr (FUSED) {
             cgo = cg_open<T>(a);
             if (!cgo.run) return;        // uniform: the whole grid exits
@@ -978,6 +990,7 @@ __device__ __forceinline__ void ax_mfma10_body(const AxArgs<float> &a, const Bas
         CgOpenRho<T> rho_open;
         if constexpr (FUSED && RHO) {
             rho_open.read(a, 128);
+            if (rho_open.stopped(a, vb)) return;   // uniform
         } else if constexpr (FUSED) {
             cgo = cg_open<T>(a);
             if (!cgo.run) return;        // uniform: the whole grid exits

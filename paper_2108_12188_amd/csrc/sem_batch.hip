@@ -13,9 +13,9 @@
 // block that the problem's own single-mesh launch would run, with the same
 // tiles, the same grid stride and the same partial slot -- so every
 // problem's reductions happen in the same order as in its solo solve and
-// its result is bitwise identical.  Problems that have stopped exit at the
-// first instruction of their blocks.  The sequence is captured once in a
-// HIP graph and replayed.
+// its result is bitwise identical.  Blocks of a problem that has stopped read
+// its state and exit.  The sequence is captured once in a HIP graph and
+// replayed.
 #include <algorithm>
 #include <chrono>
 #include <cmath>

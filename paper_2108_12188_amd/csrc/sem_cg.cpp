@@ -27,8 +27,9 @@
 // the bits of the solo solve).
 // The CG scalars never leave the device.  Iterations are enqueued in chunks
 // (replayed HIP graphs by default); after each chunk the host reads the
-// state once.  Kernels of iterations past convergence exit at their first
-// instruction.
+// state once.  Kernels of iterations past convergence read the state (in two-
+// and three-launch iterations also the first partials or tables, which a
+// live block issues behind it) and exit.
 #include <chrono>
 #include <cmath>
 #include <cstring>

@@ -618,6 +618,12 @@ __device__ __forceinline__ void update_direct_body(int64_t n, T *__restrict__ r,
         Pack4<T> mi{}, zv{};
         if constexpr (PC) mi = reinterpret_cast<const Pack4<T> *>(pc.minv)[q];
         load_fence();
+        // past convergence block 0 passes the state on (behind the loads of
+        // round 1: asked alone, a live block would wait for the state first)
+        if (stopped) {                                         // uniform
+            if (vb == 0 && t0 == 0) store_step(st, h);
+            return;
+        }
         // ---- round 2 -------------------------------------------------------
 #pragma unroll
         for (int u = 0; u < TASKS; ++u) sc[u].load_values(dir);
