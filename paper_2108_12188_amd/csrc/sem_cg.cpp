@@ -95,7 +95,10 @@ Workspace *ws_create(const Mesh &m, bool fp64) {
         ws->st = ws_alloc<CgState>(*ws, 1);
         ws->step = ws_alloc<CgStep>(*ws, 1);
         ws->dval = ws_alloc<double>(*ws, 8);
-        SEM_HIP(hipHostMalloc((void **)&ws->h_st, sizeof(CgState)));
+        SEM_HIP(hipHostMalloc((void **)&ws->h_st, sizeof(CgState) + sizeof(uint64_t),
+                              hipHostMallocMapped | hipHostMallocCoherent));
+        ws->h_seq = reinterpret_cast<uint64_t *>(ws->h_st + 1);
+        *ws->h_seq = 0;
         SEM_HIP(hipHostMalloc((void **)&ws->h_val, 8 * sizeof(double)));
         SEM_HIP(hipStreamCreateWithFlags(&ws->stream, hipStreamNonBlocking));
         SEM_HIP(hipEventCreateWithFlags(&ws->ev, hipEventDisableTiming));
@@ -298,19 +301,40 @@ void run_chunk(const Mesh &m, Workspace &ws, bool otf, bool pc, int chunk, bool 
     SEM_HIP(hipGraphLaunch(it->second, s));
 }
 
-// A fixed count runs in equal chunks of at most 50: the launches of iterations
-// past it cost 1.5 to 2 us each although they do nothing (64 iterations as two
-// chunks of 50 ran 36 of them).
+// Iterations of a fixed count that are launched before the host has seen the
+// first state: the GPU works while it reaches the host and the first chunk's
+// graph is launched.  A zero right-hand side runs no more than these.  64
+// iterations of 4^3 elements N = 7 in FP64: 904 us with no look at the first
+// state (then 100 iterations of a zero right-hand side take 624 us), 910 so
+// (89), 949 waiting for a copy of it with nothing behind; 4 and 6 iterations
+// cover no more.
+constexpr int kFixedLead = 2;
+
+// The rest of a fixed count runs in equal chunks of at most 50: the launches
+// of an iteration past the count cost 4 to 11 us although they do nothing (64
+// iterations as two chunks of 50 ran 36 of them).
 int auto_chunk(int64_t n, int fixed) {
     if (fixed > 0) {
-        const int chunks = (fixed - 1) / 50 + 1;
-        return (fixed - 1) / chunks + 1;
+        const int rest = std::max(fixed - kFixedLead, 1), chunks = (rest - 1) / 50 + 1;
+        return (rest - 1) / chunks + 1;
     }
     return n < (1 << 20) ? 32 : (n < (1 << 23) ? 16 : 8);
 }
 
+// Waits for the state published last.  The wait is short unless the caller's
+// stream still has work before the solve: then it ends in a stream wait.
+void wait_published(Workspace &ws) {
+    const auto seen = [&] { return __atomic_load_n(ws.h_seq, __ATOMIC_ACQUIRE) == ws.seq; };
+    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(500);
+    while (!seen())
+        if (std::chrono::steady_clock::now() > until) {
+            SEM_HIP(hipStreamSynchronize(ws.stream));
+            if (!seen()) fail(SEM_EDEVICE, "CG state was not published");
+        }
+}
+
 // Chunks of a fixed-count solve between two reads of the state: the host has
-// nothing to decide in them (each read leaves the GPU idle for about 10 us),
+// nothing to decide in them (each read leaves the GPU idle for 10 to 25 us),
 // but a solve that breaks down should not run on for long.
 constexpr int kFixedChunksPerPoll = 2;
 
@@ -344,8 +368,8 @@ struct InnerOut {
 // The caller has seen to it that no copy from or to ws.h_st is in flight.
 template <typename T>
 InnerOut cg_core(const Mesh &m, Workspace &ws, const T *b_dev, bool x0_zero, bool otf, bool pc,
-                 double tol, int max_iter, int fixed, int chunk, int per_poll, bool use_graph,
-                 int hist_len, KernelTimes *kt = nullptr) {
+                 double tol, int max_iter, int fixed, int lead, int chunk, int per_poll,
+                 bool use_graph, int hist_len, KernelTimes *kt = nullptr) {
     hipStream_t s = ws.stream;
     CgState h{};
     h.thresh = tol * tol;
@@ -374,13 +398,21 @@ InnerOut cg_core(const Mesh &m, Workspace &ws, const T *b_dev, bool x0_zero, boo
     // stops; a chunk that does not advance it means the device state is
     // inconsistent, which ends the loop with an error instead of spinning
     int last_iter = -1;
-    // a fixed count needs no read of the state before its first chunks
-    if (h.fixed && !kt) {
-        const int chunks = (fixed - 1) / chunk + 1;
-        for (int k = 0; k < std::min(chunks, per_poll); ++k)
-            run_chunk<T>(m, ws, otf, pc, chunk, use_graph);
+    bool stopped = false;
+    if (h.fixed && !kt && lead > 0) {
+        launch_publish_state(ws.st, ws.h_st, ws.h_seq, ++ws.seq, s);
+        const int first = std::min(lead, fixed);
+        for (int c = 0; c < first; ++c) enqueue_iteration<T>(m, ws, otf, pc, s);
+        wait_published(ws);
+        stopped = ws.h_st->stop != 0;
+        if (!stopped) {
+            const int chunks = (fixed - first + chunk - 1) / chunk;
+            for (int k = 0; k < std::min(chunks, per_poll); ++k)
+                run_chunk<T>(m, ws, otf, pc, chunk, use_graph);
+            if (chunks == 0) enqueue_close<T>(m, ws, otf, pc, s);
+        }
     }
-    for (;;) {
+    while (!stopped) {
         SEM_HIP(hipMemcpyAsync(ws.h_st, ws.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
         SEM_HIP(hipStreamSynchronize(s));
         if (ws.h_st->stop) break;
@@ -466,7 +498,8 @@ static sem_status cg_plain(Mesh &m, const sem_cg_opts &o, const void *b_user, vo
     const int hist_len = (o.hist_rho || o.hist_alpha) ? o.hist_len : 0;
     KernelTimes kt;
     const int per_poll = o.poll_every > 0 ? 1 : kFixedChunksPerPoll;
-    InnerOut io = cg_core<T>(m, ws, b, false, otf, pc, o.tol, o.max_iter, o.fixed_iters, chunk,
+    const int lead = o.poll_every > 0 ? 0 : kFixedLead;
+    InnerOut io = cg_core<T>(m, ws, b, false, otf, pc, o.tol, o.max_iter, o.fixed_iters, lead, chunk,
                              per_poll, o.use_graph != 0, hist_len, o.kernel_ms ? &kt : nullptr);
     if (o.kernel_ms)
         for (int k = 0; k < 3; ++k) o.kernel_ms[k] = kt.count ? kt.ms[k] / kt.count : 0.0;
@@ -541,7 +574,7 @@ static sem_status cg_mixed(Mesh &m, const sem_cg_opts &o, const double *b, doubl
         SEM_HIP(hipEventRecord(w64.ev, s));
         SEM_HIP(hipStreamWaitEvent(w32.stream, w64.ev, 0));
         InnerOut io = cg_core<float>(m, w32, b32, true, otf, pc,
-                                     refine_inner_tol(inner_tol, o.tol, rel), inner_cap, 0, chunk, 1,
+                                     refine_inner_tol(inner_tol, o.tol, rel), inner_cap, 0, 0, chunk, 1,
                                      o.use_graph != 0, 0, o.kernel_ms ? &kt : nullptr);
         total += io.iters;
         last_stop = io.stop;

@@ -39,6 +39,8 @@ struct Workspace {
     CgState *st = nullptr;          // device state of this workspace's solves
     CgStep *step = nullptr;         // its other copy in two-launch iterations
     CgState *h_st = nullptr;        // pinned mirror
+    uint64_t *h_seq = nullptr;      // behind it: number of the last published state
+    uint64_t seq = 0;
     double *hist = nullptr;         // device histories: rho [cap], alpha [cap]
     int hist_cap = 0;
     double *dval = nullptr;         // device scalars

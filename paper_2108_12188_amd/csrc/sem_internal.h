@@ -556,6 +556,11 @@ void launch_update_direct(const Mesh &m, bool table_free, T *r, const T *w, cons
 // launch (nthr threads a block) would form it.
 void launch_close_rho(CgState *st, const double *partial, const double *partial2, int cnt,
                       int nthr, hipStream_t s);
+// The state into pinned host memory by a kernel, then *host_seq = seq: the host
+// learns of it without a copy command or an event in the stream, either of
+// which holds the stream for about 10 us.
+void launch_publish_state(const CgState *st, CgState *host, uint64_t *host_seq, uint64_t seq,
+                          hipStream_t s);
 // r = b - w (w may be null: r = b); p = 0; rho_0 = <r, r, c>; initial state.
 // With pc.minv: z = minv r, rho = <r, z, c>, and the threshold and the
 // reported residual use <r, r, c>.

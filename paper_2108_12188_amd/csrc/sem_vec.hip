@@ -71,6 +71,16 @@ close_rho_kernel(CgState *st, const double *partial, const double *partial2, int
     close_rho_body(st, partial, partial2, cnt, nthr);
 }
 
+static_assert(sizeof(CgState) % 8 == 0 && sizeof(CgState) / 8 <= 64, "one word per lane");
+__global__ void __launch_bounds__(64)
+publish_state_kernel(const CgState *st, CgState *host, uint64_t *host_seq, uint64_t seq) {
+    const int t = threadIdx.x;                       // one wave
+    if (t < (int)(sizeof(CgState) / 8))
+        reinterpret_cast<uint64_t *>(host)[t] = reinterpret_cast<const uint64_t *>(st)[t];
+    __threadfence_system();
+    if (t == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ void __launch_bounds__(kFinalizeThreads)
 finalize_rho_kernel(CgState *st, const double *partial, int cnt, const double *partial2) {
     finalize_rho_body(st, partial, cnt, partial2);
@@ -353,6 +363,12 @@ void launch_update_direct(const Mesh &m, bool table_free, T *r, const T *w, cons
         else update_direct_form<T, false, 2>(m, table_free, r, w, st, partial, s, pc, dir);
     }
     check_hip(hipGetLastError(), "update kernel launch");
+}
+
+void launch_publish_state(const CgState *st, CgState *host, uint64_t *host_seq, uint64_t seq,
+                          hipStream_t s) {
+    hipLaunchKernelGGL(publish_state_kernel, dim3(1), dim3(64), 0, s, st, host, host_seq, seq);
+    check_hip(hipGetLastError(), "state kernel launch");
 }
 
 void launch_close_rho(CgState *st, const double *partial, const double *partial2, int cnt,
