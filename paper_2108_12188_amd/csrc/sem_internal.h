@@ -20,27 +20,45 @@ constexpr uint8_t kMultMask = 0x7F;
 constexpr int kMaxP = kMaxOrder + 1;
 // Schedules of a CG iteration on a conforming mesh (see DirectArgs): up to
 // kDirectMaxPoints local points two launches, up to kInlineMaxPoints (FP64:
-// half of it) three, beyond it four.  On the fly, us per iteration with four
-// launches and with the schedule taken here: FP32 N = 7 0.11 M points 15.3 /
-// 12.3, 0.88 M 21.8 / 18.9 (two launches; 1.7 M with two: 27.8 / 30.6, the
-// group sums formed once per copy), 4.1 M 45.2 / 43.2 (three; 8 M N = 5 76.1 /
-// 79.1), N = 9 2.2 M 40.5 / 36.0, 4.1 M 52.6 / 46.4; FP64 N = 9 0.5 M 29.8 /
-// 26.4, N = 8 2 M 54.9 / 51.5 (4.1 M N = 9 with three: 91.8 / 94.6).  N = 7
-// in FP32 keeps four launches between 2^20 and 2^21 points, where each of its
-// one-wave blocks would sum the partials for one element (1.4 M: 25.0 / 25.6,
-// 1.7 M 27.7 / 29.0).
+// half of it; FP32 without matrix cores: three quarters) three, beyond it four.
+// On the fly, us per iteration with four launches and with the schedule taken
+// here: FP32 N = 7 0.11 M points 15.3 / 12.3, 0.88 M 21.8 / 18.9 (two launches;
+// 1.7 M with two: 27.8 / 30.6, the group sums formed once per copy), 2.2 M
+// 33.6 / 32.9, 3.0 M 38.6 / 37.3, 3.9 M 44.9 / 43.8 (three); N = 9 1.1 M 30.1 /
+// 28.4, 2.2 M 40.8 / 35.9, 3.8 M 52.4 / 46.2; FP64 N = 9 0.5 M 29.8 / 26.4, N = 8
+// 2 M 54.9 / 51.5, N = 9 2.0 M 57.0 / 57.5 (4.1 M 91.8 / 94.6).
+// VALU orders win less as the mesh grows, the partials being formed once per
+// tile: N = 5 1.1 M 27.6 / 26.6, 2.0 M 35.0 / 34.7, 2.7 M 42.4 / 42.9, 3.5 M 47.4 /
+// 48.2, 3.9 M 50.1 / 50.7, stored factors 2.2 M 43.5 / 41.9, 3.5 M 59.3 / 60.0;
+// N = 6 3.2 M 47.4 / 48.4; N = 8 3.0 M 45.6 / 44.9, 3.6 M 50.2 / 50.9.
+// FP32 N = 7 keeps four launches between 2^20 and 2^21 points, where steps of
+// its update that divide evenly leave 600 to 950 blocks, too few to hide
+// their loads (1.2 M 25.1 / 27.1, 1.5 M 26.4 / 27.8, 1.84 M 29.2 / 29.8, 1.97 M 30.1 /
+// 30.1, 2.1 M with 1024 blocks 30.0 / 29.2).  The rule knows the order, not the
+// engine, which can be set after the mesh is made.
 constexpr int64_t kDirectMaxPoints = int64_t(1) << 20;
 constexpr int64_t kInlineMaxPoints = int64_t(1) << 22;
+constexpr bool mfma_order(int N) { return N == 7 || N == 9; }
 inline bool takes_inline_scalars(int N, int64_t n, bool fp64) {
     if (n <= kDirectMaxPoints) return true;
     if (fp64) return n <= kInlineMaxPoints / 2;
+    if (!mfma_order(N)) return n <= kInlineMaxPoints / 4 * 3;
     return n <= kInlineMaxPoints && (N != 7 || n >= kInlineMaxPoints / 2);
 }
-// most blocks of the update there, in equal steps: every operator block sums
-// their partials (FP32 N = 7 4.1 M points: 1000 blocks 43.2 us, 2000 45.7;
-// N = 8 1.6 M: 781 blocks 29.7, 1562 31.0; the Jacobi iterations of N = 8 1.6 M:
-// 50 in 1733 us, with a cap of 1600 blocks 1837)
+// Most blocks of the update there, in equal steps: every operator block sums
+// their partials (N = 8 1.6 M: 781 blocks 29.7, 1562 31.0; the Jacobi iterations
+// of N = 8 1.6 M: 50 in 1733 us, with a cap of 1600 blocks 1837).  A block of
+// the matrix-core operator reads 1024 of them in one round of loads, and more
+// in a second one that waits for the first: FP32 N = 7 2.2 M points 1088 blocks
+// 35.1 us, 726 32.9; 3.5 M 1143 blocks 43.7, 857 41.5; N = 9 3.6 M 1172 46.3,
+// 879 45.7.
 constexpr int kInlineVecBlocks = 1280;
+constexpr int kInlineVecBlocksMfma = 1024;
+constexpr int inline_update_blocks(int vec_blocks, int N, bool fp64) {
+    const int cap = mfma_order(N) && !fp64 ? kInlineVecBlocksMfma : kInlineVecBlocks;
+    const int steps = (vec_blocks + cap - 1) / cap;
+    return (vec_blocks + steps - 1) / steps;
+}
 // local points from which a mesh takes the table-free gather by default
 // (below it, where a CG iteration is mostly launch latency, the table form
 // measured up to 8% faster; from it on the table-free form is as fast or

@@ -127,6 +127,9 @@ struct PartialSum {
         return s;
     }
 };
+static_assert(64 * PartialSum<true>::kBatch == kInlineVecBlocksMfma &&
+                  128 * PartialSum<false>::kBatch == kInlineVecBlocksMfma,
+              "the matrix-core blocks (N = 7: 64 threads, N = 9: 128) read the partials in one round");
 template <bool kOneWave = false>
 __device__ __forceinline__ double sum_partials_all(const double *partial, int cnt, int nthr,
                                                    double *red) {

@@ -255,9 +255,7 @@ int vec_blocks(int64_t n) {
 int update_blocks(const Mesh &m, bool fp64) {
     if (m.direct) return (int)((m.n + 4 * step_packs(m.N) - 1) / (4 * step_packs(m.N)));
     const int b = vec_blocks(m.n);
-    if (!m.inline_scalars(fp64) || b <= kInlineVecBlocks) return b;
-    const int steps = (b + kInlineVecBlocks - 1) / kInlineVecBlocks;   // equal steps, as above
-    return (b + steps - 1) / steps;
+    return m.inline_scalars(fp64) ? inline_update_blocks(b, m.N, fp64) : b;
 }
 
 template <typename T>
