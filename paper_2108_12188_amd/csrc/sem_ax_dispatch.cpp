@@ -167,17 +167,20 @@ AxShape ax_shape(int N, bool fp64, bool otf, int epb_override) {
     }
     int epb = epb_override > 0 ? epb_override : g_epb[otf ? 1 : 0][fp64 ? 1 : 0][N].load();
     if (epb <= 0) epb = fp64 ? kEpb64[N] : kEpb32[N];
-    // clamp to the kernel limits (FP32 CG-fused tiles of odd N also stage
-    // the next tile's r, p and vertices in LDS)
+    // clamp to the kernel limits: 512 threads and 64 KiB of element values in
+    // LDS (two tiles; FP32 CG-fused tiles of odd N also stage the next tile's
+    // r, p and vertices).  The padding of the tiles comes on top: at most 72 KiB
+    // in all (FP64 N = 7, eight elements), of 160 per CU, so that it takes no
+    // shape away (N = 9 with four elements) and two blocks still share a CU.
     const bool staged = !fp64 && P3 % 4 == 0;
-    auto lds = [&](int q) {
-        return 2 * tsz * (size_t)q * ax_tile_stride(P) + (staged ? 8 * (size_t)q * P3 + 96 * (size_t)q : 0);
+    auto lds = [&](int q, int tile) {
+        return 2 * tsz * (size_t)q * tile + (staged ? 8 * (size_t)q * P3 + 96 * (size_t)q : 0);
     };
-    while (epb > 1 && (((epb * P2 + 63) / 64) * 64 > 512 || lds(epb) > 65536)) --epb;
+    while (epb > 1 && (((epb * P2 + 63) / 64) * 64 > 512 || lds(epb, P3) > 65536)) --epb;
     AxShape s;
     s.epb = epb;
     s.threads = ((epb * P2 + 63) / 64) * 64;
-    s.lds = lds(epb);
+    s.lds = lds(epb, ax_tile_stride(P));
     s.mfma = false;
     return s;
 }
