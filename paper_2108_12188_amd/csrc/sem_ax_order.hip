@@ -123,9 +123,20 @@ __device__ __forceinline__ double block_sum(double v) { return block_sum_f64(v, 
 
 // Waves per SIMD the registers are held to.  FP32 up to N = 7: 4 (the
 // on-the-fly form is latency-bound below that occupancy).  FP64: 3 with
-// stored factors (N = 11, whose 178 registers leave 2: 53 -> 44 us at 3 M
-// points) and up to N = 5 (on the fly: 26.6 -> 23.2 us); the higher orders'
-// on-the-fly geometry would spill there (N = 9: 29 -> 44 us).
+// stored factors and up to N = 5 on the fly; the higher orders' on-the-fly
+// geometry would spill there (N = 9 plain: 29 -> 44 us).  The plain operator
+// at 2 and 3 waves, 3 M points: N = 11 stored 53, 44 us; N <= 5 on the fly 26.6,
+// 23.2.  The CG-fused one spills a little at 3 (N = 4 on the fly 10 registers,
+// N = 5 26, N = 11 stored 24) and gains or loses with the rounds that its
+// blocks take; us per iteration at 2 / 3 waves:
+//   N = 4  0.04 M points 14.2 / 14.7, 0.27 18.4 / 19.0, 0.86 33.9 / 31.1, 1.7
+//          47.1 / 47.0, 3.0 69.9 / 70.7, 8.0 159 / 164
+//   N = 5  0.05 M 15.0 / 15.6, 0.29 17.9 / 18.8, 0.88 32.4 / 31.5, 1.7 48.6 /
+//          48.3, 3.0 65.6 / 66.6, 7.8 148 / 150
+//   N = 11 0.05 M 21.2 / 22.0, 0.37 30.4 / 33.8, 0.88 40.7 / 43.4, 1.26 56.6 /
+//          51.1, 1.7 64.2 / 65.7, 3.0 95.5 / 92.3, 3.8 120.7 / 127.5, 8.5 255 / 258
+//   N = 10 1.8 M 56.3 / 50.3, elsewhere the same within 2% (stored, 2 spilled)
+// so the plain operator decides.
 template <typename T, bool OTF>
 constexpr int ax_min_waves() {
     if (sizeof(T) == 4) return kP <= 8 ? 4 : 1;
