@@ -8,9 +8,9 @@ namespace sem {
 
 #define SEM_DECL_ORDER(N)                                                                       \
     void ax_order_##N##_f32(bool, AxMode, const AxArgs<float> &, const double *, const double *, \
-                            const double *, int64_t, hipStream_t);                              \
+                            int64_t, hipStream_t);                                              \
     void ax_order_##N##_f64(bool, AxMode, const AxArgs<double> &, const double *,               \
-                            const double *, const double *, int64_t, hipStream_t);
+                            const double *, int64_t, hipStream_t);
 SEM_DECL_ORDER(1)
 SEM_DECL_ORDER(2)
 SEM_DECL_ORDER(3)
@@ -25,9 +25,8 @@ SEM_DECL_ORDER(11)
 #undef SEM_DECL_ORDER
 
 #define SEM_DECL_BATCH(N)                                                                      \
-    void ax_batch_order_##N##_f32(bool, bool, bool, bool, const AxArgs<float> *, const int2 *,       \
-                                  int64_t, int, const double *, const double *, const double *, \
-                                  hipStream_t);
+    void ax_batch_order_##N##_f32(bool, bool, bool, bool, const AxArgs<float> *, const int2 *, \
+                                  int64_t, int, const double *, const double *, hipStream_t);
 SEM_DECL_BATCH(1)
 SEM_DECL_BATCH(2)
 SEM_DECL_BATCH(3)
@@ -42,16 +41,16 @@ SEM_DECL_BATCH(11)
 #undef SEM_DECL_BATCH
 
 using FnB = void (*)(bool, bool, bool, bool, const AxArgs<float> *, const int2 *, int64_t, int,
-                     const double *, const double *, const double *, hipStream_t);
+                     const double *, const double *, hipStream_t);
 static const FnB kFnB[kMaxOrder + 1] = {
     nullptr,           ax_batch_order_1_f32, ax_batch_order_2_f32, ax_batch_order_3_f32,
     ax_batch_order_4_f32, ax_batch_order_5_f32, ax_batch_order_6_f32, ax_batch_order_7_f32,
     ax_batch_order_8_f32, ax_batch_order_9_f32, ax_batch_order_10_f32, ax_batch_order_11_f32};
 
 using Fn32 = void (*)(bool, AxMode, const AxArgs<float> &, const double *, const double *,
-                      const double *, int64_t, hipStream_t);
+                      int64_t, hipStream_t);
 using Fn64 = void (*)(bool, AxMode, const AxArgs<double> &, const double *, const double *,
-                      const double *, int64_t, hipStream_t);
+                      int64_t, hipStream_t);
 
 // The CG-fused operator writes one FP64 partial per block; its grid is
 // capped so that the partial sum stays short (tiles are then strided).
@@ -199,7 +198,7 @@ void launch_ax<float>(const Mesh &m, bool otf, AxMode mode, AxArgs<float> a, hip
     a.edge = m.edge32;
     if (!otf) a.G = m.G32;
     const int64_t ntiles = (m.E + sh.epb - 1) / sh.epb;
-    kFn32[m.N](otf, mode, a, m.h_D.data(), m.h_xi.data(), m.h_w.data(),
+    kFn32[m.N](otf, mode, a, m.h_xi.data(), m.h_w.data(),
                ax_grid(ntiles, mode, false, sh.mfma, sh.threads), s);
     check_hip(hipGetLastError(), "ax kernel launch (fp32)");
 }
@@ -218,7 +217,7 @@ void launch_ax<double>(const Mesh &m, bool otf, AxMode mode, AxArgs<double> a, h
     a.edge = nullptr;
     if (!otf) a.G = m.G64;
     const int64_t ntiles = (m.E + sh.epb - 1) / sh.epb;
-    kFn64[m.N](otf, mode, a, m.h_D.data(), m.h_xi.data(), m.h_w.data(),
+    kFn64[m.N](otf, mode, a, m.h_xi.data(), m.h_w.data(),
                ax_grid(ntiles, mode, true, false), s);
     check_hip(hipGetLastError(), "ax kernel launch (fp64)");
 }
@@ -239,11 +238,10 @@ void ax_batch_desc(const Mesh &m, bool otf, AxArgs<float> &a) {
 }
 
 void launch_ax_batch(int N, bool otf, bool mfma, bool stream, bool rho, const AxArgs<float> *descs,
-                     const int2 *blk, int64_t nblk, int epb, const double *D, const double *xi,
-                     const double *w,
+                     const int2 *blk, int64_t nblk, int epb, const double *xi, const double *w,
                      hipStream_t s) {
     if (nblk <= 0) return;
-    kFnB[N](otf, mfma, stream, rho, descs, blk, nblk, epb, D, xi, w, s);
+    kFnB[N](otf, mfma, stream, rho, descs, blk, nblk, epb, xi, w, s);
     check_hip(hipGetLastError(), "batched ax kernel launch");
 }
 

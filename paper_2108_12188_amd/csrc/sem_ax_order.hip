@@ -24,8 +24,7 @@
 // one thread owns one (i, j) column of one element, one i-pencil and one
 // j-pencil.  Each direction is a P x P product with the lane's own vector:
 // the k direction in the column's registers, i and j on pencils exchanged
-// through LDS tiles; the D entries are wave-uniform (kernel-argument /
-// scalar registers).
+// through LDS tiles; the D entries are wave-uniform (scalar registers).
 #include "sem_geom_body.h"
 #include "sem_internal.h"
 #include "sem_reduce.h"
@@ -61,11 +60,10 @@ __device__ __forceinline__ T load_g(const T *p) {
 template <typename T>
 constexpr bool prefetch_g() { return sizeof(T) == 4 && kP <= 7; }
 
-// Kernel-argument copy of the basis: indexed only with compile-time
+// Kernel-argument copy of the points and weights: indexed only with compile-time
 // constants, so every access is a scalar load.
 template <typename T>
 struct BasisK {
-    T D[kP * kP];   // D[k*P + l] = l_l'(xi_k)
     T xi[kP];
     T w[kP];
 };
@@ -1249,9 +1247,8 @@ ax_batch_kernel(const AxArgs<T> *__restrict__ descs, const int2 *__restrict__ bl
 }
 
 template <typename T>
-BasisK<T> make_basis(const double *D, const double *xi, const double *w) {
+BasisK<T> make_basis(const double *xi, const double *w) {
     BasisK<T> b;
-    for (int q = 0; q < kP * kP; ++q) b.D[q] = (T)D[q];
     for (int q = 0; q < kP; ++q) {
         b.xi[q] = (T)xi[q];
         b.w[q] = (T)w[q];
@@ -1293,9 +1290,9 @@ void launch_fused(const AxArgs<T> &a, const BasisK<T> &bk, int64_t grid, hipStre
 #define SEM_CAT3(a, b, c) SEM_CAT3_(a, b, c)
 
 template <typename T>
-static void ax_entry(bool otf, AxMode mode, const AxArgs<T> &a, const double *D,
-                     const double *xi, const double *w, int64_t grid, hipStream_t s) {
-    const BasisK<T> bk = make_basis<T>(D, xi, w);
+static void ax_entry(bool otf, AxMode mode, const AxArgs<T> &a, const double *xi,
+                     const double *w, int64_t grid, hipStream_t s) {
+    const BasisK<T> bk = make_basis<T>(xi, w);
     const bool fused = mode == AxMode::CgFused;
     if (otf) {
         if (fused) launch_fused<T, true>(a, bk, grid, s);
@@ -1334,9 +1331,9 @@ static void ax_batch_launch(bool otf, bool mfma, const AxArgs<T> *descs, const i
 
 template <typename T>
 static void ax_batch_entry(bool otf, bool mfma, bool stream, bool rho, const AxArgs<T> *descs,
-                           const int2 *blk, int64_t nblk, int epb, const double *D,
-                           const double *xi, const double *w, hipStream_t s) {
-    const BasisK<T> bk = make_basis<T>(D, xi, w);
+                           const int2 *blk, int64_t nblk, int epb, const double *xi,
+                           const double *w, hipStream_t s) {
+    const BasisK<T> bk = make_basis<T>(xi, w);
     if (rho) {
         if (stream) ax_batch_launch<T, true, true>(otf, mfma, descs, blk, nblk, epb, bk, s);
         else ax_batch_launch<T, false, true>(otf, mfma, descs, blk, nblk, epb, bk, s);
@@ -1348,21 +1345,20 @@ static void ax_batch_entry(bool otf, bool mfma, bool stream, bool rho, const AxA
 
 void SEM_CAT3(ax_batch_order_, SEM_ORDER, _f32)(bool otf, bool mfma, bool stream, bool rho,
                                                  const AxArgs<float> *descs, const int2 *blk,
-                                                 int64_t nblk, int epb, const double *D,
-                                                 const double *xi, const double *w,
-                                                 hipStream_t s) {
-    ax_batch_entry<float>(otf, mfma, stream, rho, descs, blk, nblk, epb, D, xi, w, s);
+                                                 int64_t nblk, int epb, const double *xi,
+                                                 const double *w, hipStream_t s) {
+    ax_batch_entry<float>(otf, mfma, stream, rho, descs, blk, nblk, epb, xi, w, s);
 }
 
 void SEM_CAT3(ax_order_, SEM_ORDER, _f32)(bool otf, AxMode mode, const AxArgs<float> &a,
-                                           const double *D, const double *xi, const double *w,
-                                           int64_t grid, hipStream_t s) {
-    ax_entry<float>(otf, mode, a, D, xi, w, grid, s);
+                                           const double *xi, const double *w, int64_t grid,
+                                           hipStream_t s) {
+    ax_entry<float>(otf, mode, a, xi, w, grid, s);
 }
 void SEM_CAT3(ax_order_, SEM_ORDER, _f64)(bool otf, AxMode mode, const AxArgs<double> &a,
-                                           const double *D, const double *xi, const double *w,
-                                           int64_t grid, hipStream_t s) {
-    ax_entry<double>(otf, mode, a, D, xi, w, grid, s);
+                                           const double *xi, const double *w, int64_t grid,
+                                           hipStream_t s) {
+    ax_entry<double>(otf, mode, a, xi, w, grid, s);
 }
 
 }  // namespace sem

@@ -287,7 +287,7 @@ struct BatchImpl {
         const int f = otf ? 1 : 0;
         for (const auto &g : groups[f]) {
             launch_ax_batch(g.N, otf, g.mfma, stream_vectors, g.rho, d_ax[f], g.blk, g.nblk, g.epb,
-                            order_D[g.N].data(), order_xi[g.N].data(), order_w[g.N].data(), s);
+                            order_xi[g.N].data(), order_w[g.N].data(), s);
         }
         if (n_gs_blk > 0)
             hipLaunchKernelGGL(gs_batch_kernel, dim3((unsigned)n_gs_blk), dim3(gsb::kGsThreads), 0,
@@ -370,7 +370,7 @@ struct BatchImpl {
     }
 
     // per order: host basis copies (FP64) for the kernel-argument basis
-    std::map<int, std::vector<double>> order_D, order_xi, order_w;
+    std::map<int, std::vector<double>> order_xi, order_w;
 };
 
 namespace {
@@ -471,8 +471,7 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
             for (int64_t vb = 0; vb < af.vgrid; ++vb)
                 order_blk[f][{m.N, m.inline32}].push_back(make_int2(q, (int)vb));
         }
-        if (!order_D.count(m.N)) {
-            order_D[m.N] = m.h_D;
+        if (!order_xi.count(m.N)) {
             order_xi[m.N] = m.h_xi;
             order_w[m.N] = m.h_w;
         }

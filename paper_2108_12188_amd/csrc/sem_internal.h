@@ -498,8 +498,7 @@ void ax_batch_desc(const Mesh &m, bool otf, AxArgs<float> &a);
 // stream: p and x non-temporal (cg_streams_vectors of the batch's footprint)
 // rho: every problem's rho is formed first (AxArgs::st_out set in all of them)
 void launch_ax_batch(int N, bool otf, bool mfma, bool stream, bool rho, const AxArgs<float> *descs,
-                     const int2 *blk, int64_t nblk, int epb, const double *D, const double *xi,
-                     const double *w,
+                     const int2 *blk, int64_t nblk, int epb, const double *xi, const double *w,
                      hipStream_t s);
 
 // gather-scatter / mask / vector kernels (sem_gs.hip, sem_vec.hip)
