@@ -144,12 +144,14 @@ void ax_engine_set(int N, bool fp64, bool otf, int engine) {
 AxShape ax_shape(int N, bool fp64, bool otf, int epb_override) {
     const int P = N + 1, P2 = P * P, P3 = P2 * P;
     const size_t tsz = fp64 ? 8 : 4;
-    // default: the matrix cores where they are built (FP32, N = 7: the
-    // fused operator is 14% faster there than with VALU FMA)
     const int engine = g_engine[otf ? 1 : 0][fp64 ? 1 : 0][N].load();
     // built-in choice: the matrix cores wherever they measured faster than
-    // the best VALU tile (N = 7 in both G forms, N = 9 with G on the fly;
-    // at N = 9 with G read from HBM two VALU elements per block are ahead)
+    // the best VALU tile.  us per CG iteration at 0.9 to 1 / 3 (N = 9: 2.7) / 8 M
+    // points, matrix cores and VALU with one and two elements per block: N = 7
+    // on the fly 19.9 38.1 71.5, 23.0 40.7 83.5, 22.1 36.7 73.3; stored factors
+    // 21.0 44.7 95.2, 23.2 48.5 99.5, 23.5 44.3 96.0; N = 9 on the fly 24.6 41.0
+    // 79.1, 24.9 44.4 92.1, 24.9 45.6 86.7; stored 28.8 52.0 120.4, 28.8 51.4
+    // 107.2, 29.0 54.1 110.0: there the VALU with one element
     const bool mfma = engine == kAxEngineMfma ||
                       (engine == kAxEngineDefault && !(N == 9 && !otf));
     if (mfma && ax_mfma_available(N, fp64)) {
