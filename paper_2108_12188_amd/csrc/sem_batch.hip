@@ -234,7 +234,9 @@ struct BatchImpl {
     UpdBatchDesc *d_upd = nullptr;
     int2 *d_upd_blk = nullptr;
     int64_t n_upd_blk = 0;
-    GsumBatchDesc *d_gsum[2] = {nullptr, nullptr};   // [precomputed, on the fly]
+    // [precomputed, on the fly] of one allocation (upload_forms), as d_updg,
+    // d_upds and d_fin
+    GsumBatchDesc *d_gsum[2] = {nullptr, nullptr};
     int2 *d_gsum_blk = nullptr;
     int64_t n_gsum_blk = 0;
     // updates with gather, [precomputed, on the fly]; the block tables hold
@@ -251,10 +253,9 @@ struct BatchImpl {
     const CgState **d_stp = nullptr;                // every member's state
     StateRow *d_states = nullptr;
     StateRow *h_states = nullptr;                    // pinned
-    size_t cap_ax[2] = {0, 0}, cap_fin[2] = {0, 0}, cap_cls = 0, cap_gs = 0, cap_gs_blk = 0,
-           cap_upd = 0, cap_upd_blk = 0, cap_gsum[2] = {0, 0}, cap_gsum_blk = 0, cap_updg[2] = {0, 0},
-           cap_updg_blk = 0, cap_upds[2] = {0, 0}, cap_upds_blk = 0, cap_stp = 0, cap_states = 0,
-           cap_h_states = 0;
+    size_t cap_ax[2] = {0, 0}, cap_fin = 0, cap_cls = 0, cap_gs = 0, cap_gs_blk = 0, cap_upd = 0,
+           cap_upd_blk = 0, cap_gsum = 0, cap_gsum_blk = 0, cap_updg = 0, cap_updg_blk = 0,
+           cap_upds = 0, cap_upds_blk = 0, cap_stp = 0, cap_states = 0, cap_h_states = 0;
     hipStream_t stream = nullptr;
     hipEvent_t ev = nullptr;
     std::map<GraphKey, hipGraphExec_t> graphs;
@@ -268,8 +269,8 @@ struct BatchImpl {
             for (auto &kv : blk_tab[f])
                 if (kv.second.blk) (void)hipFree(kv.second.blk);
         void *ptrs[] = {d_ax[0],   d_ax[1], d_cls,      d_gs,   d_gs_blk,   d_upd,
-                        d_upd_blk, d_gsum[0], d_gsum[1], d_gsum_blk, d_updg[0], d_updg[1], d_updg_blk,
-                        d_upds[0], d_upds[1], d_upds_blk, d_fin[0], d_fin[1], d_stp, d_states};
+                        d_upd_blk, d_gsum[0], d_gsum_blk, d_updg[0], d_updg_blk,
+                        d_upds[0], d_upds_blk, d_fin[0], d_stp, d_states};
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
         if (h_states) (void)hipHostFree(h_states);
@@ -384,6 +385,17 @@ void ensure_cap(T *&ptr, size_t &cap, size_t need, size_t &bytes) {
     cap = 0;
     ptr = dalloc<T>(need, bytes);
     cap = std::max<size_t>(need, 1);
+}
+
+// Both G forms' tables in one allocation, the second behind the first, by one
+// copy: a server rebuilds whenever its member set changes.
+template <typename T>
+void upload_forms(T *(&d)[2], size_t &cap, std::vector<T> (&v)[2], size_t &bytes) {
+    const size_t first = v[0].size();
+    v[0].insert(v[0].end(), v[1].begin(), v[1].end());
+    ensure_cap(d[0], cap, v[0].size(), bytes);
+    upload_sync(d[0], v[0]);
+    d[1] = d[0] + first;
 }
 
 BatchImpl *batch_create(int count, const sem_mesh_t *handles) {
@@ -564,16 +576,10 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
     upload_sync(d_upd, upd);
     ensure_cap(d_stp, cap_stp, count, bytes);
     upload_sync(d_stp, stp);
-    for (int f = 0; f < 2; ++f) {
-        ensure_cap(d_gsum[f], cap_gsum[f], count, bytes);
-        upload_sync(d_gsum[f], gsumd[f]);
-        ensure_cap(d_updg[f], cap_updg[f], count, bytes);
-        upload_sync(d_updg[f], updg[f]);
-        ensure_cap(d_upds[f], cap_upds[f], count, bytes);
-        upload_sync(d_upds[f], upds[f]);
-        ensure_cap(d_fin[f], cap_fin[f], count, bytes);
-        upload_sync(d_fin[f], fin[f]);
-    }
+    upload_forms(d_gsum, cap_gsum, gsumd, bytes);
+    upload_forms(d_updg, cap_updg, updg, bytes);
+    upload_forms(d_upds, cap_upds, upds, bytes);
+    upload_forms(d_fin, cap_fin, fin, bytes);
     ensure_cap(d_states, cap_states, count, bytes);
     if (cap_h_states < (size_t)count) {
         if (h_states) (void)hipHostFree(h_states);
