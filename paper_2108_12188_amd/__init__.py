@@ -271,12 +271,19 @@ class Mesh:
         b = torch.empty(self.n, dtype=dt, device=f.device)
         _check(lib().sem_rhs(self.handle, prec, _dev_vec(f, self.n, "f"),
                              C.c_void_p(b.data_ptr()), _stream(stream)))
-        if prec == FP32 and stream is not None:
-            # the FP32 result may be used on the caller's own stream at once
-            cur, h = torch.cuda.current_stream(f.device), stream.cuda_stream
-            if cur.cuda_stream != h:
-                cur.wait_stream(torch.cuda.ExternalStream(h, device=f.device) if h
-                                else torch.cuda.default_stream(f.device))
+        if prec == FP32:
+            # the call returns before its launch: f's memory is not reused
+            # before it has run, wherever f was allocated, and the caller's own
+            # stream may use the result at once
+            cur = torch.cuda.current_stream(f.device)
+            run = stream if stream is not None else torch.cuda.current_stream()
+            if not isinstance(run, torch.cuda.Stream):
+                h = run.cuda_stream
+                run = torch.cuda.ExternalStream(h, device=f.device) if h else \
+                    torch.cuda.default_stream(f.device)
+            f.record_stream(run)
+            if cur.cuda_stream != run.cuda_stream:
+                cur.wait_stream(run)
         return b
 
     def cg_solve(self, b, x=None, prec: int | None = None, geom: int = PRECOMPUTED,
