@@ -277,7 +277,7 @@ struct Mesh {
     bool inline_scalars(bool fp64) const { return fp64 ? inline64 : inline32; }
     bool direct = false;
     int4 *elist = nullptr;         // [E][MS]
-    int4 *elist_hi = nullptr;      // [E][8]
+    int4 *elist_hi = nullptr;      // [E][8], behind elist in its allocation
     int32_t *egen = nullptr;
     int32_t *gsrc_direct = nullptr;   // [n]
     // Jacobi preconditioner (built on first use): 1 / diag(A) on the free
@@ -341,8 +341,10 @@ struct HostTables {
     std::vector<int32_t> gsrc_direct;   // gsrc with the edge slots of larger groups
 };
 // Fills the tables of the two-launch iteration where it applies; points: also
-// the per-point table, which a mesh with the table-free gather need not have.
-void build_direct_tables(int64_t E, int N, HostTables &t, bool points = true);
+// the per-point table, which a mesh with the table-free gather need not have;
+// keep_gsrc: t.gsrc stays valid beside it.
+void build_direct_tables(int64_t E, int N, HostTables &t, bool points = true,
+                         bool keep_gsrc = true);
 // Validates glob_id / dirichlet (fail() on error) and fills t.
 void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, HostTables &t);
 

@@ -40,7 +40,7 @@ void free_mesh_arrays(Mesh *m) {
     void *ptrs[] = {m->vert64,     m->vert32,  m->edge32,  m->G32,     m->G64,       m->B64,
                     m->mcode,      m->gs_idx,  m->gs_lb_order, m->gs_zero, m->dir_idx, m->gsrc,
                     m->wedge_idx,  m->basis_blob, m->scratch, m->state,   m->minv64,
-                    m->minv32,     m->erec,    m->pos_tab, m->ewedge_idx, m->elist, m->elist_hi,
+                    m->minv32,     m->erec,    m->pos_tab, m->ewedge_idx, m->elist,
                     m->egen,       m->gsrc_direct};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -155,7 +155,7 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
     m->gs_struct = t.gs_struct && !(flags & SEM_MESH_GATHER_TABLE);
     m->gs_struct_solo =
         m->gs_struct && ((flags & SEM_MESH_GATHER_TABLE_FREE) || n >= kTableFreeMinPoints);
-    build_direct_tables(E, N, t, !m->gs_struct_solo);
+    build_direct_tables(E, N, t, !m->gs_struct_solo, !m->gs_struct);
     m->direct = t.direct;
     if (m->gs_struct) {
         m->ecls = t.ecls;
@@ -189,8 +189,8 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
         if (table && m->direct) m->gsrc_direct = dev_alloc<int32_t>(*m, t.gsrc_direct.size());
         if (t.gsum_wedge) m->wedge_idx = dev_alloc<int32_t>(*m, t.wedge_idx.size());
         if (m->direct) {
-            m->elist = dev_alloc<int4>(*m, t.elist.size());
-            m->elist_hi = dev_alloc<int4>(*m, t.elist_hi.size());
+            m->elist = dev_alloc<int4>(*m, t.elist.size() + t.elist_hi.size());
+            m->elist_hi = m->elist + t.elist.size();
             m->egen = dev_alloc<int32_t>(*m, t.egen.size());   // null: none
         }
         if (m->gs_struct) {

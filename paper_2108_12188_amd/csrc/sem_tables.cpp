@@ -83,10 +83,9 @@ bool build_struct_tables(int64_t E, int N, const std::vector<uint8_t> &mcode,
     t.p3_shift = 31 + lg;
     t.p3_magic = (uint32_t)(((uint64_t)1 << t.p3_shift) / (uint64_t)P3 + 1);
     // interior points: unshared and free
-    for (int64_t l = 0; l < n; ++l) {
-        const uint32_t pe = t.pos_tab[l % P3];
-        if ((pe & 3) == 0 && mcode[l] != 1) return false;
-    }
+    for (int64_t e = 0; e < E; ++e)
+        for (int q = 0; q < P3; ++q)
+            if ((t.pos_tab[q] & 3) == 0 && mcode[e * P3 + q] != 1) return false;
     const auto fits32 = [](int64_t v) { return v >= INT32_MIN && v <= INT32_MAX; };
     t.erec.assign((size_t)E * NR, ElemRec{0, 0});
     // faces
@@ -122,10 +121,11 @@ bool build_struct_tables(int64_t E, int N, const std::vector<uint8_t> &mcode,
             t.erec[(size_t)e * NR + f] = rc;
         }
     // edge and corner nodes: codes, and their groups of two or more copies
-    for (int64_t l = 0; l < n; ++l) {
-        const uint32_t pe = t.pos_tab[l % P3];
-        if ((pe & 3) == 2) t.erec[(size_t)(l / P3) * NR + (pe >> 12)] = ElemRec{0, mcode[l]};
-    }
+    for (int64_t e = 0; e < E; ++e)
+        for (int q = 0; q < P3; ++q) {
+            const uint32_t pe = t.pos_tab[q];
+            if ((pe & 3) == 2) t.erec[(size_t)e * NR + (pe >> 12)] = ElemRec{0, mcode[e * P3 + q]};
+        }
     const int64_t G = (int64_t)cnt.size();
     auto edge_pos = [&](int64_t l) -> int64_t {
         const uint32_t pe = t.pos_tab[l % P3];
@@ -176,13 +176,14 @@ bool build_struct_tables(int64_t E, int N, const std::vector<uint8_t> &mcode,
     gs_classes_finish(ec);
     t.ecls = ec;
     // every local index: the division, and the decoded code against mcode
-    for (int64_t l = 0; l < n; ++l) {
-        const int64_t e = (int64_t)(((uint64_t)l * t.p3_magic) >> t.p3_shift);
-        if (e != l / P3) return false;
-        const uint32_t pe = t.pos_tab[l - e * P3];
-        const int code = (pe & 3) == 0 ? 1 : (t.erec[(size_t)e * NR + (pe >> 12)].hi & 255);
-        if (code != mcode[l]) return false;
-    }
+    for (int64_t e = 0; e < E; ++e)
+        for (int q = 0; q < P3; ++q) {
+            const int64_t l = e * P3 + q;
+            if ((int64_t)(((uint64_t)l * t.p3_magic) >> t.p3_shift) != e) return false;
+            const uint32_t pe = t.pos_tab[q];
+            const int code = (pe & 3) == 0 ? 1 : (t.erec[(size_t)e * NR + (pe >> 12)].hi & 255);
+            if (code != mcode[l]) return false;
+        }
     return true;
 }
 
@@ -364,11 +365,14 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     // order of the group-sum kernel's output); any other point holds its own
     // index.  One entry per point: the update loads 4 at once.
     bool ok = true;
-    for (int64_t l = 0; l < n && ok; ++l) {
-        if ((mcode[l] & kMultMask) <= 1) continue;
-        const int loc = (int)(l % P3), i = loc % P, j = (loc / P) % P, k = loc / (P * P);
-        if (!(i == 0 || i == N || j == 0 || j == N || k == 0 || k == N)) ok = false;
-    }
+    const uint8_t *code = mcode.data();
+    for (int64_t e = 0; e < E && ok; ++e)
+        for (int k = 0; k < P; ++k)
+            for (int j = 0; j < P; ++j)
+                for (int i = 0; i < P; ++i, ++code) {
+                    const bool inside = i > 0 && i < N && j > 0 && j < N && k > 0 && k < N;
+                    if (inside && (*code & kMultMask) > 1) ok = false;
+                }
     t.gsrc.clear();
     if (ok) {
         t.gsrc.resize((size_t)n);
@@ -411,7 +415,7 @@ void build_tables(int64_t E, int N, const int64_t *gid, const uint8_t *dir, Host
     t.gs_struct = ok && build_struct_tables(E, N, mcode, plink, cnt, start, byid, t);
 }
 
-void build_direct_tables(int64_t E, int N, HostTables &t, bool points) {
+void build_direct_tables(int64_t E, int N, HostTables &t, bool points, bool keep_gsrc) {
     const int MS = edge_slots(N);
     const int64_t n = E * (N + 1) * (N + 1) * (N + 1);
     t.direct = false;
@@ -420,26 +424,30 @@ void build_direct_tables(int64_t E, int N, HostTables &t, bool points) {
     // every slot its own value, then the groups: of more than two copies
     // (the per-point table adds pairs by their partner's index), or with the
     // table-free gather every edge-node group off the Dirichlet boundary
-    t.elist.resize((size_t)(E * MS));
-    for (int64_t g = 0; g < E * MS; ++g) t.elist[(size_t)g] = make_int4((int)g, -1, -1, -1);
+    t.elist.clear();
+    t.elist.reserve((size_t)(E * MS));
+    for (int64_t g = 0; g < E * MS; ++g) t.elist.push_back(make_int4((int)g, -1, -1, -1));
     t.elist_hi.assign((size_t)(E * 8), make_int4(-1, -1, -1, -1));
     t.egen.clear();
     const auto add_group = [&](const int32_t *pos, int M) {
+        const int4 lo = make_int4(pos[0], M > 1 ? pos[1] : -1, M > 2 ? pos[2] : -1,
+                                  M > 3 ? pos[3] : -1);
+        if (M <= 4) {
+            for (int q = 0; q < M; ++q) t.elist[(size_t)pos[q]] = lo;
+            return;
+        }
+        const int4 hi = make_int4(pos[4], M > 5 ? pos[5] : -1, M > 6 ? pos[6] : -1,
+                                  M > 7 ? pos[7] : -1);
         const int gen = (int)t.egen.size();
         for (int q = 0; q < M; ++q) {
-            const int64_t g = pos[q], e = g / MS;
-            const int cn = M > 4 ? corner_of_slot(N, (int)(g - e * MS)) : -1;
-            if (M > (cn >= 0 ? 8 : 4)) {
+            const int g = pos[q], e = g / MS, cn = corner_of_slot(N, g - e * MS);
+            if (cn < 0 || M > 8) {
                 if ((int)t.egen.size() == gen) t.egen.insert(t.egen.end(), pos, pos + M);
                 t.elist[(size_t)g] = make_int4(-2, gen, M, 0);
                 continue;
             }
-            t.elist[(size_t)g] = make_int4(pos[0], M > 1 ? pos[1] : -1, M > 2 ? pos[2] : -1,
-                                           M > 3 ? pos[3] : -1);
-            if (M > 4)
-                t.elist_hi[(size_t)(8 * e + cn)] =
-                    make_int4(pos[4], M > 5 ? pos[5] : -1, M > 6 ? pos[6] : -1,
-                              M > 7 ? pos[7] : -1);
+            t.elist[(size_t)g] = lo;
+            t.elist_hi[(size_t)(8 * e + cn)] = hi;
         }
     };
     if (t.gs_struct) {
@@ -449,7 +457,8 @@ void build_direct_tables(int64_t E, int N, HostTables &t, bool points) {
     }
     t.direct = true;
     if (t.gs_struct && !points) return;
-    t.gsrc_direct = t.gsrc;
+    if (keep_gsrc) t.gsrc_direct = t.gsrc;
+    else t.gsrc_direct = std::move(t.gsrc);
     for (int c = 0; c < t.gs.ncls; ++c) {
         const int M = t.gs.M[c];
         if (M <= 2) continue;
