@@ -342,9 +342,8 @@ sem_status sem_mesh_footprint(int64_t n_elem, int order_N, uint32_t flags, sem_p
 
 /*
  * Tile shape of the local-operator kernels: elements per workgroup for an
- * order, precision (SEM_FP32 / SEM_FP64) and geometric-factor form; one
- * thread per (i, j) column, so a workgroup has roundup64(epb (N+1)^2)
- * threads.  0 restores the built-in default; values are clamped to 512
+ * order, precision (SEM_FP32 / SEM_FP64) and geometric-factor form; (N+1)^2
+ * threads an element, so a workgroup has roundup64(epb (N+1)^2) threads.  0 restores the built-in default; values are clamped to 512
  * threads and 64 KiB of element values in LDS (lds_bytes adds the padding of
  * the tiles).  Process-wide, used by later launches (the
  * shape fixes the grouping of the FP64 partial sums, so solves that must
@@ -357,8 +356,8 @@ sem_status sem_ax_shape_get(int order_N, sem_precision prec, sem_geom geom, int 
 /*
  * Contraction engine of the local operator for an order, precision and
  * G form: SEM_AX_ENGINE_VALU runs the D contractions as FP32/FP64 FMAs
- * (one thread per (i, j) column, sem_ax_shape_set picks elements per
- * block); SEM_AX_ENGINE_MFMA runs them on the FP32 matrix cores (16-block
+ * (a thread per pencil of each direction, sem_ax_shape_set picks elements
+ * per block); SEM_AX_ENGINE_MFMA runs them on the FP32 matrix cores (16-block
  * 4x4x1 MFMA, one element per workgroup of 64 (N = 7) or 128 (N = 9)
  * threads; available for SEM_FP32 at N = 7 and N = 9, else
  * SEM_EUNSUPPORTED).  The two engines accumulate every

@@ -1195,8 +1195,9 @@ constexpr int kMfmaThreads = kP == 10 ? 128 : 64;
 // Waves per SIMD.  The fused N = 9 kernel is held to 3 by its LDS.  The plain
 // forms on the fly are bound by VALU issue, most of it the geometry (N = 9 with
 // 3 waves: the VALU busy 67% of the time, the matrix cores 26%), which one wave
-// more fills better: 8 M points, N = 9 41.5 us with 3 waves, 39.0 with 4 (with
-// 5, which spill, 75), N = 7 29.7 with 4, 28.0 with 5 (with 6 32.4).
+// more fills better: 8 M points, N = 9 36.1 us with 3 waves, 33.6 with 4, which
+// spill one register (5 spill many and take 1.8 times as long as 3), N = 7 27.0
+// with 4, 25.3 with 5 (6 take 9% longer than 4).
 template <bool FUSED>
 constexpr int mfma_waves() {
     if (FUSED) return kP == 10 ? 3 : 4;

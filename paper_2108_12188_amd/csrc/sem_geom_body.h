@@ -50,7 +50,7 @@ struct ColumnGeom {
 // column geometry uses them: along xi (v1 - v0, v3 - v2, v5 - v4, v7 - v6),
 // along eta (v2 - v0, v3 - v1, v6 - v4, v7 - v5), along gamma (v4 - v0,
 // v5 - v1, v6 - v2, v7 - v3); ed[t * 3 + d].  The host builds the same
-// FP32 array per element (Mesh::vedge32) with the same subtractions.
+// FP32 array per element (Mesh::edge32) with the same subtractions.
 template <typename T, typename VertPtr>
 __device__ __forceinline__ void element_edges(VertPtr ve, T (&ed)[36]) {
     constexpr int kA[12] = {1, 3, 5, 7, 2, 3, 6, 7, 4, 5, 6, 7};
