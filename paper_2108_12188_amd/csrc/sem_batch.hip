@@ -448,9 +448,11 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
     int64_t footprint = 0;
     for (int q = 0; q < count; ++q) footprint += cg_footprint(*ms[q], 4, ms[q]->gs_struct);
     // two-launch iterations while they pay for all members together (the same
-    // sums in the same order as with three launches)
+    // sums in the same order as with three launches): each member counts by its
+    // share of its order's limit
     int64_t npts = 0;
-    for (int q = 0; q < count; ++q) npts += ms[q]->n;
+    for (int q = 0; q < count; ++q)
+        npts += ms[q]->n * (kDirectMaxPoints / direct_max_points(ms[q]->N));
     const bool two = npts <= kDirectMaxPoints;
     const int stream = cg_streams_vectors(footprint) ? 1 : 0;
     stream_vectors = stream != 0;

@@ -19,11 +19,10 @@ constexpr uint8_t kDirichletBit = 0x80;
 constexpr uint8_t kMultMask = 0x7F;
 constexpr int kMaxP = kMaxOrder + 1;
 // Schedules of a CG iteration on a conforming mesh (see DirectArgs): up to
-// kDirectMaxPoints local points two launches, up to kInlineMaxPoints (FP64:
+// direct_max_points(N) local points two launches, up to kInlineMaxPoints (FP64:
 // half of it; FP32 without matrix cores: three quarters) three, beyond it four.
 // On the fly, us per iteration with four launches and with the schedule taken
-// here: FP32 N = 7 0.11 M points 15.3 / 12.3, 0.88 M 21.8 / 18.9 (two launches;
-// 1.7 M with two: 27.8 / 30.6, the group sums formed once per copy), 2.2 M
+// here: FP32 N = 7 0.11 M points 15.3 / 12.3, 0.88 M 21.8 / 18.9 (two), 2.2 M
 // 33.6 / 32.9, 3.0 M 38.6 / 37.3, 3.9 M 44.9 / 43.8 (three); N = 9 1.1 M 30.1 /
 // 28.4, 2.2 M 40.8 / 35.9, 3.8 M 52.4 / 46.2; FP64 N = 9 0.5 M 29.8 / 26.4, N = 8
 // 2 M 54.9 / 51.5, N = 9 2.0 M 57.0 / 57.5 (4.1 M 91.8 / 94.6).
@@ -36,7 +35,22 @@ constexpr int kMaxP = kMaxOrder + 1;
 // their loads (1.2 M 25.1 / 27.1, 1.5 M 26.4 / 27.8, 1.84 M 29.2 / 29.8, 1.97 M 30.1 /
 // 30.1, 2.1 M with 1024 blocks 30.0 / 29.2).  The rule knows the order, not the
 // engine, which can be set after the mesh is made.
+// Two launches form a group's sum once per copy, in every block that touches
+// it, so the limit falls where most of an element is edge and corner nodes
+// (all of it at N = 1, half at N = 3).  FP32 on the fly, us per iteration with
+// two / three launches: N = 1 0.15 M points 15.4 / 15.5, 0.29 M 19.1 / 17.0, 0.89 M
+// 33.1 / 26.5 (four 27.4); N = 2 0.15 M 15.3 / 15.4, 0.29 M 18.4 / 17.2, 0.89 M 28.6 /
+// 27.4; N = 3 0.39 M 17.4 / 17.9, 0.54 M 22.2 / 21.3, 1.0 M 27.8 / 26.2 (four 27.3);
+// N = 4 1.0 M 24.6 / 25.9; N = 5 1.0 M 25.7 / 26.3, 1.3 M 28.5 / 28.5, 1.9 M 35.8 / 33.5;
+// N = 7 0.96 M 20.0 / 23.2, 1.2 M 25.3 / 24.8 (four), 1.97 M 33.6 / 30.3; N = 8
+// 0.97 M 24.0 / 26.1, 1.26 M 28.6 / 29.8, 1.48 M 30.2 / 28.9; N = 9 1.0 M 24.2 / 25.8,
+// 1.2 M 27.4 / 28.8, 1.6 M 32.5 / 31.8.  FP64: N = 1 0.15 M 17.1 / 16.7, 0.89 M 41.5 /
+// 33.6 (four 36.1), N = 3 0.39 M 20.7 / 22.4, 0.54 M 26.0 / 25.3, N = 5 0.89 M 31.8 /
+// 33.0, 1.0 M 35.3 / 34.1, N = 9 1.0 M 33.2 / 34.6, 1.6 M 52.6 / 52.0.
 constexpr int64_t kDirectMaxPoints = int64_t(1) << 20;
+constexpr int64_t direct_max_points(int N) {
+    return N < 4 ? int64_t(1) << (16 + N) : kDirectMaxPoints;
+}
 constexpr int64_t kInlineMaxPoints = int64_t(1) << 22;
 constexpr bool mfma_order(int N) { return N == 7 || N == 9; }
 inline bool takes_inline_scalars(int N, int64_t n, bool fp64) {
@@ -264,7 +278,7 @@ struct Mesh {
     int32_t *ewedge_idx = nullptr;
     uint32_t p3_magic = 0;
     int p3_shift = 0;
-    // Two-launch CG iterations (n <= kDirectMaxPoints, every group of more
+    // Two-launch CG iterations (n <= direct_max_points(N), every group of more
     // than two copies made of edge and corner nodes): the update sums those
     // groups itself from the operator's compact edge array.  elist[e * MS +
     // s] (MS = edge_slots(N)): the positions in that array of the copies of

@@ -78,7 +78,7 @@ size_t mesh_footprint(int64_t E, int N, uint32_t flags, sem_precision prec) {
         const size_t ms = (size_t)edge_slots(N);
         b += (size_t)E * (6 + ms) * 8 + ((size_t)E * ms + 8 * kMaxGsClasses) * 4 + P3 * 4;
     }
-    if (n <= (size_t)kDirectMaxPoints)             // two-launch iteration: edge lists
+    if (n <= (size_t)direct_max_points(N))             // two-launch iteration: edge lists
         b += (size_t)E * ((edge_slots(N) + 8) * 16 + edge_slots(N) * 4) + n * 4;
     if (flags & SEM_MESH_G_FP32) b += n * 24;
     if (flags & SEM_MESH_G_FP64) b += n * 48;
@@ -87,7 +87,7 @@ size_t mesh_footprint(int64_t E, int N, uint32_t flags, sem_precision prec) {
     // copies), reduction partials
     const size_t we = (size_t)E * edge_slots(N);      // compact edge array
     size_t nvec = (size_t)vec_blocks((int64_t)n);
-    if (n <= (size_t)kDirectMaxPoints)
+    if (n <= (size_t)direct_max_points(N))
         nvec = std::max(nvec, n / (4 * (size_t)step_packs(N)) + 1);
     const size_t ws32 = n * 4 * 5 + n / 3 * 4 + we * 4 + (size_t)E * 8 + nvec * 8 + 1024;
     const size_t ws64 = n * 8 * 5 + n / 3 * 8 + we * 8 + (size_t)E * 8 + nvec * 8 + 1024;

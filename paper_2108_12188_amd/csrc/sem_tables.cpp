@@ -419,7 +419,7 @@ void build_direct_tables(int64_t E, int N, HostTables &t, bool points, bool keep
     const int MS = edge_slots(N);
     const int64_t n = E * (N + 1) * (N + 1) * (N + 1);
     t.direct = false;
-    if (!t.gs_in_update || n > kDirectMaxPoints) return;
+    if (!t.gs_in_update || n > direct_max_points(N)) return;
     if (t.n_groups_multi > 0 && !t.gsum_wedge) return;
     // every slot its own value, then the groups: of more than two copies
     // (the per-point table adds pairs by their partner's index), or with the

@@ -13,7 +13,7 @@ int main(int argc, char **argv) {
     const bool fp64 = std::atoi(argv[2]) != 0;
     for (int q = 3; q < argc; ++q) {
         const int64_t n = std::atoll(argv[q]);
-        const int launches = n <= sem::kDirectMaxPoints                ? 2
+        const int launches = n <= sem::direct_max_points(N)            ? 2
                              : sem::takes_inline_scalars(N, n, fp64) ? 3
                                                                      : 4;
         const int vec = (int)((n + 1023) / 1024);      // vec_blocks up to 4096 of them

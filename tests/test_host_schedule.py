@@ -49,7 +49,9 @@ def test_update_blocks_of_three_launches(checker, N, fp64):
 
 # last and first size of each schedule, as measured
 @pytest.mark.parametrize("N,fp64,n,launches", [
-    (5, False, 1 << 20, 2), (5, False, (1 << 20) + 216, 3), (5, False, 3 << 20, 3),
+    (1, False, 1 << 17, 2), (1, True, (1 << 17) + 8, 3), (2, False, 1 << 18, 2),
+    (2, False, (1 << 18) + 27, 3), (3, True, 1 << 19, 2), (3, False, (1 << 19) + 64, 3),
+    (4, False, 1 << 20, 2), (5, False, 1 << 20, 2), (5, False, (1 << 20) + 216, 3), (5, False, 3 << 20, 3),
     (5, False, (3 << 20) + 216, 4), (8, False, 3582 * 1000, 4), (6, False, 3177 * 1000, 4),
     (9, False, 1 << 22, 3), (9, False, (1 << 22) + 1000, 4), (7, False, (1 << 20) + 512, 4),
     (7, False, (1 << 21) - 512, 4), (7, False, 1 << 21, 3), (7, False, 1 << 22, 3),
