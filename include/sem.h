@@ -345,7 +345,8 @@ sem_status sem_mesh_footprint(int64_t n_elem, int order_N, uint32_t flags, sem_p
  * order, precision (SEM_FP32 / SEM_FP64) and geometric-factor form; (N+1)^2
  * threads an element, so a workgroup has roundup64(epb (N+1)^2) threads.  0 restores the built-in default; values are clamped to 512
  * threads and 64 KiB of element values in LDS (lds_bytes adds the padding of
- * the tiles).  Process-wide, used by later launches (the
+ * the tiles); the stand-alone operator has another default at N = 2 on the
+ * fly and at N = 3 and 6 in FP64 with stored factors.  Process-wide, used by later launches (the
  * shape fixes the grouping of the FP64 partial sums, so solves that must
  * agree bitwise need the same shapes).  For the autotuner.
  */

@@ -111,6 +111,17 @@ static const Fn64 kFn64[kMaxOrder + 1] = {nullptr,        ax_order_1_f64, ax_ord
 static const int kEpb32[kMaxOrder + 1] = {0, 64, 28, 16, 5, 7, 5, 4, 3, 1, 1, 1};
 static const int kEpb64[kMaxOrder + 1] = {0, 64, 28, 16, 5, 7, 5, 1, 3, 1, 1, 1};
 
+// The plain operator where another number than the CG-fused one's measured
+// faster (us at 1.6, 3.4 and 8 M points): N = 2 on the fly, FP64 28 elements 14.1,
+// 25.5, 53.4, 7 (one wave) 12.8, 22.7, 47.2, FP32 8.8, 14.7, 29.7 and 9.0, 14.7, 29.6;
+// FP64 with stored factors, N = 3 16 elements 15.3, 31.6, 94.5, 20 15.2, 30.7, 91.2;
+// N = 6 5 elements 19.8, 36.0, 95.9, 1 19.7, 34.1, 94.3 (the fused one keeps 5: 8 M
+// points 219 us an iteration, with 1 229).
+static int plain_epb(int N, bool fp64, bool otf) {
+    if (otf) return N == 2 ? 7 : 0;
+    return !fp64 ? 0 : N == 3 ? 20 : N == 6 ? 1 : 0;
+}
+
 // Process-wide tile shapes set by the autotuner (0: built-in default),
 // indexed [on-the-fly][fp64][N], and a generation counter that tells cached
 // graphs and batch tables that a shape changed.
@@ -186,9 +197,16 @@ AxShape ax_shape(int N, bool fp64, bool otf, int epb_override) {
     return s;
 }
 
+// The shape of a launch: the caller's, else the autotuner's, else the default.
+static AxShape launch_shape(int N, bool fp64, bool otf, AxMode mode, int epb) {
+    if (mode != AxMode::CgFused && epb <= 0 && g_epb[otf ? 1 : 0][fp64 ? 1 : 0][N].load() <= 0)
+        epb = plain_epb(N, fp64, otf);
+    return ax_shape(N, fp64, otf, epb);
+}
+
 template <>
 void launch_ax<float>(const Mesh &m, bool otf, AxMode mode, AxArgs<float> a, hipStream_t s) {
-    const AxShape sh = ax_shape(m.N, false, otf, a.epb);
+    const AxShape sh = launch_shape(m.N, false, otf, mode, a.epb);
     a.epb = sh.epb;
     a.mfma = sh.mfma ? 1 : 0;
     a.E = m.E;
@@ -207,7 +225,7 @@ void launch_ax<float>(const Mesh &m, bool otf, AxMode mode, AxArgs<float> a, hip
 
 template <>
 void launch_ax<double>(const Mesh &m, bool otf, AxMode mode, AxArgs<double> a, hipStream_t s) {
-    const AxShape sh = ax_shape(m.N, true, otf, a.epb);
+    const AxShape sh = launch_shape(m.N, true, otf, mode, a.epb);
     a.epb = sh.epb;
     a.mfma = 0;
     a.E = m.E;

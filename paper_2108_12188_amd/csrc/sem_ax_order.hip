@@ -54,11 +54,17 @@ __device__ __forceinline__ T load_g(const T *p) {
 }
 
 // Precomputed form: the loads of all 6 P factors of a column go out before
-// the gradient where the registers allow it (FP32, N <= 6, 3 M points, plain
-// operator: N = 5 22.6 -> 20.0 us, N = 6 24.6 -> 22.1 us; N = 8 22.2 us
-// either way, and FP64 runs at the copy rate without it).
-template <typename T>
-constexpr bool prefetch_g() { return sizeof(T) == 4 && kP <= 7; }
+// the gradient where the registers allow it.  FP32, N <= 6, 3 M points, plain
+// operator: N = 5 22.6 -> 20.0 us, N = 6 24.6 -> 22.1.  The plain operator has
+// registers for it at FP32 N = 8 (3.4 M points 25.2 -> 21.8 us, 7.8 M 52.4 -> 45.8;
+// 23.8 and 48.7 when a column read its lines itself) and FP64 N = 4 (1.6 M
+// 17.8 -> 17.2, 3.4 M 32.2 -> 31.5) and 5 (19.2 -> 17.7, 32.7 -> 31.8); below that
+// FP64 gains nothing, N = 6 spills.
+template <typename T, bool FUSED>
+constexpr bool prefetch_g() {
+    if (FUSED) return sizeof(T) == 4 && kP <= 7;
+    return sizeof(T) == 4 ? kP <= 9 : kP == 5 || kP == 6;
+}
 
 // Kernel-argument copy of the points and weights: indexed only with compile-time
 // constants, so every access is a scalar load.
@@ -518,6 +524,17 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
 #pragma unroll
                 for (int k = 0; k < P; ++k) uc[k] = a.u[base + k * P2];
             }
+        }
+        // at the lowest orders an element's vertices are as many bytes as its
+        // values: their loads go out with u's (3.4 M points plain: FP32 N = 1
+        // 17.2 -> 15.5 us, FP64 N = 2 28.8 -> 25.5; the CG-fused form gains
+        // nothing)
+        constexpr bool kGeomFirst = OTF && !FUSED && kP <= 3;
+        ColumnGeom<T> cg;
+        if constexpr (kGeomFirst) {
+            if (valid) cg = column_geom<T>(a.vert + e * 24, xi_i, eta_j, wij);
+        }
+        if (valid) {
 #pragma unroll
             for (int k = 0; k < P; ++k) sa[k * kSlab + col] = uc[k];
         }
@@ -527,7 +544,7 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
         else elem_sync();
 
         // the column's factors, in flight during the gradient
-        constexpr bool kPre = !OTF && prefetch_g<T>();
+        constexpr bool kPre = !OTF && prefetch_g<T, FUSED>();
         T gq[kPre ? 6 : 1][kPre ? P : 1];
         if constexpr (kPre) {
             if (valid) {
@@ -562,8 +579,7 @@ __device__ __forceinline__ void ax_body(const AxArgs<T> &a, const BasisK<T> &bk,
         // G pointwise, back in the column layout; each thread rewrites only
         // its own column's slots, in place
         if (valid) {
-            ColumnGeom<T> cg;
-            if constexpr (OTF) {
+            if constexpr (OTF && !kGeomFirst) {
                 if constexpr (kDma)
                     cg = column_geom<T>(reinterpret_cast<const T *>(sV) + el * 24, xi_i, eta_j,
                                         wij);
