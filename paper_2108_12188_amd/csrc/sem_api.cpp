@@ -257,6 +257,19 @@ sem_status sem_coords(sem_mesh_t mesh, double *xyz_dev, void *hip_stream) {
     });
 }
 
+// Points up to which the FP64 right-hand side is one launch.  It gathers two
+// vectors where the sums over a stored product gather one, so it loses once they
+// outgrow the caches, earlier where more of an element is shared; us in one /
+// two launches: N = 1 2.2 M points 24.5 / 30.4, 4.0 M 41.7 / 42.9, 8 M 80.8 / 79.1;
+// N = 2 1.2 M 20.2 / 20.7, 1.6 M 24.8 / 23.3, 3.4 M 62.2 / 40.4, 8 M 159 / 84; N = 3
+// 1.6 M 20.8 / 21.5, 2.2 M 30.6 / 26.5, 8 M 114 / 68; N = 4 1.6 M 20.6 / 21.2, 1.9 M
+// 25.1 / 23.1; N = 5 1.8 M 20.3 / 23.1, 2.2 M 26.7 / 25.8, 8 M 95.1 / 67.3; N = 7 2.1 M
+// 22.3 / 25.1, 3.0 M 30.9 / 27.7, 8 M 77.8 / 62.3; N = 9 2.2 M 23.0 / 22.9, 8 M 79.9 /
+// 61.6.
+static int64_t rhs_one_launch_points(int N) {
+    return N == 1 ? int64_t(1) << 22 : N < 5 ? int64_t(3) << 19 : int64_t(1) << 21;
+}
+
 sem_status sem_rhs(sem_mesh_t mesh, sem_precision prec, const double *f_dev, void *b_dev,
                    void *hip_stream) {
     return guarded([&]() -> sem_status {
@@ -269,7 +282,8 @@ sem_status sem_rhs(sem_mesh_t mesh, sem_precision prec, const double *f_dev, voi
         hipStream_t s = static_cast<hipStream_t>(hip_stream);
         // N = 7, 2.1 M points, FP32: product, sums, mask and conversion as
         // passes over a temporary 34 us, one launch that reads f at every
-        // copy 21.  Over its own input the product goes to memory first.
+        // copy 21.  Over its own input, and in FP64 on larger meshes, the
+        // product goes to memory first.
         const uintptr_t f0 = (uintptr_t)f_dev, b0 = (uintptr_t)b_dev;
         const uintptr_t f_len = sizeof(double) * (size_t)m->n;
         const uintptr_t b_len = prec == SEM_FP32 ? f_len / 2 : f_len;
@@ -289,7 +303,7 @@ sem_status sem_rhs(sem_mesh_t mesh, sem_precision prec, const double *f_dev, voi
             check_hip(e, "rhs");
         } else {
             double *b = static_cast<double *>(b_dev);
-            if (!overlap) {
+            if (!overlap && m->n <= rhs_one_launch_points(m->N)) {
                 launch_rhs<double>(*m, f_dev, b, s);
                 return SEM_OK;
             }
