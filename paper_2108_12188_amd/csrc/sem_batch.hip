@@ -471,10 +471,10 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
             a.x = static_cast<float *>(ws.x);
             a.wedge = (m.gsum_wedge || m.gs_struct || m.direct) ? static_cast<float *>(ws.wedge)
                                                                  : nullptr;
-            if (m.inline32) {
+            if (m.inline32[0]) {
                 a.st_out = ws.step;
                 a.rho_part = ws.part_vec;
-                a.n_rho = update_blocks(m, false);
+                a.n_rho = update_blocks(m, false, false);
             }
             ax[otf].push_back(a);
         }
@@ -483,7 +483,7 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
             order_epb[f][m.N] = af.epb;
             order_mfma[f][m.N] = af.mfma != 0;
             for (int64_t vb = 0; vb < af.vgrid; ++vb)
-                order_blk[f][{m.N, m.inline32}].push_back(make_int2(q, (int)vb));
+                order_blk[f][{m.N, m.inline32[0]}].push_back(make_int2(q, (int)vb));
         }
         if (!order_xi.count(m.N)) {
             order_xi[m.N] = m.h_xi;
@@ -491,14 +491,14 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
         }
         cls.push_back(m.gs_struct ? m.ecls : m.gs);
         const int64_t nlb = m.n_groups > 0 ? gs_logical_blocks(m) : 0;
-        const int nv = update_blocks(m, false);
+        const int nv = update_blocks(m, false, false);
         const bool direct = two && m.direct;
         const int packs = m.direct ? step_packs(m.N) : vecb::kVecThreads;
         // the single-mesh schedule of each problem: the same logical and
         // virtual blocks
         const bool compact = m.gsum_wedge;
         const float *const wedge = static_cast<const float *>(ws.wedge);
-        const CgStep *const step = m.inline32 ? ws.step : nullptr;
+        const CgStep *const step = m.inline32[0] ? ws.step : nullptr;
         DirectArgs<float> dir[2] = {};
         if (direct)
             for (int f = 0; f < 2; ++f)
@@ -555,7 +555,7 @@ void BatchImpl::rebuild(const std::vector<Mesh *> &ms) {
                 upd_blk.push_back(make_int2((int)upd.size() - 1, vb));
         }
         for (int f = 0; f < 2; ++f)
-            (m.inline32 ? fin_direct[f] : fin[f])
+            (m.inline32[0] ? fin_direct[f] : fin[f])
                 .push_back({ws.st, ws.part_ax, ax[f].back().vgrid, ws.part_vec, nv,
                             ax_threads(m.N, false, f != 0)});
         stp.push_back(ws.st);

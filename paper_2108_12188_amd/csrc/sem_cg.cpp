@@ -89,7 +89,8 @@ Workspace *ws_create(const Mesh &m, bool fp64) {
             ws->wedge = ws_alloc<char>(*ws, (size_t)m.E * edge_slots(m.N) * tsz);
         // the smallest shape (1 element per block) bounds the Ax partial count
         ws->cap_ax = m.E;
-        ws->cap_vec = std::max(vec_blocks(m.n), update_blocks(m, fp64));
+        ws->cap_vec = std::max({vec_blocks(m.n), update_blocks(m, fp64, false),
+                                update_blocks(m, fp64, true)});
         ws->part_ax = ws_alloc<double>(*ws, ws->cap_ax);
         ws->part_vec = ws_alloc<double>(*ws, ws->cap_vec);
         ws->st = ws_alloc<CgState>(*ws, 1);
@@ -199,12 +200,12 @@ void enqueue_iteration(const Mesh &m, Workspace &ws, bool otf, bool pc, hipStrea
     a.partial = ws.part_ax;
     a.wedge = (m.gsum_wedge || m.gs_struct_solo || m.direct) ? wedge : nullptr;
     a.x = x;
-    const CgStep *const step = m.inline_scalars(sizeof(T) == 8) ? ws.step : nullptr;
+    const CgStep *const step = m.inline_scalars(sizeof(T) == 8, pc) ? ws.step : nullptr;
     if (step) {
         a.st_out = ws.step;
         a.rho_part = ws.part_vec;
         a.rr_part = pa.partial2;
-        a.n_rho = update_blocks(m, sizeof(T) == 8);
+        a.n_rho = update_blocks(m, sizeof(T) == 8, pc);
     }
     a.stream = ((sizeof(T) == 4 || otf) &&
                 cg_streams_vectors(cg_footprint(m, (int)sizeof(T), m.gs_struct_solo)))
@@ -236,9 +237,9 @@ void enqueue_iteration(const Mesh &m, Workspace &ws, bool otf, bool pc, hipStrea
 // After the last of a run of iterations: the state as the host reads it.
 template <typename T>
 void enqueue_close(const Mesh &m, Workspace &ws, bool otf, bool pc, hipStream_t s) {
-    if (!m.inline_scalars(sizeof(T) == 8)) return;
-    launch_close_rho(ws.st, ws.part_vec, pc ? ws.part_vec2 : nullptr, update_blocks(m, sizeof(T) == 8),
-                     ax_threads(m.N, sizeof(T) == 8, otf), s);
+    if (!m.inline_scalars(sizeof(T) == 8, pc)) return;
+    launch_close_rho(ws.st, ws.part_vec, pc ? ws.part_vec2 : nullptr,
+                     update_blocks(m, sizeof(T) == 8, pc), ax_threads(m.N, sizeof(T) == 8, otf), s);
 }
 
 struct KernelTimes {

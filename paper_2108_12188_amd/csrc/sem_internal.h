@@ -34,7 +34,13 @@ constexpr int kMaxP = kMaxOrder + 1;
 // its update that divide evenly leave 600 to 950 blocks, too few to hide
 // their loads (1.2 M 25.1 / 27.1, 1.5 M 26.4 / 27.8, 1.84 M 29.2 / 29.8, 1.97 M 30.1 /
 // 30.1, 2.1 M with 1024 blocks 30.0 / 29.2).  The rule knows the order, not the
-// engine, which can be set after the mesh is made.
+// engine, which can be set after the mesh is made.  N = 3 in FP32 and N = 1 in
+// FP64, whose steps hold many small tiles, keep four beyond 2^20 points (N = 3
+// 1.3 M 29.6 / 30.3, 2.8 M 46.4 / 49.1; N = 1 2.0 M 57.0 / 59.1).
+// With a preconditioner every block sums twice the partials: three launches
+// stop paying at 2^21 points at N = 5 (2.0 M 42.7 / 42.5, 2.9 M 53.3 / 55.5) and do
+// not begin to at N = 7 (2.1 M 35.9 / 35.8, 2.5 M 41.7 / 42.5, 3.7 M 52.5 / 53.9); at
+// the other orders they pay as far as without (N = 9 3.6 M 57.8 / 52.7).
 // Two launches form a group's sum once per copy, in every block that touches
 // it, so the limit falls where most of an element is edge and corner nodes
 // (all of it at N = 1, half at N = 3).  FP32 on the fly, us per iteration with
@@ -53,9 +59,11 @@ constexpr int64_t direct_max_points(int N) {
 }
 constexpr int64_t kInlineMaxPoints = int64_t(1) << 22;
 constexpr bool mfma_order(int N) { return N == 7 || N == 9; }
-inline bool takes_inline_scalars(int N, int64_t n, bool fp64) {
+inline bool takes_inline_scalars(int N, int64_t n, bool fp64, bool pc) {
     if (n <= kDirectMaxPoints) return true;
+    if (N == (fp64 ? 1 : 3)) return false;
     if (fp64) return n <= kInlineMaxPoints / 2;
+    if (pc && (N == 5 || N == 7)) return N == 5 && n <= kInlineMaxPoints / 2;
     if (!mfma_order(N)) return n <= kInlineMaxPoints / 4 * 3;
     return n <= kInlineMaxPoints && (N != 7 || n >= kInlineMaxPoints / 2);
 }
@@ -287,8 +295,9 @@ struct Mesh {
     // corner_of_slot).  More copies than that: {-2, offset into egen, count,
     // 0}.  gsrc_direct is gsrc with e * MS + s for the points of groups of
     // more than two copies.
-    bool inline32 = false, inline64 = false;   // two or three launches, per precision
-    bool inline_scalars(bool fp64) const { return fp64 ? inline64 : inline32; }
+    // two or three launches, [preconditioned], per precision
+    bool inline32[2] = {false, false}, inline64[2] = {false, false};
+    bool inline_scalars(bool fp64, bool pc) const { return fp64 ? inline64[pc] : inline32[pc]; }
     bool direct = false;
     int4 *elist = nullptr;         // [E][MS]
     int4 *elist_hi = nullptr;      // [E][8], behind elist in its allocation
@@ -557,8 +566,8 @@ int64_t gs_logical_blocks(const Mesh &m);
 // partial per block (`partial`, at least vec_blocks(n) entries) and a
 // one-block finalize kernel sums them in index order.
 int vec_blocks(int64_t n);
-// blocks (and partials) of the CG update of a mesh
-int update_blocks(const Mesh &m, bool fp64);
+// blocks (and partials) of the CG update of a mesh; pc: preconditioned
+int update_blocks(const Mesh &m, bool fp64, bool pc);
 // r -= alpha mask(w); rho = <r, r, c>; then beta, convergence, history (x is
 // advanced by the next operator launch or launch_x_flush)
 template <typename T>

@@ -135,8 +135,10 @@ Mesh *mesh_create(int64_t E, int N, const double *vert, const int64_t *gid, cons
         t.gsum_wedge = false;
         t.gs_struct = false;
     }
-    m->inline32 = t.gs_in_update && takes_inline_scalars(N, n, false);
-    m->inline64 = t.gs_in_update && takes_inline_scalars(N, n, true);
+    for (int pc = 0; pc < 2; ++pc) {
+        m->inline32[pc] = t.gs_in_update && takes_inline_scalars(N, n, false, pc != 0);
+        m->inline64[pc] = t.gs_in_update && takes_inline_scalars(N, n, true, pc != 0);
+    }
     m->n_glob = t.n_glob;
     m->gs = t.gs;
     m->n_groups = t.n_groups;

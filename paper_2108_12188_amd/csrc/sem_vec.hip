@@ -252,10 +252,10 @@ int vec_blocks(int64_t n) {
     return (int)(b > 0 ? b : 1);
 }
 
-int update_blocks(const Mesh &m, bool fp64) {
+int update_blocks(const Mesh &m, bool fp64, bool pc) {
     if (m.direct) return (int)((m.n + 4 * step_packs(m.N) - 1) / (4 * step_packs(m.N)));
     const int b = vec_blocks(m.n);
-    return m.inline_scalars(fp64) ? inline_update_blocks(b, m.N, fp64) : b;
+    return m.inline_scalars(fp64, pc) ? inline_update_blocks(b, m.N, fp64) : b;
 }
 
 template <typename T>
@@ -294,14 +294,14 @@ void launch_update_gather(const Mesh &m, T *r, const T *w, const T *gsum, CgStat
         fail(SEM_EUNSUPPORTED, "mesh shares points inside elements: no gather in the update");
     if (!m.gsrc) fail(SEM_EUNSUPPORTED, "mesh holds no per-point gather table");
     const GatherMap gm{m.gsrc};
-    const int nb = update_blocks(m, sizeof(T) == 8);
+    const int nb = update_blocks(m, sizeof(T) == 8, pc.minv != nullptr);
     if (pc.minv)
         hipLaunchKernelGGL((update_gather_kernel<T, true>), dim3(nb), dim3(kVecThreads), 0, s,
                            m.n, r, w, gsum, m.mcode, gm, st, partial, pc);
     else
         hipLaunchKernelGGL((update_gather_kernel<T, false>), dim3(nb), dim3(kVecThreads), 0, s,
                            m.n, r, w, gsum, m.mcode, gm, st, partial, pc);
-    if (!m.inline_scalars(sizeof(T) == 8))
+    if (!m.inline_scalars(sizeof(T) == 8, pc.minv != nullptr))
         hipLaunchKernelGGL(finalize_rho_kernel, dim3(1), dim3(kFinalizeThreads), 0, s, st,
                        (const double *)partial, nb, (const double *)pc.partial2);
     check_hip(hipGetLastError(), "update kernel launch");
@@ -313,14 +313,14 @@ void launch_update_struct(const Mesh &m, T *r, const T *wg, CgState *st, double 
     if (!m.gs_struct) fail(SEM_EUNSUPPORTED, "mesh has no table-free gather");
     if (m.P3 > kMaxPosTab || m.n % 4) fail(SEM_EUNSUPPORTED, "table-free gather: bad order");
     const StructMap sm{m.erec, m.pos_tab, m.P3, 6 + edge_slots(m.N), m.p3_magic, m.p3_shift};
-    const int nb = update_blocks(m, sizeof(T) == 8);
+    const int nb = update_blocks(m, sizeof(T) == 8, pc.minv != nullptr);
     if (pc.minv)
         hipLaunchKernelGGL((update_struct_kernel<T, true>), dim3(nb), dim3(kVecThreads), 0, s,
                            m.n, r, wg, sm, st, partial, pc);
     else
         hipLaunchKernelGGL((update_struct_kernel<T, false>), dim3(nb), dim3(kVecThreads), 0, s,
                            m.n, r, wg, sm, st, partial, pc);
-    if (!m.inline_scalars(sizeof(T) == 8))
+    if (!m.inline_scalars(sizeof(T) == 8, pc.minv != nullptr))
         hipLaunchKernelGGL(finalize_rho_kernel, dim3(1), dim3(kFinalizeThreads), 0, s, st,
                        (const double *)partial, nb, (const double *)pc.partial2);
     check_hip(hipGetLastError(), "update kernel launch");
@@ -331,7 +331,7 @@ template <typename T, bool PC, int TASKS>
 void update_direct_form(const Mesh &m, bool table_free, T *r, const T *w, CgState *st,
                         double *partial, hipStream_t s, const PcArgs<T> &pc,
                         const DirectArgs<T> &dir) {
-    const int nb = update_blocks(m, sizeof(T) == 8);
+    const int nb = update_blocks(m, sizeof(T) == 8, pc.minv != nullptr);
     if (table_free) {
         const StructMap sm{m.erec, m.pos_tab, m.P3, 6 + edge_slots(m.N), m.p3_magic, m.p3_shift};
         hipLaunchKernelGGL((update_struct_direct_kernel<T, PC, TASKS>), dim3(nb),
