@@ -19,9 +19,10 @@
 // itself: a face node adds its partner's w, an edge or vertex node takes its
 // group's sum.  The summed w is never written back, and the results are
 // bitwise those of the three-pass form.
-// Meshes of up to 4 M points (FP64: 2 M) leave rho to the next operator
-// launch, whose blocks each sum the update's partials, and up to 1 M points
-// the update's blocks also each sum alpha and the groups they need: three and
+// Meshes of up to 4 M points (FP64: 2 M; less at some orders, see
+// takes_inline_scalars) leave rho to the next operator launch, whose blocks
+// each sum the update's partials, and up to 1 M points (direct_max_points) the
+// update's blocks also each sum alpha and the groups they need: three and
 // two launches per iteration (DirectArgs; the schedule is the mesh's, batches
 // included, and the sums keep one order, so a batch of either schedule gives
 // the bits of the solo solve).
