@@ -76,9 +76,10 @@ def ax_flops_per_point(N: int, geom: str) -> float:
 
 # the sources of every kernel the committed counter summary describes (the
 # operator, the gathered update and its group sums, the stand-alone
-# gather-scatter)
+# gather-scatter), their headers, and the launch shapes
 COUNTER_SOURCES = ("sem_ax_order.hip", "sem_geom_body.h", "sem_vec.hip", "sem_vec_body.h",
-                   "sem_gs.hip", "sem_gs_body.h")
+                   "sem_gs.hip", "sem_gs_body.h", "sem_reduce.h", "sem_internal.h",
+                   "sem_ax_dispatch.cpp")
 
 
 def src_hash() -> str:
