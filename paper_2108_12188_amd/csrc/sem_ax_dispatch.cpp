@@ -106,6 +106,9 @@ static const Fn64 kFn64[kMaxOrder + 1] = {nullptr,        ax_order_1_f64, ax_ord
 // hold back fewer waves (3 M points, plain operator on the fly: FP64 N = 9
 // 39.6 us with three elements, 29.6 with one; FP32 N = 11 32.2 us with two,
 // 21.3 with one; FP64 N = 7, whose elements are one wave each, 24.1 / 22.9).
+// FP32 N = 1 on the fly takes 32, two waves (us per iteration with 64 and 32:
+// 1.6 M points 37.1, 34.9, 3.4 M 59.2, 58.5, 8 M 129.2, 123.2; stored factors 52.5,
+// 51.4, 96.6, 96.8, 208.9, 211.1).
 // The autotuner (sem_ax_shape_set) overrides them per order, precision
 // and geometric-factor form.
 static const int kEpb32[kMaxOrder + 1] = {0, 64, 28, 16, 5, 7, 5, 4, 3, 1, 1, 1};
@@ -178,7 +181,7 @@ AxShape ax_shape(int N, bool fp64, bool otf, int epb_override) {
         return s;
     }
     int epb = epb_override > 0 ? epb_override : g_epb[otf ? 1 : 0][fp64 ? 1 : 0][N].load();
-    if (epb <= 0) epb = fp64 ? kEpb64[N] : kEpb32[N];
+    if (epb <= 0) epb = fp64 ? kEpb64[N] : N == 1 && otf ? 32 : kEpb32[N];
     // clamp to the kernel limits: 512 threads and 64 KiB of element values in
     // LDS (two tiles; FP32 CG-fused tiles of odd N also stage the next tile's
     // r, p and vertices).  The padding of the tiles comes on top: at most 72 KiB
