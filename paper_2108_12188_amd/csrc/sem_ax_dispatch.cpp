@@ -100,7 +100,7 @@ static const Fn64 kFn64[kMaxOrder + 1] = {nullptr,        ax_order_1_f64, ax_ord
                                           ax_order_6_f64, ax_order_7_f64, ax_order_8_f64,
                                           ax_order_9_f64, ax_order_10_f64, ax_order_11_f64};
 
-// Default elements per block, at most 512 threads and 64 KiB of LDS: a
+// Default elements per block, at most 512 threads and 64 KiB of values in LDS: a
 // multiple of 64 lanes filled as tightly as possible with (i, j) columns,
 // except where one element per block measured faster because its barriers
 // hold back fewer waves (3 M points, plain operator on the fly: FP64 N = 9
